@@ -117,65 +117,150 @@ __device__ __forceinline__ uint32_t *lds_bond(int d, int c)
 // Update the colour-C words of this workgroup's replica (eq. 9), reading the
 // other colour and the couplings from LDS.  The colour is a template
 // argument so that every plane's LDS offset is a compile-time constant.
+// Bound by VALU issue: the multiplies of a 32-site word's eight Philox blocks
+// alone take 128 x 4.3 cycles of its SIMD, its other ~260 instructions as
+// much again where they pair perfectly (ea_device.h), 1110 cycles in all.
+// Measured per half-step on a full CU: L = 64 9.3 us (1390 cycles per word
+// and wave; 11.35 before the multiplies, compares and XORs ran in phases and
+// the addresses advanced with z), L = 48 4.5 (5.43), L = 32 1.63 (1.81),
+// L = 24 1.05 (1.16).
 template <int L, int RW, int SEL, int C>
 __device__ __forceinline__ void batch_half_step(const BatchJobDev &J, int r, uint32_t t)
 {
     using S = Shape<L, RW>;
     constexpr int W = S::W;
     constexpr int c = C;
-    uint32_t *own = lds_spin<S>(c);
-    const uint32_t *oth = lds_spin<S>(c ^ 1);
-    const uint32_t *bx_own = lds_bond<S>(0, c), *by_own = lds_bond<S>(1, c), *bz_own = lds_bond<S>(2, c);
-    const uint32_t *bx_oth = lds_bond<S>(0, c ^ 1), *by_oth = lds_bond<S>(1, c ^ 1),
-                   *bz_oth = lds_bond<S>(2, c ^ 1);
-    const uint32_t c2 = counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r);
+    const PhiloxStep step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
     // Recompute the addresses every half-step: hoisting them out of the
     // sweep loop would keep some thirty address registers live and spill.
     int tid = (int)threadIdx.x;
     asm volatile("" : "+v"(tid));
-    // Each thread keeps one (y, w) column of the z-planes and walks z in
-    // steps of nt / PLANE (threads past the last whole column stay idle), so
-    // the y and x neighbour offsets are computed once per half-step.  One
+    // Each thread keeps one (y, w) column and walks nz consecutive z-planes
+    // of it (threads past the last whole column stay idle): the y and x
+    // neighbour offsets are computed once per half-step, the word above
+    // becomes the next word, and the addresses advance by one plane.  One
     // word at a time: a word already carries W/4 independent Philox blocks of
     // instruction-level parallelism, and unrolling further spills.
     constexpr unsigned PLANE = (unsigned)(L * RW);
-    const unsigned q = (unsigned)tid % PLANE;
+    const unsigned groups = (unsigned)J.nt / PLANE, nz = ((unsigned)L + groups - 1) / groups;
+    const unsigned q = (unsigned)tid % PLANE, zg = (unsigned)tid / PLANE;
+    if (zg >= groups) return;
     const unsigned w = q % RW;
     const unsigned y = q / RW;
-    const unsigned dz = (unsigned)J.nt / PLANE;
-    const unsigned z_first = (unsigned)tid < dz * PLANE ? (unsigned)tid / PLANE : (unsigned)L;
-    const unsigned qm = q - w + (w == 0 ? RW - 1 : w - 1);  // word w - 1 of the row (cyclic)
-    const unsigned qp = q - w + (w == RW - 1 ? 0 : w + 1);  // word w + 1
-    const unsigned qym = (y == 0 ? L - 1 : y - 1) * RW + w;
-    const unsigned qyp = (y == L - 1 ? 0 : y + 1) * RW + w;
-    const unsigned par0 = (y + (unsigned)c) & 1u;
-    const unsigned quad_col = (y * S::R + w * W) >> 2;  // y R + w W is a multiple of 4
+    unsigned z = zg * nz;
+    const unsigned z_end = min(z + nz, (unsigned)L);
+    if constexpr (PLANE % 64 == 0) z = (unsigned)__builtin_amdgcn_readfirstlane((int)z);  // whole waves share a plane
+    if (z >= z_end) return;
+    // byte offsets from the word to the row's neighbour words (RW > 1) and rows
+    const int qm = 4 * (w == 0 ? RW - 1 : -1), qp = 4 * (w == RW - 1 ? 1 - RW : 1);
+    const int qym = 4 * (y == 0 ? (L - 1) * RW : -RW), qyp = 4 * (y == L - 1 ? -(L - 1) * RW : RW);
+    uint32_t odd = 0u - ((y + z + (unsigned)c) & 1u);  // all ones where x = 2 xh + 1
+    // counter word 1 of the word's first block: (row R + w W) / 4, row = y + L z
+    uint32_t quad0 = ((y * S::R + w * W) >> 2) + z * (unsigned)(L * S::R / 4);
+    // The word's place in the spin and x-coupling planes (lo) and in the y-
+    // and z-coupling planes (hi); two addresses, because one LDS access
+    // reaches 64 KiB from its address register.
+    constexpr int STEP = 4 * (int)PLANE;
+    const int p0 = 4 * (int)(z * PLANE + q), below = z == 0 ? (L - 1) * STEP : -STEP;
+    char *lo = reinterpret_cast<char *>(batch_lds) + p0;
+    const char *hi = reinterpret_cast<char *>(batch_lds) + 16 * S::POS + p0;
+    const char *hi_zm = hi + below, *lo_yp = lo + qyp, *lo_ym = lo + qym, *hi_ym = hi + qym;
+    auto spin = [](const char *a, int col) { return *reinterpret_cast<const uint32_t *>(a + 4 * col * S::POS); };
+    auto xbond = [](const char *a, int col) { return *reinterpret_cast<const uint32_t *>(a + 4 * (2 + col) * S::POS); };
+    auto ybond = [](const char *a, int col) { return *reinterpret_cast<const uint32_t *>(a + 4 * col * S::POS); };
+    auto zbond = [](const char *a, int col) { return *reinterpret_cast<const uint32_t *>(a + 4 * (2 + col) * S::POS); };
+    constexpr int o = c ^ 1;
+    uint32_t O = spin(lo, o), Zm = spin(lo + below, o);
 #pragma unroll 1
-    for (unsigned z = z_first; z < (unsigned)L; z += dz) {
-        const unsigned base = z * PLANE;
-        const unsigned p = base + q;
-        const int par = (int)((par0 ^ z) & 1u);
-        const unsigned zm = (z == 0 ? L - 1 : z - 1) * PLANE + q, zp = (z == L - 1 ? 0 : z + 1) * PLANE + q;
-        const uint32_t S0 = own[p];
-        const uint32_t O = oth[p], Om = oth[base + qm], Op = oth[base + qp];
-        const uint32_t Xo = bx_oth[p], Xom = bx_oth[base + qm];
-        const uint32_t xp = par ? take_plus1<W>(O, Op) : O;
-        const uint32_t xm = par ? (O ^ Xo) : take_minus1<W>(O ^ Xo, Om ^ Xom);
-        const uint32_t a1 = S0 ^ xp ^ bx_own[p];
-        const uint32_t a2 = S0 ^ xm;
-        const uint32_t a3 = xor3(S0, oth[base + qyp], by_own[p]);
-        const uint32_t a4 = xor3(S0, oth[base + qym], by_oth[base + qym]);
-        const uint32_t a5 = xor3(S0, oth[zp], bz_own[p]);
-        const uint32_t a6 = xor3(S0, oth[zm], bz_oth[zm]);
-        const Decision d = classify(a1, a2, a3, a4, a5, a6);
-        const uint32_t quad0 = quad_col + ((z * (unsigned)(L * S::R)) >> 2);  // (row R + w W) / 4, row = y + L z
+    for (; z < z_end; ++z) {
+        char *lo_zp = lo + (z == L - 1 ? -(L - 1) * STEP : STEP);
+        const uint32_t S0 = spin(lo, c), Zp = spin(lo_zp, o);
+        const uint32_t Om = RW == 1 ? O : spin(lo + qm, o), Op = RW == 1 ? O : spin(lo + qp, o);
+        const uint32_t Xo = xbond(lo, o), Xom = RW == 1 ? Xo : xbond(lo + qm, o);
+        const uint32_t Bx = xbond(lo, c), By = ybond(hi, c), Bz = zbond(hi, c);
+        const uint32_t Yp = spin(lo_yp, o), Ym = spin(lo_ym, o), Bym = ybond(hi_ym, o), Bzm = zbond(hi_zm, o);
+        auto decide = [&]() {
+            // x neighbours: +x shares xh on even rows and sits at xh + 1 on
+            // odd ones, -x at xh - 1 on even rows and shares xh on odd ones
+            const uint32_t xp = __builtin_amdgcn_bitop3_b32(odd, take_plus1<W>(O, Op), O, kBitopSelect);
+            const uint32_t xm = __builtin_amdgcn_bitop3_b32(odd, O ^ Xo, take_minus1<W>(O ^ Xo, Om ^ Xom), kBitopSelect);
+            return classify(xor3(S0, xp, Bx), S0 ^ xm, xor3(S0, Yp, By), xor3(S0, Ym, Bym), xor3(S0, Zp, Bz),
+                            xor3(S0, Zm, Bzm));
+        };
         uint32_t flips;
         if constexpr (SEL == SEL_LDS)
-            flips = flip_mask_lds<W>(d, t, quad0, c2, J.sample, J.k0, J.k1, batch_tables());
+            flips = flip_mask_lds<W>(step, quad0, batch_tables(), decide);
         else
-            flips = flip_mask<W>(d, t, quad0, c2, J.sample, J.k0, J.k1, J.thr1, J.thr2, J.thr3);
-        own[p] = S0 ^ flips;
+            flips = flip_mask<W>(decide(), step, quad0, J.thr1, J.thr2, J.thr3);
+        *reinterpret_cast<uint32_t *>(lo + 4 * c * S::POS) = S0 ^ flips;
+        lo = lo_zp;
+        hi_zm = hi;
+        hi += STEP;
+        lo_yp += STEP;
+        lo_ym += STEP;
+        hi_ym += STEP;
+        Zm = O;
+        O = Zp;
+        odd = ~odd;
+        quad0 += (uint32_t)(L * S::R / 4);
     }
+}
+
+// Between half-steps.  A wave's half-step reads the words of its own planes
+// and of the planes next to them, so it only has to follow the waves that own
+// those: every wave counts its finished half-steps in LDS and starts the next
+// one when the waves of its neighbourhood have finished as many.  A neighbour
+// is then at most one half-step away, so no word is overwritten that a wave
+// still reads, and waves further apart may drift.  Against a workgroup
+// barrier, where the SIMD with the most waves sets the pace and its last wave
+// runs alone, at a fraction of the issue rate: L = 24 (nine waves) 1.02
+// against 1.13 us per half-step, L = 40 3.25 / 3.42, L = 48 4.49 / 4.58,
+// L = 56 8.15 / 8.53; but L = 64, whose sixteen waves load the four SIMDs
+// evenly, 9.51 / 9.36: where a plane is whole waves the barrier stays.
+template <int L, int RW>
+constexpr bool kBatchDrift = (L * RW) % 64 != 0;
+
+constexpr int kBatchWaves = kBatchThreads / 64;
+__shared__ uint32_t batch_progress[kBatchWaves];
+
+// Waves whose planes touch those of this wave (bit v: wave v), itself left
+// out; nt threads work, nz planes each (batch_half_step).
+template <int L, int RW>
+__device__ __forceinline__ uint32_t batch_neighbours(int nt)
+{
+    constexpr int PLANE = L * RW;
+    const int nz = (L + nt / PLANE - 1) / (nt / PLANE), G = (L + nz - 1) / nz;  // plane groups in use
+    const int lane = (int)(threadIdx.x & 63), me = (int)(threadIdx.x >> 6);
+    const int a0 = 64 * me / PLANE, b0 = min((64 * me + 63) / PLANE, G - 1);
+    const int a1 = 64 * lane / PLANE, b1 = min((64 * lane + 63) / PLANE, G - 1);
+    bool near = false;
+#pragma unroll
+    for (int k = -1; k <= 1; ++k) near |= a1 + k * G <= b0 + 1 && b1 + k * G >= a0 - 1;
+    near = near && a0 < G && a1 < G && lane != me && lane < nt / 64;
+    return (uint32_t)__ballot(near);
+}
+
+template <bool DRIFT>
+__device__ __forceinline__ void batch_wait(uint32_t neighbours, uint32_t done)
+{
+    if constexpr (!DRIFT) return;  // batch_done was a barrier
+    for (;;) {
+        const uint32_t p = __hip_atomic_load(batch_progress + (threadIdx.x & (kBatchWaves - 1)), __ATOMIC_ACQUIRE,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (((uint32_t)__ballot((int)(p - done) < 0) & neighbours) == 0) return;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+template <bool DRIFT>
+__device__ __forceinline__ void batch_done(uint32_t done)
+{
+    if constexpr (!DRIFT) {
+        __syncthreads();
+        return;
+    }
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_store(batch_progress + (threadIdx.x >> 6), done, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Copy this replica's two colour planes between LDS and a global array.
@@ -301,6 +386,24 @@ __device__ void batch_measure(const BatchJobDev &J, int r, int m, int n_taken)
     batch_publish_and_pair<L, RW>(J, r, m, 0, L * L, POS, S::LATTICE_WORDS);
 }
 
+// Sweeps t .. t_end - 1; done counts the half-steps of the unit so far.
+template <int L, int RW, int SEL>
+__device__ __forceinline__ void batch_sweeps(const BatchJobDev &J, int r, uint32_t t, uint32_t t_end,
+                                             uint32_t neighbours, uint32_t &done)
+{
+    constexpr bool D = kBatchDrift<L, RW>;
+    for (; t < t_end; ++t) {
+        batch_wait<D>(neighbours, done);
+        if (r == 0) batch_half_step<L, RW, SEL, 0>(J, r, t);
+        else batch_half_step<L, RW, SEL, 1>(J, r, t);
+        batch_done<D>(++done);
+        batch_wait<D>(neighbours, done);
+        if (r == 0) batch_half_step<L, RW, SEL, 1>(J, r, t);
+        else batch_half_step<L, RW, SEL, 0>(J, r, t);
+        batch_done<D>(++done);
+    }
+}
+
 // Run one unit: load the replica and the couplings into LDS, sweep up to
 // t_stop taking the events scheduled in (t0, t_stop] (and at t0 itself on the
 // job's first span), then write the replica back.
@@ -316,13 +419,15 @@ __device__ void batch_run_unit(const BatchJobDev &J, int r, uint32_t t_stop, boo
     for (int i = (int)threadIdx.x; i < 2 * S::POS; i += nt) batch_lds[i] = src[i];
     for (int i = (int)threadIdx.x; i < 6 * S::POS; i += nt) batch_lds[2 * S::POS + i] = J.bonds[i];
     if constexpr (SEL == SEL_LDS) fill_select_tables(batch_tables(), J.thr1, J.thr2, J.thr3, (int)threadIdx.x, nt);
+    if (threadIdx.x < kBatchWaves) batch_progress[threadIdx.x] = 0;
     __syncthreads();
 
     int im = 0, iw = 0;
     while (im < J.n_meas && (J.meas_t[im] < t0 || (!first && J.meas_t[im] == t0))) ++im;
     while (iw < J.n_tw && (J.tw_t[iw] < t0 || (!first && J.tw_t[iw] == t0))) ++iw;
 
-    uint32_t t = t0;
+    const uint32_t neighbours = batch_neighbours<L, RW>(nt);
+    uint32_t t = t0, done = 0;
     for (;;) {
         if (iw < J.n_tw && J.tw_t[iw] == t) {
             batch_store_spins<S>(J.snaps + ((size_t)iw * 2 + (size_t)r) * 2 * S::POS, nt);
@@ -336,17 +441,13 @@ __device__ void batch_run_unit(const BatchJobDev &J, int r, uint32_t t_stop, boo
             __syncthreads();
         }
         if (t >= t_stop) break;
-        if (r == 0) {
-            batch_half_step<L, RW, SEL, 0>(J, r, t);
-            __syncthreads();
-            batch_half_step<L, RW, SEL, 1>(J, r, t);
-        } else {
-            batch_half_step<L, RW, SEL, 1>(J, r, t);
-            __syncthreads();
-            batch_half_step<L, RW, SEL, 0>(J, r, t);
-        }
+        // to the next event or the end
+        uint32_t t_next = t_stop;
+        if (iw < J.n_tw) t_next = min(t_next, J.tw_t[iw]);
+        if (im < J.n_meas) t_next = min(t_next, J.meas_t[im]);
+        batch_sweeps<L, RW, SEL>(J, r, t, t_next, neighbours, done);
+        t = t_next;
         __syncthreads();
-        ++t;
     }
     batch_store_spins<S>(J.spins + (size_t)r * 2 * S::POS, nt);
     if (threadIdx.x == 0) J.t_now[r] = t;
@@ -478,7 +579,7 @@ __device__ __forceinline__ bool slab_wait_words(unsigned long long *pub, unsigne
 // New value of slab word p (colour c, sweep t), given its z-1 and z+1
 // neighbour words of the other colour and the coupling to the z-1 neighbour.
 template <int L, int RW, int SEL>
-__device__ __forceinline__ uint32_t slab_new_word(const BatchJobDev &J, int r, int c, uint32_t t, int z0, int p,
+__device__ __forceinline__ uint32_t slab_new_word(const BatchJobDev &J, const PhiloxStep &step, int c, int z0, int p,
                                                   uint32_t Ozm, uint32_t Ozp, uint32_t Bzm)
 {
     using S = Slab<L, RW>;
@@ -499,22 +600,21 @@ __device__ __forceinline__ uint32_t slab_new_word(const BatchJobDev &J, int r, i
     const uint32_t S0 = own[p];
     const uint32_t O = oth[base + w], Om = oth[base + wm], Op = oth[base + wp];
     const uint32_t Xo = bx_oth[base + w], Xom = bx_oth[base + wm];
-    const uint32_t xp = par ? take_plus1<W>(O, Op) : O;
-    const uint32_t xm = par ? (O ^ Xo) : take_minus1<W>(O ^ Xo, Om ^ Xom);
-    const uint32_t a1 = S0 ^ xp ^ bx_own[p];
-    const uint32_t a2 = S0 ^ xm;
-    const uint32_t a3 = xor3(S0, oth[yp * RW + w], by_own[p]);
-    const uint32_t a4 = xor3(S0, oth[ym * RW + w], by_oth[ym * RW + w]);
-    const uint32_t a5 = xor3(S0, Ozp, bz_own[p]);
-    const uint32_t a6 = xor3(S0, Ozm, Bzm);
-    const Decision d = classify(a1, a2, a3, a4, a5, a6);
+    const uint32_t Bx = bx_own[p], By = by_own[p], Bz = bz_own[p];
+    const uint32_t Yp = oth[yp * RW + w], Ym = oth[ym * RW + w], Bym = by_oth[ym * RW + w];
+    auto decide = [&]() {
+        const uint32_t odd = 0u - (uint32_t)par;
+        const uint32_t xp = __builtin_amdgcn_bitop3_b32(odd, take_plus1<W>(O, Op), O, kBitopSelect);
+        const uint32_t xm = __builtin_amdgcn_bitop3_b32(odd, O ^ Xo, take_minus1<W>(O ^ Xo, Om ^ Xom), kBitopSelect);
+        return classify(xor3(S0, xp, Bx), S0 ^ xm, xor3(S0, Yp, By), xor3(S0, Ym, Bym), xor3(S0, Ozp, Bz),
+                        xor3(S0, Ozm, Bzm));
+    };
     const uint32_t quad0 = (uint32_t)(((row + (unsigned)(L * z0)) * S::R + w * W) >> 2);
-    const uint32_t c2 = counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r);
     uint32_t flips;
     if constexpr (SEL == SEL_LDS)
-        flips = flip_mask_lds<W>(d, t, quad0, c2, J.sample, J.k0, J.k1, batch_tables());
+        flips = flip_mask_lds<W>(step, quad0, batch_tables(), decide);
     else
-        flips = flip_mask<W>(d, t, quad0, c2, J.sample, J.k0, J.k1, J.thr1, J.thr2, J.thr3);
+        flips = flip_mask<W>(decide(), step, quad0, J.thr1, J.thr2, J.thr3);
     return S0 ^ flips;
 }
 
@@ -531,11 +631,12 @@ __device__ __forceinline__ bool slab_half_step(const BatchJobDev &J, int r, int 
     const uint32_t *bz_oth = slab_bond<S>(2, c ^ 1);
     int tid = (int)threadIdx.x;
     asm volatile("" : "+v"(tid));
+    const PhiloxStep step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
     if (tid >= 64) {
         // interior planes 1 .. NZ-2
 #pragma unroll 1
         for (int p = S::PL + tid - 64; p < S::SPOS - S::PL; p += J.nt - 64)
-            own[p] = slab_new_word<L, RW, SEL>(J, r, c, t, z0, p, oth[p - S::PL], oth[p + S::PL], bz_oth[p - S::PL]);
+            own[p] = slab_new_word<L, RW, SEL>(J, step, c, z0, p, oth[p - S::PL], oth[p + S::PL], bz_oth[p - S::PL]);
         return true;
     }
     if (!slab_wait_words(J.pub + 2 * r + (slab ^ 1), want)) return false;
@@ -553,9 +654,9 @@ __device__ __forceinline__ bool slab_half_step(const BatchJobDev &J, int r, int 
         const int p = k ? S::SPOS - S::PL + j : j;
         uint32_t v;
         if (k == 0)
-            v = slab_new_word<L, RW, SEL>(J, r, c, t, z0, p, load_agent(part_last + j), oth[p + S::PL], halo_bz[j]);
+            v = slab_new_word<L, RW, SEL>(J, step, c, z0, p, load_agent(part_last + j), oth[p + S::PL], halo_bz[j]);
         else
-            v = slab_new_word<L, RW, SEL>(J, r, c, t, z0, p, oth[p - S::PL], load_agent(part_first + j),
+            v = slab_new_word<L, RW, SEL>(J, step, c, z0, p, oth[p - S::PL], load_agent(part_first + j),
                                           bz_oth[p - S::PL]);
         own[p] = v;
         store_agent(slab_xbuf<S>(J, r, slab, wslot, c, k) + j, v);

@@ -65,56 +65,177 @@ constexpr bool kQuadOr = ((W / 4) & (W / 4 - 1)) == 0;
 
 constexpr int kBitopOrXor = 0x56;  // (src0 | src1) ^ src2, bitwise
 
-// Two blocks whose counters differ only in word 1 (quad0 + Ja, quad0 + Jb),
-// computed round by round side by side: the two dependency chains
-// interleave, so each round's multiplies of one block issue while the
-// other's are in flight.  In the first round words 0, 2, 3 and the key are
-// uniform across the wavefront, so only the word-1 XOR is per lane.
-template <bool ORQ>
-__device__ __forceinline__ void philox10_pair(uint32_t x0, uint32_t quad0, uint32_t Ja, uint32_t Jb, uint32_t x2,
-                                              uint32_t x3, uint32_t k0, uint32_t k1, Words4 &a, Words4 &b)
+// How a gfx950 SIMD issues (probed with one instruction class at a time and
+// mixed, two to eight waves per SIMD; cycles per wave instruction at 2.4 GHz):
+// additions, right shifts and bitwise operations whose operands are VGPRs or
+// constants issue from two waves at once (2.3); compares, carries, selects
+// and any operation that reads an SGPR do not pair with each other (4.3) but
+// do pair with one of the first kind; the 32 x 32 -> 64-bit multiply-add
+// (4.3) pairs with nothing.  The oldest wave goes first, so waves that mix
+// the kinds freely hardly ever meet at a pair (alternating multiply-adds and
+// XORs: 4.25 each, as if nothing paired).  Raising a wave's priority while it
+// runs its multiplies or compares lets the waves catch up there and meet in
+// their XORs: 3.4 each at four waves.  Hence the phases below, and the round
+// keys and the wavefront-uniform words of the first rounds in VGPRs.
+// The multiplies of a phase are one asm block between its two priority
+// changes (the compiler would move plain multiplies across them).
+#define EA_MAD(d, x, m) "v_mad_u64_u32 %" d ", vcc, %" x ", %" m ", 0\n\t"
+#define EA_MULS_BEGIN "s_setprio 2\n\t"
+#define EA_MULS_END "s_setprio 0"
+
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM2 = 0xCD9E8D57u;
+constexpr uint32_t kPhiloxK0 = 0x9E3779B9u, kPhiloxK1 = 0xBB67AE85u;
+
+// p[g] = x[g] M
+template <int G>
+__device__ __forceinline__ void mul_phase(uint64_t (&p)[G], const uint32_t (&x)[G], uint32_t M)
 {
-    const uint64_t n0 = (uint64_t)x0 * 0xD2511F53u;
-    const uint64_t n2 = (uint64_t)x2 * 0xCD9E8D57u;
-    const uint32_t h = (uint32_t)(n2 >> 32) ^ k0;
-    uint32_t a0, b0;
-    if constexpr (ORQ) {
-        a0 = __builtin_amdgcn_bitop3_b32(quad0, Ja, h, kBitopOrXor);
-        b0 = __builtin_amdgcn_bitop3_b32(quad0, Jb, h, kBitopOrXor);
-    } else {
-        a0 = (quad0 + Ja) ^ h;
-        b0 = (quad0 + Jb) ^ h;
-    }
-    uint32_t a1 = (uint32_t)n2, a2 = xor3((uint32_t)(n0 >> 32), x3, k1), a3 = (uint32_t)n0;
-    uint32_t b1 = a1, b2 = a2, b3 = a3;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-#pragma unroll
-    for (int round = 1; round < 10; ++round) {
-        const uint64_t ma0 = (uint64_t)a0 * 0xD2511F53u, mb0 = (uint64_t)b0 * 0xD2511F53u;
-        const uint64_t ma2 = (uint64_t)a2 * 0xCD9E8D57u, mb2 = (uint64_t)b2 * 0xCD9E8D57u;
-        const uint32_t ya0 = xor3((uint32_t)(ma2 >> 32), a1, k0), yb0 = xor3((uint32_t)(mb2 >> 32), b1, k0);
-        const uint32_t ya2 = xor3((uint32_t)(ma0 >> 32), a3, k1), yb2 = xor3((uint32_t)(mb0 >> 32), b3, k1);
-        a1 = (uint32_t)ma2;
-        b1 = (uint32_t)mb2;
-        a3 = (uint32_t)ma0;
-        b3 = (uint32_t)mb0;
-        a0 = ya0;
-        b0 = yb0;
-        a2 = ya2;
-        b2 = yb2;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
-    }
-    a.v[0] = a0;
-    a.v[1] = a1;
-    a.v[2] = a2;
-    a.v[3] = a3;
-    b.v[0] = b0;
-    b.v[1] = b1;
-    b.v[2] = b2;
-    b.v[3] = b3;
+    static_assert(G >= 1 && G <= 4, "blocks side by side");
+    if constexpr (G == 1)
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "1", "2") EA_MULS_END : "=&v"(p[0]) : "v"(x[0]), "s"(M) : "vcc");
+    else if constexpr (G == 2)
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "2", "4") EA_MAD("1", "3", "4") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(p[1])
+                     : "v"(x[0]), "v"(x[1]), "s"(M)
+                     : "vcc");
+    else if constexpr (G == 3)
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "3", "6") EA_MAD("1", "4", "6") EA_MAD("2", "5", "6") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2])
+                     : "v"(x[0]), "v"(x[1]), "v"(x[2]), "s"(M)
+                     : "vcc");
+    else
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "4", "8") EA_MAD("1", "5", "8") EA_MAD("2", "6", "8")
+                         EA_MAD("3", "7", "8") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3])
+                     : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(M)
+                     : "vcc");
 }
+
+// p[g] = x[g] M0 and r[g] = y[g] M2
+template <int G>
+__device__ __forceinline__ void mul_phase(uint64_t (&p)[G], const uint32_t (&x)[G], uint64_t (&r)[G],
+                                          const uint32_t (&y)[G])
+{
+    static_assert(G >= 1 && G <= 4, "blocks side by side");
+    if constexpr (G == 1)
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "2", "4") EA_MAD("1", "3", "5") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(r[0])
+                     : "v"(x[0]), "v"(y[0]), "s"(kPhiloxM0), "s"(kPhiloxM2)
+                     : "vcc");
+    else if constexpr (G == 2)
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "4", "8") EA_MAD("1", "5", "8") EA_MAD("2", "6", "9")
+                         EA_MAD("3", "7", "9") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(p[1]), "=&v"(r[0]), "=&v"(r[1])
+                     : "v"(x[0]), "v"(x[1]), "v"(y[0]), "v"(y[1]), "s"(kPhiloxM0), "s"(kPhiloxM2)
+                     : "vcc");
+    else if constexpr (G == 3)
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "6", "12") EA_MAD("1", "7", "12") EA_MAD("2", "8", "12")
+                         EA_MAD("3", "9", "13") EA_MAD("4", "10", "13") EA_MAD("5", "11", "13") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2])
+                     : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(y[0]), "v"(y[1]), "v"(y[2]), "s"(kPhiloxM0),
+                       "s"(kPhiloxM2)
+                     : "vcc");
+    else
+        asm volatile(EA_MULS_BEGIN EA_MAD("0", "8", "16") EA_MAD("1", "9", "16") EA_MAD("2", "10", "16")
+                         EA_MAD("3", "11", "16") EA_MAD("4", "12", "17") EA_MAD("5", "13", "17")
+                             EA_MAD("6", "14", "17") EA_MAD("7", "15", "17") EA_MULS_END
+                     : "=&v"(p[0]), "=&v"(p[1]), "=&v"(p[2]), "=&v"(p[3]), "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]),
+                       "=&v"(r[3])
+                     : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]),
+                       "s"(kPhiloxM0), "s"(kPhiloxM2)
+                     : "vcc");
+}
+#undef EA_MAD
+
+// A wavefront-uniform value held in a VGPR.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+
+// The uniform part of the blocks of one half-step: counter words 0, 2, 3 and
+// the key are the same for every lane, so only word 1's path is per lane in
+// the first rounds (word 0 from round 1 on, word 2 from round 2 on, all four
+// from round 4 on).  Rounds are numbered from 0.
+struct PhiloxStep {
+    uint32_t h;           // round 0: word 0 = counter word 1 ^ h
+    uint32_t e1;          // round 1: word 2 = hi(m0) ^ e1
+    uint32_t e2, e3;      // round 2: word 0 = hi(m2) ^ e2, word 2 = word 3 ^ e3
+    uint32_t e4;          // round 3: word 2 = hi(m0) ^ e4
+    uint32_t k0, k1;      // keys of round 3
+};
+
+__device__ __forceinline__ PhiloxStep philox_step(uint32_t x0, uint32_t x2, uint32_t x3, uint32_t k0, uint32_t k1)
+{
+    const uint64_t n0 = (uint64_t)x0 * kPhiloxM0, n2 = (uint64_t)x2 * kPhiloxM2;
+    const uint32_t b2 = (uint32_t)(n0 >> 32) ^ x3 ^ k1;                      // word 2 after round 0
+    const uint64_t p2 = (uint64_t)b2 * kPhiloxM2;                            // round 1
+    const uint32_t c0 = (uint32_t)(p2 >> 32) ^ (uint32_t)n2 ^ (k0 + kPhiloxK0);  // word 0 after round 1
+    const uint64_t q0 = (uint64_t)c0 * kPhiloxM0;                            // round 2
+    PhiloxStep s;
+    s.h = in_vgpr((uint32_t)(n2 >> 32) ^ k0);
+    s.e1 = in_vgpr((uint32_t)n0 ^ (k1 + kPhiloxK1));
+    s.e2 = in_vgpr((uint32_t)p2 ^ (k0 + 2 * kPhiloxK0));
+    s.e3 = in_vgpr((uint32_t)(q0 >> 32) ^ (k1 + 2 * kPhiloxK1));
+    s.e4 = in_vgpr((uint32_t)q0 ^ (k1 + 3 * kPhiloxK1));
+    s.k0 = in_vgpr(k0 + 3 * kPhiloxK0);
+    s.k1 = in_vgpr(k1 + 3 * kPhiloxK1);
+    return s;
+}
+
+// Blocks J, J - 1, ... J - G + 1 of a word side by side, round by round: each
+// round's 2 G multiplies, then its 2 G XORs and the next keys.
+template <int G, bool ORQ>
+__device__ __forceinline__ void philox10_group(const PhiloxStep &s, uint32_t quad0, int J, Words4 (&w)[G])
+{
+    uint32_t x0[G], x1[G], x2[G], x3[G];
+    uint64_t m0[G], m2[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const uint32_t j = (uint32_t)(J - g);
+        x0[g] = ORQ ? __builtin_amdgcn_bitop3_b32(quad0, j, s.h, kBitopOrXor) : ((quad0 + j) ^ s.h);
+    }
+    mul_phase(m0, x0, kPhiloxM0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        x2[g] = (uint32_t)(m0[g] >> 32) ^ s.e1;
+        x3[g] = (uint32_t)m0[g];
+    }
+    mul_phase(m2, x2, kPhiloxM2);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        x0[g] = (uint32_t)(m2[g] >> 32) ^ s.e2;
+        x1[g] = (uint32_t)m2[g];
+        x2[g] = x3[g] ^ s.e3;
+    }
+    uint32_t k0 = s.k0, k1 = s.k1;
+#pragma unroll
+    for (int round = 3; round < 10; ++round) {
+        mul_phase(m0, x0, m2, x2);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            x0[g] = xor3((uint32_t)(m2[g] >> 32), x1[g], k0);
+            x2[g] = round == 3 ? (uint32_t)(m0[g] >> 32) ^ s.e4 : xor3((uint32_t)(m0[g] >> 32), x3[g], k1);
+            x1[g] = (uint32_t)m2[g];
+            x3[g] = (uint32_t)m0[g];
+        }
+        k0 += kPhiloxK0;
+        k1 += kPhiloxK1;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        w[g].v[0] = x0[g];
+        w[g].v[1] = x1[g];
+        w[g].v[2] = x2[g];
+        w[g].v[3] = x3[g];
+    }
+}
+
+// Blocks taken together when n are left: at most four, and never all of a
+// word's, so that its lattice reads and its table reads each have a group's
+// rounds to arrive in.
+constexpr int philox_group(int n) { return n >= 7 ? 4 : (n >= 5 ? 3 : (n >= 3 ? 2 : n)); }
 
 enum : uint32_t { TAG_METRO = 0u, TAG_BOND = 1u, TAG_INIT = 2u };
 
@@ -189,6 +310,13 @@ __device__ __forceinline__ int wrap(int v, int L)
 // thr1, thr2, thr3.  The counter is reduced with two full adders:
 // n = s + 2 (c0 + c1 + c2), so "any" = (c0|c1|c2) means n >= 2 and
 // "always" = maj(c0,c1,c2) | (any & s) means n >= 3.
+constexpr int kBitopMaj = 0xE8, kBitopOr3 = 0xFE, kBitopOrAnd = 0xF8;  // 0xF8: src0 | (src1 & src2)
+
+__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, kBitopMaj);
+}
+
 struct Decision {
     uint32_t always;  // n >= 3
     uint32_t any;     // n >= 2
@@ -198,18 +326,14 @@ struct Decision {
 __device__ __forceinline__ Decision classify(uint32_t a1, uint32_t a2, uint32_t a3, uint32_t a4,
                                              uint32_t a5, uint32_t a6)
 {
-    const uint32_t s1 = xor3(a1, a2, a3);
-    const uint32_t c1 = (a1 & a2) | (a3 & (a1 | a2));
-    const uint32_t s2 = xor3(a4, a5, a6);
-    const uint32_t c2 = (a4 & a5) | (a6 & (a4 | a5));
+    const uint32_t s1 = xor3(a1, a2, a3), c1 = maj3(a1, a2, a3);
+    const uint32_t s2 = xor3(a4, a5, a6), c2 = maj3(a4, a5, a6);
     const uint32_t s = s1 ^ s2;
     const uint32_t c0 = s1 & s2;
-    const uint32_t any = c0 | c1 | c2;
-    const uint32_t two = (c0 & c1) | (c2 & (c0 | c1));
     Decision d;
-    d.any = any;
+    d.any = __builtin_amdgcn_bitop3_b32(c0, c1, c2, kBitopOr3);
     d.odd = s;
-    d.always = two | (any & s);
+    d.always = __builtin_amdgcn_bitop3_b32(maj3(c0, c1, c2), d.any, s, kBitopOrAnd);
     return d;
 }
 
@@ -233,16 +357,47 @@ __device__ __forceinline__ uint32_t append_below4(uint32_t accept, uint32_t u3, 
                                                   uint32_t t0)
 {
     uint64_t m3, m2, m1, m0, co;
-    asm("v_cmp_lt_u32_e64 %1, %6, %7\n\t"
-        "v_cmp_lt_u32_e64 %2, %8, %9\n\t"
-        "v_cmp_lt_u32_e64 %3, %10, %11\n\t"
-        "v_cmp_lt_u32_e64 %4, %12, %13\n\t"
-        "v_addc_co_u32_e64 %0, %5, %0, %0, %1\n\t"
-        "v_addc_co_u32_e64 %0, %5, %0, %0, %2\n\t"
-        "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
-        "v_addc_co_u32_e64 %0, %5, %0, %0, %4"
-        : "+v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
-        : "v"(u3), "v"(t3), "v"(u2), "v"(t2), "v"(u1), "v"(t1), "v"(u0), "v"(t0));
+    asm volatile("s_setprio 1\n\t"
+                 "v_cmp_lt_u32_e64 %1, %6, %7\n\t"
+                 "v_cmp_lt_u32_e64 %2, %8, %9\n\t"
+                 "v_cmp_lt_u32_e64 %3, %10, %11\n\t"
+                 "v_cmp_lt_u32_e64 %4, %12, %13\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %1\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %2\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %4\n\t"
+                 "s_setprio 0"
+                 : "+v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
+                 : "v"(u3), "v"(t3), "v"(u2), "v"(t2), "v"(u1), "v"(t1), "v"(u0), "v"(t0));
+    return accept;
+}
+
+// Two blocks' bits (a above b) in one phase.
+__device__ __forceinline__ uint32_t append_below8(uint32_t accept, const uint32_t (&a)[4], const uint4 &ta,
+                                                  const uint32_t (&b)[4], const uint4 &tb)
+{
+    uint64_t m3, m2, m1, m0, co;
+    asm volatile("s_setprio 1\n\t"
+                 "v_cmp_lt_u32_e64 %1, %6, %7\n\t"
+                 "v_cmp_lt_u32_e64 %2, %8, %9\n\t"
+                 "v_cmp_lt_u32_e64 %3, %10, %11\n\t"
+                 "v_cmp_lt_u32_e64 %4, %12, %13\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %1\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %2\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %4\n\t"
+                 "v_cmp_lt_u32_e64 %1, %14, %15\n\t"
+                 "v_cmp_lt_u32_e64 %2, %16, %17\n\t"
+                 "v_cmp_lt_u32_e64 %3, %18, %19\n\t"
+                 "v_cmp_lt_u32_e64 %4, %20, %21\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %1\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %2\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
+                 "v_addc_co_u32_e64 %0, %5, %0, %0, %4\n\t"
+                 "s_setprio 0"
+                 : "+v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
+                 : "v"(a[3]), "v"(ta.w), "v"(a[2]), "v"(ta.z), "v"(a[1]), "v"(ta.y), "v"(a[0]), "v"(ta.x),
+                   "v"(b[3]), "v"(tb.w), "v"(b[2]), "v"(tb.z), "v"(b[1]), "v"(tb.y), "v"(b[0]), "v"(tb.x));
     return accept;
 }
 
@@ -265,68 +420,58 @@ __device__ __forceinline__ uint32_t site_threshold(const Decision &d, uint32_t t
                                        kBitopSelect);
 }
 
-// Blocks J = W/4-1 down to 0: block J covers sites 4J..4J+3 and has counter
-// word 1 equal to quad0 + J; words 0, 2, 3 (sweep, tag/colour/replica,
-// sample) are wave-uniform, so the first rounds run largely on the SALU.
-template <int W, int J>
-__device__ __forceinline__ uint32_t accept_blocks(uint32_t accept, const Decision &d, uint32_t c0,
-                                                  uint32_t quad0, uint32_t c2, uint32_t c3, uint32_t k0,
-                                                  uint32_t k1, uint32_t thr1, uint32_t thr2, uint32_t thr3)
+template <int J, int I, int G>
+__device__ __forceinline__ uint32_t append_blocks_reg(uint32_t accept, const Decision &d, const Words4 (&u)[G],
+                                                      uint32_t thr1, uint32_t thr2, uint32_t thr3)
 {
-    if constexpr (J > 0) {
-        // blocks J and J - 1 side by side
-        Words4 u, v;
-        philox10_pair<kQuadOr<W>>(c0, quad0, (uint32_t)J, (uint32_t)(J - 1), c2, c3, k0, k1, u, v);
-        accept = append_below4(accept, u.v[3], site_threshold<4 * J + 3>(d, thr1, thr2, thr3), u.v[2],
-                               site_threshold<4 * J + 2>(d, thr1, thr2, thr3), u.v[1],
-                               site_threshold<4 * J + 1>(d, thr1, thr2, thr3), u.v[0],
-                               site_threshold<4 * J + 0>(d, thr1, thr2, thr3));
-        accept = append_below4(accept, v.v[3], site_threshold<4 * J - 1>(d, thr1, thr2, thr3), v.v[2],
-                               site_threshold<4 * J - 2>(d, thr1, thr2, thr3), v.v[1],
-                               site_threshold<4 * J - 3>(d, thr1, thr2, thr3), v.v[0],
-                               site_threshold<4 * J - 4>(d, thr1, thr2, thr3));
-        if constexpr (J > 1)
-            return accept_blocks<W, J - 2>(accept, d, c0, quad0, c2, c3, k0, k1, thr1, thr2, thr3);
-        else
-            return accept;
-    } else {
-        const Words4 u = philox10(c0, quad0, c2, c3, k0, k1);
-        return append_below4(accept, u.v[3], site_threshold<3>(d, thr1, thr2, thr3), u.v[2],
-                             site_threshold<2>(d, thr1, thr2, thr3), u.v[1], site_threshold<1>(d, thr1, thr2, thr3),
-                             u.v[0], site_threshold<0>(d, thr1, thr2, thr3));
-    }
+    accept = append_below4(accept, u[I].v[3], site_threshold<4 * J + 3>(d, thr1, thr2, thr3), u[I].v[2],
+                           site_threshold<4 * J + 2>(d, thr1, thr2, thr3), u[I].v[1],
+                           site_threshold<4 * J + 1>(d, thr1, thr2, thr3), u[I].v[0],
+                           site_threshold<4 * J>(d, thr1, thr2, thr3));
+    if constexpr (I + 1 < G)
+        return append_blocks_reg<J - 1, I + 1, G>(accept, d, u, thr1, thr2, thr3);
+    else
+        return accept;
+}
+
+// Blocks N-1 down to 0: block J covers sites 4J..4J+3 and has counter word 1
+// equal to quad0 + J.
+template <int W, int N>
+__device__ __forceinline__ uint32_t accept_blocks(uint32_t accept, const Decision &d, const PhiloxStep &s,
+                                                  uint32_t quad0, uint32_t thr1, uint32_t thr2, uint32_t thr3)
+{
+    constexpr int G = philox_group(N);
+    Words4 u[G];
+    philox10_group<G, kQuadOr<W>>(s, quad0, N - 1, u);
+    accept = append_blocks_reg<N - 1, 0, G>(accept, d, u, thr1, thr2, thr3);
+    if constexpr (N > G)
+        return accept_blocks<W, N - G>(accept, d, s, quad0, thr1, thr2, thr3);
+    else
+        return accept;
 }
 
 // Flip mask of one packed word of W sites (bits W..31 stay zero).
 template <int W>
-__device__ __forceinline__ uint32_t flip_mask(const Decision &d, uint32_t c0, uint32_t quad0,
-                                              uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
-                                              uint32_t thr1, uint32_t thr2, uint32_t thr3)
+__device__ __forceinline__ uint32_t flip_mask(const Decision &d, const PhiloxStep &s, uint32_t quad0, uint32_t thr1,
+                                              uint32_t thr2, uint32_t thr3)
 {
-    return d.always | accept_blocks<W, W / 4 - 1>(0u, d, c0, quad0, c2, c3, k0, k1, thr1, thr2, thr3);
+    return d.always | accept_blocks<W, W / 4>(0u, d, s, quad0, thr1, thr2, thr3);
 }
 
 // The same flip mask in two steps, for kernels that wait on global loads:
 // first the W random words (they depend only on the counter, so they can be
 // computed while the neighbour words are in flight), then the decisions.
-template <int J, int W>
-__device__ __forceinline__ void random_words(uint32_t c0, uint32_t quad0, uint32_t c2, uint32_t c3, uint32_t k0,
-                                             uint32_t k1, uint32_t (&u)[W])
+template <int N, int W>
+__device__ __forceinline__ void random_words(const PhiloxStep &s, uint32_t quad0, uint32_t (&u)[W])
 {
-    if constexpr (J > 0) {
-        Words4 a, b;
-        philox10_pair<kQuadOr<W>>(c0, quad0, (uint32_t)J, (uint32_t)(J - 1), c2, c3, k0, k1, a, b);
+    constexpr int G = philox_group(N);
+    Words4 w[G];
+    philox10_group<G, kQuadOr<W>>(s, quad0, N - 1, w);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            u[4 * J + i] = a.v[i];
-            u[4 * J - 4 + i] = b.v[i];
-        }
-        if constexpr (J > 1) random_words<J - 2, W>(c0, quad0, c2, c3, k0, k1, u);
-    } else {
-        const Words4 a = philox10(c0, quad0, c2, c3, k0, k1);
+    for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) u[i] = a.v[i];
-    }
+        for (int i = 0; i < 4; ++i) u[4 * (N - 1 - g) + i] = w[g].v[i];
+    if constexpr (N > G) random_words<N - G, W>(s, quad0, u);
 }
 
 template <int J, int W>
@@ -371,59 +516,83 @@ __device__ __forceinline__ void fill_select_tables(uint32_t *tab, uint32_t thr1,
     }
 }
 
-// The W thresholds of one word from the table (16-byte aligned).
-template <int W>
-__device__ __forceinline__ void select_thresholds(const Decision &d, const uint32_t *tab, uint32_t (&thr)[W])
+// Index bytes of a word's blocks: those of blocks 0, 2, 4, 6 and 1, 3, 5, 7.
+struct SelectIndex {
+    uint32_t lo, hi;
+};
+
+__device__ __forceinline__ SelectIndex select_index(const Decision &d)
 {
-    const uint32_t nib = 0x0F0F0F0Fu;
-    const uint32_t lo = __builtin_amdgcn_bitop3_b32(nib, d.any, d.odd << 4, kBitopSelect);
-    const uint32_t hi = __builtin_amdgcn_bitop3_b32(nib, d.any >> 4, d.odd, kBitopSelect);
-#pragma unroll
-    for (int g = 0; g < W / 4; ++g) {
-        const uint32_t src = (g & 1) ? hi : lo;
-        const uint32_t byte_off = ((src >> (8 * (g >> 1))) & 0xffu) << 4;
-        const uint4 q = *(const uint4 *)((const char *)tab + byte_off);
-        thr[4 * g + 0] = q.x;
-        thr[4 * g + 1] = q.y;
-        thr[4 * g + 2] = q.z;
-        thr[4 * g + 3] = q.w;
-    }
+    const uint32_t nib = in_vgpr(0x0F0F0F0Fu);
+    SelectIndex x;
+    x.lo = __builtin_amdgcn_bitop3_b32(nib, d.any, d.odd << 4, kBitopSelect);
+    x.hi = __builtin_amdgcn_bitop3_b32(nib, d.any >> 4, d.odd, kBitopSelect);
+    return x;
 }
 
-template <int J, int W>
-__device__ __forceinline__ uint32_t accept_blocks_lds(uint32_t accept, const uint32_t (&thr)[W], uint32_t c0,
-                                                      uint32_t quad0, uint32_t c2, uint32_t c3, uint32_t k0,
-                                                      uint32_t k1)
+// The four thresholds of block g from the table (16-byte aligned).
+__device__ __forceinline__ uint4 select_block(const SelectIndex &x, const uint32_t *tab, int g)
 {
-    if constexpr (J > 0) {
-        // blocks J and J - 1 side by side
-        Words4 u, v;
-        philox10_pair<kQuadOr<W>>(c0, quad0, (uint32_t)J, (uint32_t)(J - 1), c2, c3, k0, k1, u, v);
-        accept = append_below4(accept, u.v[3], thr[4 * J + 3], u.v[2], thr[4 * J + 2], u.v[1], thr[4 * J + 1],
-                               u.v[0], thr[4 * J]);
-        accept = append_below4(accept, v.v[3], thr[4 * J - 1], v.v[2], thr[4 * J - 2], v.v[1], thr[4 * J - 3],
-                               v.v[0], thr[4 * J - 4]);
-        if constexpr (J > 1)
-            return accept_blocks_lds<J - 2, W>(accept, thr, c0, quad0, c2, c3, k0, k1);
-        else
-            return accept;
+    const uint32_t src = (g & 1) ? x.hi : x.lo;
+    const uint32_t byte_off = ((src >> (8 * (g >> 1))) & 0xffu) << 4;
+    return *(const uint4 *)((const char *)tab + byte_off);
+}
+
+// The bits of G blocks, the first uppermost.
+template <int G>
+__device__ __forceinline__ uint32_t append_blocks(uint32_t accept, const Words4 (&u)[G], const uint4 (&t)[G])
+{
+#pragma unroll
+    for (int g = 0; g + 1 < G; g += 2) accept = append_below8(accept, u[g].v, t[g], u[g + 1].v, t[g + 1]);
+    if constexpr (G & 1) {
+        const Words4 &e = u[G - 1];
+        const uint4 &f = t[G - 1];
+        accept = append_below4(accept, e.v[3], f.w, e.v[2], f.z, e.v[1], f.y, e.v[0], f.x);
+    }
+    return accept;
+}
+
+// Blocks M-1 down to 0 after the group above them (G blocks, words u and
+// thresholds t): this group's thresholds are read, its words drawn, and only
+// then is the group above compared, so neither the table reads nor the
+// compares wait.
+template <int W, int M, int G>
+__device__ __forceinline__ uint32_t accept_rest(uint32_t accept, const SelectIndex &x, const PhiloxStep &s,
+                                                uint32_t quad0, const uint32_t *tab, const Words4 (&u)[G],
+                                                const uint4 (&t)[G])
+{
+    if constexpr (M > 0) {
+        constexpr int G2 = philox_group(M);
+        uint4 t2[G2];
+        Words4 u2[G2];
+#pragma unroll
+        for (int g = 0; g < G2; ++g) t2[g] = select_block(x, tab, M - 1 - g);
+        philox10_group<G2, kQuadOr<W>>(s, quad0, M - 1, u2);
+        accept = append_blocks(accept, u, t);
+        return accept_rest<W, M - G2, G2>(accept, x, s, quad0, tab, u2, t2);
     } else {
-        const Words4 u = philox10(c0, quad0, c2, c3, k0, k1);
-        return append_below4(accept, u.v[3], thr[3], u.v[2], thr[2], u.v[1], thr[1], u.v[0], thr[0]);
+        return append_blocks(accept, u, t);
     }
 }
 
 // Flip mask of one packed word of W sites, thresholds from the LDS table
 // (tab = kSelectTableWords words filled by fill_select_tables, 16-byte
-// aligned).  All W thresholds are read before the random words are
-// computed, so the LDS latency overlaps the Philox rounds.
-template <int W>
-__device__ __forceinline__ uint32_t flip_mask_lds(const Decision &d, uint32_t c0, uint32_t quad0, uint32_t c2,
-                                                  uint32_t c3, uint32_t k0, uint32_t k1, const uint32_t *tab)
+// aligned).  decide() classifies the word; it is called after the first
+// group's words are drawn, so that the lattice loads it waits for (issued
+// before this call) are in flight meanwhile.
+template <int W, class Decide>
+__device__ __forceinline__ uint32_t flip_mask_lds(const PhiloxStep &s, uint32_t quad0, const uint32_t *tab,
+                                                  const Decide &decide)
 {
-    uint32_t thr[W];
-    select_thresholds<W>(d, tab, thr);
-    return d.always | accept_blocks_lds<W / 4 - 1, W>(0u, thr, c0, quad0, c2, c3, k0, k1);
+    constexpr int N = W / 4, G = philox_group(N);
+    Words4 u[G];
+    philox10_group<G, kQuadOr<W>>(s, quad0, N - 1, u);
+    const Decision d = decide();
+    const SelectIndex x = select_index(d);
+    uint4 t[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) t[g] = select_block(x, tab, N - 1 - g);
+    return d.always | accept_rest<W, N - G, G>(0u, x, s, quad0, tab, u, t);
 }
 
 }  // namespace ea

@@ -116,29 +116,22 @@ __device__ __forceinline__ int slab_item_plane(int j, int s, int g, int k)
     return j < lo ? k + j : g + s + (j - lo);
 }
 
-// Acceptance bits of a word's W sites from their random words u and their
-// thresholds thr (bit i set iff u[i] < thr[i]), built from the top block
-// down as in accept_words.
-template <int J, int W>
-__device__ __forceinline__ uint32_t below_each(uint32_t accept, const uint32_t (&u)[W], const uint32_t (&thr)[W])
-{
-    accept = append_below4(accept, u[4 * J + 3], thr[4 * J + 3], u[4 * J + 2], thr[4 * J + 2], u[4 * J + 1],
-                           thr[4 * J + 1], u[4 * J], thr[4 * J]);
-    if constexpr (J > 0)
-        return below_each<J - 1, W>(accept, u, thr);
-    else
-        return accept;
-}
-
 // The general acceptance of a word with thresholds from the LDS select
 // table (fill_select_tables): four sites per 16-byte read, as in
 // flip_mask_lds, but with the random words already drawn.
 template <int W>
 __device__ __forceinline__ uint32_t accept_words_tab(const Decision &d, const uint32_t (&u)[W], const uint32_t *tab)
 {
-    uint32_t thr[W];
-    select_thresholds<W>(d, tab, thr);
-    return below_each<W / 4 - 1, W>(0u, u, thr);
+    const SelectIndex x = select_index(d);
+    uint4 thr[W / 4];
+#pragma unroll
+    for (int g = 0; g < W / 4; ++g) thr[g] = select_block(x, tab, g);
+    uint32_t accept = 0u;
+#pragma unroll
+    for (int g = W / 4 - 1; g >= 0; --g)
+        accept = append_below4(accept, u[4 * g + 3], thr[g].w, u[4 * g + 2], thr[g].z, u[4 * g + 1], thr[g].y,
+                               u[4 * g], thr[g].x);
+    return accept;
 }
 
 // accept_screened with the general case through the tables: where uphill
@@ -221,10 +214,9 @@ struct SlabWord {
         Bzm = P.bz_oth[base - PL + q];
     }
 
-    __device__ __forceinline__ void draw(uint32_t t, uint32_t quad0, uint32_t c2, uint32_t sample, uint32_t k0,
-                                         uint32_t k1)
+    __device__ __forceinline__ void draw(const PhiloxStep &step, uint32_t quad0)
     {
-        random_words<W / 4 - 1, W>(t, quad0, c2, sample, k0, k1, u);
+        random_words<W / 4, W>(step, quad0, u);
     }
 
     // par: the row's x parity (x = 2 xh + par)
@@ -362,7 +354,8 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 const int c = r ^ (int)(j & 1u);
                 const uint32_t t = run.t0 + (j >> 1);
                 const uint32_t ep_prev = run.serial + j, ep_now = run.serial + j + 1u;
-                const uint32_t c2 = counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r);
+                const PhiloxStep step =
+                    philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), run.sample, run.k0, run.k1);
                 unsigned long long *xb = run.xbuf + (size_t)r * xrep;
                 unsigned long long *gl = xb + (((size_t)slot_prev * 2 + (c ^ 1)) * L + wrap(z0 - 1, L)) * PL + q;
                 unsigned long long *gu = xb + (((size_t)slot_prev * 2 + (c ^ 1)) * L + wrap(z0 + s, L)) * PL + q;
@@ -386,7 +379,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                     SlabWord<W> sw;
                     sw.load(P, base, q, qm, qp, qym, qyp, PL);
                     __builtin_amdgcn_sched_barrier(0);
-                    sw.draw(t, (uint32_t)(((y + L * zg) * R + w * W) >> 2), c2, run.sample, run.k0, run.k1);
+                    sw.draw(step, (uint32_t)(((y + L * zg) * R + w * W) >> 2));
                     if (need_lo && (uint32_t)(vl >> 32) != ep_prev && !slab_poll(gl, ep_prev, a.err, vl)) flag[1] = 1;
                     if (need_hi && (uint32_t)(vu >> 32) != ep_prev && !slab_poll(gu, ep_prev, a.err, vu)) flag[1] = 1;
                     if (need_lo) sw.Zm = (uint32_t)vl;
@@ -422,7 +415,8 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 const uint32_t t = run.t0 + (j_half >> 1);
                 const int c = r ^ (int)(j_half & 1u);
                 const bool publish = k >= G - 1;  // the colour's last update in this cycle
-                const uint32_t c2 = counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r);
+                const PhiloxStep step =
+                    philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), run.sample, run.k0, run.k1);
                 const SlabPlanes P = slab_planes(lspin, lbond, EM * PL, c);
                 const int n_items = E - 2 * k;
                 if (worker) {
@@ -431,7 +425,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                         const int zg = wrap(zb + e, L);
                         SlabWord<W> sw;
                         sw.load(P, e * PL, q, qm, qp, qym, qyp, PL);
-                        sw.draw(t, (uint32_t)(((y + L * zg) * R + w * W) >> 2), c2, run.sample, run.k0, run.k1);
+                        sw.draw(step, (uint32_t)(((y + L * zg) * R + w * W) >> 2));
                         const uint32_t v =
                             sw.template update<SCREEN>((y + zg + c) & 1, run.thr1, run.thr2, run.thr3, tab);
                         P.own[e * PL + q] = v;
