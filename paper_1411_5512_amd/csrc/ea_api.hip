@@ -141,16 +141,19 @@ bool slab_capable(int L, int rw) { return L * rw <= ea::kSlabThreads; }
 // Modelled time per sweep (us) of a plan whose workgroups own at most s
 // planes each, used to pick one, with constants measured on MI355X.  A
 // workgroup updates 1024 / (L rw) planes at once; in each such round its
-// waves share the four SIMDs, and a SIMD runs the dependent chains of its
-// waves' words about one after the other, one chain being ~(13.2 W + 40)
-// instructions at ~4 cycles each.  With g = 1 a half-step costs ~0.9 us of
+// waves share the four SIMDs, and a SIMD is priced as running the dependent
+// chains of its waves' words one after the other, one chain being ~(13.2 W +
+// 40) instructions at ~4 cycles each.  With g = 1 a half-step costs ~0.9 us of
 // exchange and barrier beyond its rounds; a cycle of g >= 2 half-steps costs
 // ~3 us beyond its rounds (the ghost planes are read only after the
-// neighbours' whole cycle, with a barrier on either side).  Measured per
-// sweep against the model: L = 64 one plane of 4 words of 8 sites 2.36 us
-// (2.29), L = 96 one plane of 2 words 2.97 (2.99) and of 3 words 3.34
-// (3.48), L = 128 one plane 3.41 (3.34), five L = 128 runs on shares of 5
-// planes 9.96 (9.50).
+// neighbours' whole cycle, with a barrier on either side).  Measured per sweep
+// against the model: L = 64 one plane of 4 words of 8 sites 2.13 us (2.29),
+// L = 96 one plane of 2 words 2.82 (2.99) and of 3 words 3.01 (3.48), L = 128
+// one plane 3.23 (3.34), five L = 128 runs on shares of 5 planes 8.52 (9.50).
+// Waves of one SIMD really overlap (a further one adds 0.7 of a chain), but
+// pricing that makes the finer packings of L = 32 and 80 look better than they
+// are (L = 32 in 2 words 2.40 us against 2.03 in 4; five L = 80 runs in 5 words
+// 5.85 against 4.33 in 2).
 double slab_model_us(int L, int rw, int s, int g)
 {
     const int W = L / 2 / rw, PL = L * rw;
@@ -170,6 +173,11 @@ double slab_model_us(int L, int rw, int s, int g)
     return 2.0 * cycle / g;
 }
 
+size_t slab_lds_bytes(int L, int rw, int emax)
+{
+    return 4 * (8 * (size_t)emax * (size_t)(L * rw) + 16);
+}
+
 double slab_best_model_us(int L, int rw)
 {
     if (!slab_capable(L, rw)) return -1.0;
@@ -177,8 +185,7 @@ double slab_best_model_us(int L, int rw)
     for (int K = 1; K <= L && 2 * K <= 256; ++K)
         for (int g = 1; g <= 4; ++g) {
             const int emax = (L + K - 1) / K + 2 * g;
-            if (4 * (8 * (size_t)emax * (size_t)(L * rw) + 16) > 160 * 1024 - 4 * (size_t)ea::kSelectTableWords)
-                continue;
+            if (slab_lds_bytes(L, rw, emax) > 160 * 1024 - 4 * (size_t)ea::kSelectTableWords) continue;
             const double c = slab_model_us(L, rw, (L + K - 1) / K, g);
             if (best < 0.0 || c < best) best = c;
         }
@@ -444,24 +451,24 @@ int slab_emax(int L, int n_runs, int B, int g)
     return emax;
 }
 
-size_t slab_lds_bytes(int L, int rw, int emax) { return 4 * (8 * (size_t)emax * (size_t)(L * rw) + 16); }
+
 
 std::mutex g_slab_mu;
 int g_slab_cus = 0, g_slab_lds_limit = 0;
 bool g_slab_attr[33] = {};
 
-template <bool SCREEN, bool SPAN>
+template <bool SPAN>
 const void *slab_kernel_fn(int W)
 {
     switch (W) {
-    case 4: return (const void *)ea::slab_sweep_kernel<4, SCREEN, SPAN>;
-    case 8: return (const void *)ea::slab_sweep_kernel<8, SCREEN, SPAN>;
-    case 12: return (const void *)ea::slab_sweep_kernel<12, SCREEN, SPAN>;
-    case 16: return (const void *)ea::slab_sweep_kernel<16, SCREEN, SPAN>;
-    case 20: return (const void *)ea::slab_sweep_kernel<20, SCREEN, SPAN>;
-    case 24: return (const void *)ea::slab_sweep_kernel<24, SCREEN, SPAN>;
-    case 28: return (const void *)ea::slab_sweep_kernel<28, SCREEN, SPAN>;
-    default: return (const void *)ea::slab_sweep_kernel<32, SCREEN, SPAN>;
+    case 4: return (const void *)ea::slab_sweep_kernel<4, SPAN>;
+    case 8: return (const void *)ea::slab_sweep_kernel<8, SPAN>;
+    case 12: return (const void *)ea::slab_sweep_kernel<12, SPAN>;
+    case 16: return (const void *)ea::slab_sweep_kernel<16, SPAN>;
+    case 20: return (const void *)ea::slab_sweep_kernel<20, SPAN>;
+    case 24: return (const void *)ea::slab_sweep_kernel<24, SPAN>;
+    case 28: return (const void *)ea::slab_sweep_kernel<28, SPAN>;
+    default: return (const void *)ea::slab_sweep_kernel<32, SPAN>;
     }
 }
 
@@ -480,8 +487,7 @@ ea_status slab_device(int W, int *n_cu, int *lds_limit)
     }
     if (W < 4 || W > 32 || W % 4) return fail(EA_ERR_STATE, "unsupported word width %d", W);
     if (!g_slab_attr[W]) {
-        const void *fns[4] = {slab_kernel_fn<false, false>(W), slab_kernel_fn<true, false>(W),
-                              slab_kernel_fn<false, true>(W), slab_kernel_fn<true, true>(W)};
+        const void *fns[2] = {slab_kernel_fn<false>(W), slab_kernel_fn<true>(W)};
         for (const void *fn : fns)
             EA_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, g_slab_lds_limit));
         g_slab_attr[W] = true;
@@ -634,20 +640,12 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
             m->xserial += n_cycles + 1;
         }
         const dim3 grid((unsigned)plan.B);
-        // the screen pays where every workgroup gives each SIMD four waves of work
-        const bool screen = (long)(a.P / plan.B) * y.L * y.RW >= ea::kSlabThreads;
-        if (screen && span) {
-            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, true, true>), grid,
-                                                  dim3(ea::kSlabThreads), lds, lead->stream, a));
-        } else if (screen) {
-            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, true, false>), grid,
-                                                  dim3(ea::kSlabThreads), lds, lead->stream, a));
-        } else if (span) {
-            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, false, true>), grid,
-                                                  dim3(ea::kSlabThreads), lds, lead->stream, a));
+        if (span) {
+            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, true>), grid, dim3(ea::kSlabThreads),
+                                                  lds, lead->stream, a));
         } else {
-            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, false, false>), grid,
-                                                  dim3(ea::kSlabThreads), lds, lead->stream, a));
+            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, false>), grid, dim3(ea::kSlabThreads),
+                                                  lds, lead->stream, a));
         }
         EA_HIP(hipGetLastError());
         done += chunk;

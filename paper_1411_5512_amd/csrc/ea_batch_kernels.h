@@ -130,7 +130,7 @@ __device__ __forceinline__ void batch_half_step(const BatchJobDev &J, int r, uin
     using S = Shape<L, RW>;
     constexpr int W = S::W;
     constexpr int c = C;
-    const PhiloxStep step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
+    const PhiloxStep<true> step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
     // Recompute the addresses every half-step: hoisting them out of the
     // sweep loop would keep some thirty address registers live and spill.
     int tid = (int)threadIdx.x;
@@ -579,7 +579,7 @@ __device__ __forceinline__ bool slab_wait_words(unsigned long long *pub, unsigne
 // New value of slab word p (colour c, sweep t), given its z-1 and z+1
 // neighbour words of the other colour and the coupling to the z-1 neighbour.
 template <int L, int RW, int SEL>
-__device__ __forceinline__ uint32_t slab_new_word(const BatchJobDev &J, const PhiloxStep &step, int c, int z0, int p,
+__device__ __forceinline__ uint32_t slab_new_word(const BatchJobDev &J, const PhiloxStep<true> &step, int c, int z0, int p,
                                                   uint32_t Ozm, uint32_t Ozp, uint32_t Bzm)
 {
     using S = Slab<L, RW>;
@@ -631,7 +631,7 @@ __device__ __forceinline__ bool slab_half_step(const BatchJobDev &J, int r, int 
     const uint32_t *bz_oth = slab_bond<S>(2, c ^ 1);
     int tid = (int)threadIdx.x;
     asm volatile("" : "+v"(tid));
-    const PhiloxStep step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
+    const PhiloxStep<true> step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
     if (tid >= 64) {
         // interior planes 1 .. NZ-2
 #pragma unroll 1

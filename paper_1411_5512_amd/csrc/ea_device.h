@@ -75,8 +75,10 @@ constexpr int kBitopOrXor = 0x56;  // (src0 | src1) ^ src2, bitwise
 // the kinds freely hardly ever meet at a pair (alternating multiply-adds and
 // XORs: 4.25 each, as if nothing paired).  Raising a wave's priority while it
 // runs its multiplies or compares lets the waves catch up there and meet in
-// their XORs: 3.4 each at four waves.  Hence the phases below, and the round
-// keys and the wavefront-uniform words of the first rounds in VGPRs.
+// their XORs: 3.4 each at four waves.  Hence the phases below (PHASED), and
+// the round keys and the wavefront-uniform words of the first rounds in
+// VGPRs.  A wave that runs alone on its SIMD issues one instruction of any
+// kind per 4.6 cycles, priority changes included, and takes the plain forms.
 // The multiplies of a phase are one asm block between its two priority
 // changes (the compiler would move plain multiplies across them).
 #define EA_MAD(d, x, m) "v_mad_u64_u32 %" d ", vcc, %" x ", %" m ", 0\n\t"
@@ -87,11 +89,14 @@ constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM2 = 0xCD9E8D57u;
 constexpr uint32_t kPhiloxK0 = 0x9E3779B9u, kPhiloxK1 = 0xBB67AE85u;
 
 // p[g] = x[g] M
-template <int G>
+template <bool PHASED, int G>
 __device__ __forceinline__ void mul_phase(uint64_t (&p)[G], const uint32_t (&x)[G], uint32_t M)
 {
     static_assert(G >= 1 && G <= 4, "blocks side by side");
-    if constexpr (G == 1)
+    if constexpr (!PHASED) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) p[g] = (uint64_t)x[g] * M;
+    } else if constexpr (G == 1)
         asm volatile(EA_MULS_BEGIN EA_MAD("0", "1", "2") EA_MULS_END : "=&v"(p[0]) : "v"(x[0]), "s"(M) : "vcc");
     else if constexpr (G == 2)
         asm volatile(EA_MULS_BEGIN EA_MAD("0", "2", "4") EA_MAD("1", "3", "4") EA_MULS_END
@@ -112,12 +117,18 @@ __device__ __forceinline__ void mul_phase(uint64_t (&p)[G], const uint32_t (&x)[
 }
 
 // p[g] = x[g] M0 and r[g] = y[g] M2
-template <int G>
+template <bool PHASED, int G>
 __device__ __forceinline__ void mul_phase(uint64_t (&p)[G], const uint32_t (&x)[G], uint64_t (&r)[G],
                                           const uint32_t (&y)[G])
 {
     static_assert(G >= 1 && G <= 4, "blocks side by side");
-    if constexpr (G == 1)
+    if constexpr (!PHASED) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            p[g] = (uint64_t)x[g] * kPhiloxM0;
+            r[g] = (uint64_t)y[g] * kPhiloxM2;
+        }
+    } else if constexpr (G == 1)
         asm volatile(EA_MULS_BEGIN EA_MAD("0", "2", "4") EA_MAD("1", "3", "5") EA_MULS_END
                      : "=&v"(p[0]), "=&v"(r[0])
                      : "v"(x[0]), "v"(y[0]), "s"(kPhiloxM0), "s"(kPhiloxM2)
@@ -158,6 +169,7 @@ __device__ __forceinline__ uint32_t in_vgpr(uint32_t v)
 // the key are the same for every lane, so only word 1's path is per lane in
 // the first rounds (word 0 from round 1 on, word 2 from round 2 on, all four
 // from round 4 on).  Rounds are numbered from 0.
+template <bool PHASED>
 struct PhiloxStep {
     uint32_t h;           // round 0: word 0 = counter word 1 ^ h
     uint32_t e1;          // round 1: word 2 = hi(m0) ^ e1
@@ -166,28 +178,30 @@ struct PhiloxStep {
     uint32_t k0, k1;      // keys of round 3
 };
 
-__device__ __forceinline__ PhiloxStep philox_step(uint32_t x0, uint32_t x2, uint32_t x3, uint32_t k0, uint32_t k1)
+template <bool PHASED = true>
+__device__ __forceinline__ PhiloxStep<PHASED> philox_step(uint32_t x0, uint32_t x2, uint32_t x3, uint32_t k0, uint32_t k1)
 {
     const uint64_t n0 = (uint64_t)x0 * kPhiloxM0, n2 = (uint64_t)x2 * kPhiloxM2;
     const uint32_t b2 = (uint32_t)(n0 >> 32) ^ x3 ^ k1;                      // word 2 after round 0
     const uint64_t p2 = (uint64_t)b2 * kPhiloxM2;                            // round 1
     const uint32_t c0 = (uint32_t)(p2 >> 32) ^ (uint32_t)n2 ^ (k0 + kPhiloxK0);  // word 0 after round 1
     const uint64_t q0 = (uint64_t)c0 * kPhiloxM0;                            // round 2
-    PhiloxStep s;
-    s.h = in_vgpr((uint32_t)(n2 >> 32) ^ k0);
-    s.e1 = in_vgpr((uint32_t)n0 ^ (k1 + kPhiloxK1));
-    s.e2 = in_vgpr((uint32_t)p2 ^ (k0 + 2 * kPhiloxK0));
-    s.e3 = in_vgpr((uint32_t)(q0 >> 32) ^ (k1 + 2 * kPhiloxK1));
-    s.e4 = in_vgpr((uint32_t)q0 ^ (k1 + 3 * kPhiloxK1));
-    s.k0 = in_vgpr(k0 + 3 * kPhiloxK0);
-    s.k1 = in_vgpr(k1 + 3 * kPhiloxK1);
+    auto hold = [](uint32_t v) { return PHASED ? in_vgpr(v) : v; };
+    PhiloxStep<PHASED> s;
+    s.h = hold((uint32_t)(n2 >> 32) ^ k0);
+    s.e1 = hold((uint32_t)n0 ^ (k1 + kPhiloxK1));
+    s.e2 = hold((uint32_t)p2 ^ (k0 + 2 * kPhiloxK0));
+    s.e3 = hold((uint32_t)(q0 >> 32) ^ (k1 + 2 * kPhiloxK1));
+    s.e4 = hold((uint32_t)q0 ^ (k1 + 3 * kPhiloxK1));
+    s.k0 = hold(k0 + 3 * kPhiloxK0);
+    s.k1 = hold(k1 + 3 * kPhiloxK1);
     return s;
 }
 
 // Blocks J, J - 1, ... J - G + 1 of a word side by side, round by round: each
 // round's 2 G multiplies, then its 2 G XORs and the next keys.
-template <int G, bool ORQ>
-__device__ __forceinline__ void philox10_group(const PhiloxStep &s, uint32_t quad0, int J, Words4 (&w)[G])
+template <int G, bool ORQ, bool PHASED>
+__device__ __forceinline__ void philox10_group(const PhiloxStep<PHASED> &s, uint32_t quad0, int J, Words4 (&w)[G])
 {
     uint32_t x0[G], x1[G], x2[G], x3[G];
     uint64_t m0[G], m2[G];
@@ -196,13 +210,13 @@ __device__ __forceinline__ void philox10_group(const PhiloxStep &s, uint32_t qua
         const uint32_t j = (uint32_t)(J - g);
         x0[g] = ORQ ? __builtin_amdgcn_bitop3_b32(quad0, j, s.h, kBitopOrXor) : ((quad0 + j) ^ s.h);
     }
-    mul_phase(m0, x0, kPhiloxM0);
+    mul_phase<PHASED>(m0, x0, kPhiloxM0);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         x2[g] = (uint32_t)(m0[g] >> 32) ^ s.e1;
         x3[g] = (uint32_t)m0[g];
     }
-    mul_phase(m2, x2, kPhiloxM2);
+    mul_phase<PHASED>(m2, x2, kPhiloxM2);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         x0[g] = (uint32_t)(m2[g] >> 32) ^ s.e2;
@@ -212,7 +226,7 @@ __device__ __forceinline__ void philox10_group(const PhiloxStep &s, uint32_t qua
     uint32_t k0 = s.k0, k1 = s.k1;
 #pragma unroll
     for (int round = 3; round < 10; ++round) {
-        mul_phase(m0, x0, m2, x2);
+        mul_phase<PHASED>(m0, x0, m2, x2);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             x0[g] = xor3((uint32_t)(m2[g] >> 32), x1[g], k0);
@@ -357,18 +371,16 @@ __device__ __forceinline__ uint32_t append_below4(uint32_t accept, uint32_t u3, 
                                                   uint32_t t0)
 {
     uint64_t m3, m2, m1, m0, co;
-    asm volatile("s_setprio 1\n\t"
-                 "v_cmp_lt_u32_e64 %1, %6, %7\n\t"
-                 "v_cmp_lt_u32_e64 %2, %8, %9\n\t"
-                 "v_cmp_lt_u32_e64 %3, %10, %11\n\t"
-                 "v_cmp_lt_u32_e64 %4, %12, %13\n\t"
-                 "v_addc_co_u32_e64 %0, %5, %0, %0, %1\n\t"
-                 "v_addc_co_u32_e64 %0, %5, %0, %0, %2\n\t"
-                 "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
-                 "v_addc_co_u32_e64 %0, %5, %0, %0, %4\n\t"
-                 "s_setprio 0"
-                 : "+v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
-                 : "v"(u3), "v"(t3), "v"(u2), "v"(t2), "v"(u1), "v"(t1), "v"(u0), "v"(t0));
+    asm("v_cmp_lt_u32_e64 %1, %6, %7\n\t"
+        "v_cmp_lt_u32_e64 %2, %8, %9\n\t"
+        "v_cmp_lt_u32_e64 %3, %10, %11\n\t"
+        "v_cmp_lt_u32_e64 %4, %12, %13\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
+        "v_addc_co_u32_e64 %0, %5, %0, %0, %4"
+        : "+v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
+        : "v"(u3), "v"(t3), "v"(u2), "v"(t2), "v"(u1), "v"(t1), "v"(u0), "v"(t0));
     return accept;
 }
 
@@ -437,7 +449,7 @@ __device__ __forceinline__ uint32_t append_blocks_reg(uint32_t accept, const Dec
 // Blocks N-1 down to 0: block J covers sites 4J..4J+3 and has counter word 1
 // equal to quad0 + J.
 template <int W, int N>
-__device__ __forceinline__ uint32_t accept_blocks(uint32_t accept, const Decision &d, const PhiloxStep &s,
+__device__ __forceinline__ uint32_t accept_blocks(uint32_t accept, const Decision &d, const PhiloxStep<true> &s,
                                                   uint32_t quad0, uint32_t thr1, uint32_t thr2, uint32_t thr3)
 {
     constexpr int G = philox_group(N);
@@ -452,7 +464,7 @@ __device__ __forceinline__ uint32_t accept_blocks(uint32_t accept, const Decisio
 
 // Flip mask of one packed word of W sites (bits W..31 stay zero).
 template <int W>
-__device__ __forceinline__ uint32_t flip_mask(const Decision &d, const PhiloxStep &s, uint32_t quad0, uint32_t thr1,
+__device__ __forceinline__ uint32_t flip_mask(const Decision &d, const PhiloxStep<true> &s, uint32_t quad0, uint32_t thr1,
                                               uint32_t thr2, uint32_t thr3)
 {
     return d.always | accept_blocks<W, W / 4>(0u, d, s, quad0, thr1, thr2, thr3);
@@ -461,17 +473,17 @@ __device__ __forceinline__ uint32_t flip_mask(const Decision &d, const PhiloxSte
 // The same flip mask in two steps, for kernels that wait on global loads:
 // first the W random words (they depend only on the counter, so they can be
 // computed while the neighbour words are in flight), then the decisions.
-template <int N, int W>
-__device__ __forceinline__ void random_words(const PhiloxStep &s, uint32_t quad0, uint32_t (&u)[W])
+template <int N, int W, bool PHASED>
+__device__ __forceinline__ void random_words(const PhiloxStep<PHASED> &s, uint32_t quad0, uint32_t (&u)[W])
 {
-    constexpr int G = philox_group(N);
+    constexpr int G = PHASED ? philox_group(N) : (N >= 2 ? 2 : 1);
     Words4 w[G];
     philox10_group<G, kQuadOr<W>>(s, quad0, N - 1, w);
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i) u[4 * (N - 1 - g) + i] = w[g].v[i];
-    if constexpr (N > G) random_words<N - G, W>(s, quad0, u);
+    if constexpr (N > G) random_words<N - G, W, PHASED>(s, quad0, u);
 }
 
 template <int J, int W>
@@ -557,7 +569,7 @@ __device__ __forceinline__ uint32_t append_blocks(uint32_t accept, const Words4 
 // then is the group above compared, so neither the table reads nor the
 // compares wait.
 template <int W, int M, int G>
-__device__ __forceinline__ uint32_t accept_rest(uint32_t accept, const SelectIndex &x, const PhiloxStep &s,
+__device__ __forceinline__ uint32_t accept_rest(uint32_t accept, const SelectIndex &x, const PhiloxStep<true> &s,
                                                 uint32_t quad0, const uint32_t *tab, const Words4 (&u)[G],
                                                 const uint4 (&t)[G])
 {
@@ -581,7 +593,7 @@ __device__ __forceinline__ uint32_t accept_rest(uint32_t accept, const SelectInd
 // group's words are drawn, so that the lattice loads it waits for (issued
 // before this call) are in flight meanwhile.
 template <int W, class Decide>
-__device__ __forceinline__ uint32_t flip_mask_lds(const PhiloxStep &s, uint32_t quad0, const uint32_t *tab,
+__device__ __forceinline__ uint32_t flip_mask_lds(const PhiloxStep<true> &s, uint32_t quad0, const uint32_t *tab,
                                                   const Decide &decide)
 {
     constexpr int N = W / 4, G = philox_group(N);

@@ -159,7 +159,7 @@ __device__ __forceinline__ void half_step_word(const Lattice &lat, const Geom &g
     // every load issued before them)
     __builtin_amdgcn_sched_barrier(0);
     uint32_t u[W];
-    random_words<W / 4, W>(philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), sample, k0, k1),
+    random_words<W / 4, W>(philox_step<SCREEN>(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), sample, k0, k1),
                            (uint32_t)((row * g.R + w * W) >> 2), u);
 
     // x neighbours: on even rows (par = 0) the +x neighbour shares xh and the

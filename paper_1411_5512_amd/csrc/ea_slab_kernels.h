@@ -116,55 +116,6 @@ __device__ __forceinline__ int slab_item_plane(int j, int s, int g, int k)
     return j < lo ? k + j : g + s + (j - lo);
 }
 
-// The general acceptance of a word with thresholds from the LDS select
-// table (fill_select_tables): four sites per 16-byte read, as in
-// flip_mask_lds, but with the random words already drawn.
-template <int W>
-__device__ __forceinline__ uint32_t accept_words_tab(const Decision &d, const uint32_t (&u)[W], const uint32_t *tab)
-{
-    const SelectIndex x = select_index(d);
-    uint4 thr[W / 4];
-#pragma unroll
-    for (int g = 0; g < W / 4; ++g) thr[g] = select_block(x, tab, g);
-    uint32_t accept = 0u;
-#pragma unroll
-    for (int g = W / 4 - 1; g >= 0; --g)
-        accept = append_below4(accept, u[4 * g + 3], thr[g].w, u[4 * g + 2], thr[g].z, u[4 * g + 1], thr[g].y,
-                               u[4 * g], thr[g].x);
-    return accept;
-}
-
-// accept_screened with the general case through the tables: where uphill
-// moves of dE >= 8 are rare, a word none of whose random words falls below
-// thr2 accepts exactly its n = 2 sites whose word is below thr1; other words
-// take the table select, so the decisions are the same either way.
-template <int W, bool SCREEN>
-__device__ __forceinline__ uint32_t accept_slab(const Decision &d, const uint32_t (&u)[W], uint32_t thr1,
-                                                uint32_t thr2, uint32_t thr3, const uint32_t *tab)
-{
-    if constexpr (SCREEN) {
-        const bool rare = (uint64_t)thr2 * (uint64_t)W < (1ull << 24) && thr3 <= thr2;  // uniform
-        if (rare) {
-            const uint32_t a1 = below_words<W / 4 - 1, W>(0u, u, thr1);
-            uint32_t v[W];
-#pragma unroll
-            for (int i = 0; i < W; ++i) v[i] = u[i];
-#pragma unroll
-            for (int n = W; n > 1; n = (n + 2) / 3) {
-#pragma unroll
-                for (int i = 0; 3 * i < n; ++i) {
-                    uint32_t m = v[3 * i];
-                    if (3 * i + 1 < n) m = min(m, v[3 * i + 1]);
-                    if (3 * i + 2 < n) m = min(m, v[3 * i + 2]);
-                    v[i] = m;
-                }
-            }
-            if (v[0] >= thr2) return a1 & d.any & ~d.always;
-        }
-    }
-    return accept_words_tab<W>(d, u, tab);
-}
-
 // The LDS planes a half-step of colour c reads and writes.
 struct SlabPlanes {
     uint32_t *own;
@@ -186,13 +137,12 @@ __device__ __forceinline__ SlabPlanes slab_planes(uint32_t *lspin, const uint32_
 }
 
 // One packed word's update (eq. 9): its own word and the fifteen words
-// around it, the W random words, and the flip decision.  Zm and Zp (the z
-// neighbours of the other colour) may be replaced before update() by words
-// that come from a neighbouring slab.
+// around it, and the decision.  Zm and Zp (the z neighbours of the other
+// colour) may be replaced before decide() by words that come from a
+// neighbouring slab.
 template <int W>
 struct SlabWord {
     uint32_t S, O, Om, Op, Xo, Xom, Bx, By, Bz, Yp, Ym, Bym, Zp, Zm, Bzm;
-    uint32_t u[W];
 
     __device__ __forceinline__ void load(const SlabPlanes &P, int base, int q, int qm, int qp, int qym, int qyp,
                                          int PL)
@@ -214,22 +164,14 @@ struct SlabWord {
         Bzm = P.bz_oth[base - PL + q];
     }
 
-    __device__ __forceinline__ void draw(const PhiloxStep &step, uint32_t quad0)
-    {
-        random_words<W / 4, W>(step, quad0, u);
-    }
-
     // par: the row's x parity (x = 2 xh + par)
-    template <bool SCREEN>
-    __device__ __forceinline__ uint32_t update(int par, uint32_t thr1, uint32_t thr2, uint32_t thr3,
-                                               const uint32_t *tab) const
+    __device__ __forceinline__ Decision decide(int par) const
     {
         const uint32_t pm = 0u - (uint32_t)par;
         const uint32_t xp = __builtin_amdgcn_bitop3_b32(pm, take_plus1<W>(O, Op), O, kBitopSelect);
         const uint32_t xm = __builtin_amdgcn_bitop3_b32(pm, O ^ Xo, take_minus1<W>(O ^ Xo, Om ^ Xom), kBitopSelect);
-        const Decision d = classify(S ^ xp ^ Bx, S ^ xm, xor3(S, Yp, By), xor3(S, Ym, Bym), xor3(S, Zp, Bz),
-                                    xor3(S, Zm, Bzm));
-        return S ^ (d.always | accept_slab<W, SCREEN>(d, u, thr1, thr2, thr3, tab));
+        return classify(xor3(S, xp, Bx), S ^ xm, xor3(S, Yp, By), xor3(S, Ym, Bym), xor3(S, Zp, Bz),
+                        xor3(S, Zm, Bzm));
     }
 };
 
@@ -249,13 +191,21 @@ __device__ __forceinline__ bool slab_poll(const unsigned long long *p, uint32_t 
 
 __shared__ __align__(16) uint32_t slab_select_tables[kSelectTableWords];
 
-// SCREEN: launches whose slabs give every SIMD four or more waves of work
-// per half-step screen the rare uphill moves (accept_slab); smaller ones are
-// bound by one wave's chain of dependent instructions, which the screen
-// lengthens.  SPAN: some workgroup's share spans two replicas (two pieces);
-// launches of whole slabs take the one-piece instantiation, whose constants
-// all stay in scalar registers across the half-steps.
-template <int W, bool SCREEN, bool SPAN>
+// SPAN: some workgroup's share spans two replicas (two pieces); launches of
+// whole slabs take the one-piece instantiation, whose constants all stay in
+// scalar registers across the half-steps.
+//
+// Thick shares are bound by VALU issue as the batched update is (ea_device.h),
+// shares of one plane by the exchange and one word's chain of instructions.
+// Measured per sweep, now and before the update issued in phases with the
+// ghosts checked behind the first group of random words: five L = 128 runs
+// (shares of five planes) 8.52 us (9.75), L = 256 11.7 (14.6), sixteen L = 64
+// runs 5.99 (6.98), L = 128 alone 3.23 (3.48), L = 96 2.82 (2.99), L = 64 2.13
+// (2.19).  Against it, all random words before the ghosts (the form that was
+// best before): 9.64, 14.7, 6.59, 4.16, 2.96, 2.25; waves that follow their
+// neighbour planes' progress counters instead of the barrier: 8.78, 12.7,
+// 6.81, 3.94, 3.62, 2.70.
+template <int W, bool SPAN>
 __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
 {
     const int L = a.L, RW = a.RW, PL = L * RW, R = L / 2;
@@ -331,11 +281,10 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
         // its piece is its z neighbour in the ghost plane, same column, of the
         // colour the neighbouring slab updated in the previous half-step: the
         // thread that updates the word loads that entry itself before its
-        // random words and checks the epoch after them, so no ghost pass and
-        // no extra barrier are needed, and the interior planes overlap the
-        // exchange.  Ghost planes in LDS are read only in the first half-step.
-        // (Measured: a look after the random words instead, or a second look
-        // there, is 5-10% slower at L = 64.)
+        // random words and checks the epoch after the first group of them, so
+        // no ghost pass and no extra barrier are needed, and the interior
+        // planes overlap the exchange.  Ghost planes in LDS are read only in
+        // the first half-step.
         const uint32_t *tab_1 = a.tables == 2 ? tab1 : slab_select_tables;
         for (uint32_t j = 0; j < n_half; ++j) {
             const int slot_now = (int)(j % (uint32_t)kSlabSlots);
@@ -354,8 +303,8 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 const int c = r ^ (int)(j & 1u);
                 const uint32_t t = run.t0 + (j >> 1);
                 const uint32_t ep_prev = run.serial + j, ep_now = run.serial + j + 1u;
-                const PhiloxStep step =
-                    philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), run.sample, run.k0, run.k1);
+                const PhiloxStep<true> step = philox_step(
+                    t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), run.sample, run.k0, run.k1);
                 unsigned long long *xb = run.xbuf + (size_t)r * xrep;
                 unsigned long long *gl = xb + (((size_t)slot_prev * 2 + (c ^ 1)) * L + wrap(z0 - 1, L)) * PL + q;
                 unsigned long long *gu = xb + (((size_t)slot_prev * 2 + (c ^ 1)) * L + wrap(z0 + s, L)) * PL + q;
@@ -376,15 +325,25 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                     if (need_lo) vl = __hip_atomic_load(gl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (need_hi) vu = __hip_atomic_load(gu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     const int base = (off + e) * PL;
+                    const uint32_t quad0 = (uint32_t)(((y + L * zg) * R + w * W) >> 2);
                     SlabWord<W> sw;
                     sw.load(P, base, q, qm, qp, qym, qyp, PL);
-                    __builtin_amdgcn_sched_barrier(0);
-                    sw.draw(step, (uint32_t)(((y + L * zg) * R + w * W) >> 2));
-                    if (need_lo && (uint32_t)(vl >> 32) != ep_prev && !slab_poll(gl, ep_prev, a.err, vl)) flag[1] = 1;
-                    if (need_hi && (uint32_t)(vu >> 32) != ep_prev && !slab_poll(gu, ep_prev, a.err, vu)) flag[1] = 1;
-                    if (need_lo) sw.Zm = (uint32_t)vl;
-                    if (need_hi) sw.Zp = (uint32_t)vu;
-                    const uint32_t v = sw.template update<SCREEN>((y + zg + c) & 1, run.thr1, run.thr2, run.thr3, tab);
+                    auto ghosts = [&]() {
+                        bool ok = true;
+                        if (need_lo && (uint32_t)(vl >> 32) != ep_prev) ok &= slab_poll(gl, ep_prev, a.err, vl);
+                        if (need_hi && (uint32_t)(vu >> 32) != ep_prev) ok &= slab_poll(gu, ep_prev, a.err, vu);
+                        if (!ok) {
+                            __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(flag + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                        if (need_lo) sw.Zm = (uint32_t)vl;
+                        if (need_hi) sw.Zp = (uint32_t)vu;
+                    };
+                    const uint32_t flips = flip_mask_lds<W>(step, quad0, tab, [&]() {
+                        ghosts();
+                        return sw.decide((y + zg + c) & 1);
+                    });
+                    const uint32_t v = sw.S ^ flips;
                     P.own[base + q] = v;
                     if (lo || hi)
                         __hip_atomic_store(pub + (size_t)zg * PL, ((unsigned long long)ep_now << 32) | v,
@@ -392,10 +351,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 }
             }
             __syncthreads();
-            if (flag[1]) {
-                if (tid == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return;  // after an error the run's state is undefined
-            }
+            if (flag[1]) return;  // after an error the run's state is undefined
         }
     } else {
         // g half-steps per exchange on the shrinking extended region of the
@@ -415,7 +371,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 const uint32_t t = run.t0 + (j_half >> 1);
                 const int c = r ^ (int)(j_half & 1u);
                 const bool publish = k >= G - 1;  // the colour's last update in this cycle
-                const PhiloxStep step =
+                const PhiloxStep<true> step =
                     philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), run.sample, run.k0, run.k1);
                 const SlabPlanes P = slab_planes(lspin, lbond, EM * PL, c);
                 const int n_items = E - 2 * k;
@@ -425,9 +381,10 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                         const int zg = wrap(zb + e, L);
                         SlabWord<W> sw;
                         sw.load(P, e * PL, q, qm, qp, qym, qyp, PL);
-                        sw.draw(step, (uint32_t)(((y + L * zg) * R + w * W) >> 2));
-                        const uint32_t v =
-                            sw.template update<SCREEN>((y + zg + c) & 1, run.thr1, run.thr2, run.thr3, tab);
+                        const uint32_t flips =
+                            flip_mask_lds<W>(step, (uint32_t)(((y + L * zg) * R + w * W) >> 2), tab,
+                                             [&]() { return sw.decide((y + zg + c) & 1); });
+                        const uint32_t v = sw.S ^ flips;
                         P.own[e * PL + q] = v;
                         // owned planes within g of a face are read by the neighbours
                         if (publish && it < s && (e - g < g || g + s - 1 - e < g))
