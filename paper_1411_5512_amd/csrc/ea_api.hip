@@ -283,7 +283,7 @@ struct ea_sim {
     uint32_t *snaps = nullptr;
     unsigned long long *meas = nullptr;
     uint32_t *t_dev = nullptr;  // device copy of the sweep counter base
-    std::vector<unsigned long long> host_meas;
+    std::vector<unsigned long long> host_meas, meas_before;  // the counters now and at the measurement before
     // captured graph of kGraphSweeps sweeps (built on first use)
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
@@ -339,18 +339,23 @@ unsigned blocks_for(size_t n, unsigned bs = 256) { return (unsigned)((n + bs - 1
     }
 
 ea_status launch_init_lattice(const ea::Lattice &lat, const ea::Geom &g, int W, uint64_t seed, uint32_t sample,
-                              uint64_t pcut, hipStream_t stream)
+                              uint64_t pcut, hipStream_t stream, uint32_t *err = nullptr,
+                              unsigned long long *clear = nullptr, int n_clear = 0)
 {
     dim3 grid(blocks_for(g.plane), 5, 2);
     EA_DISPATCH_W(W, hipLaunchKernelGGL((ea::init_kernel<WW>), grid, dim3(256), 0, stream, lat, g,
-                                        (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32), sample, pcut));
+                                        (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32), sample, pcut, err,
+                                        clear, n_clear));
     EA_HIP(hipGetLastError());
     return EA_OK;
 }
 
+// Initial state, error word and measurement counters.
 ea_status launch_init(ea_sim *s)
 {
-    return launch_init_lattice(s->lat, s->geom(), s->lay.W, s->seed, s->sample, s->pcut, s->stream);
+    std::fill(s->meas_before.begin(), s->meas_before.end(), 0);
+    return launch_init_lattice(s->lat, s->geom(), s->lay.W, s->seed, s->sample, s->pcut, s->stream, s->err_dev,
+                               s->meas, (int)s->lay.meas_count);
 }
 
 // Half-step launches with at least this many threads (four waves per SIMD
@@ -657,6 +662,12 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
     return EA_OK;
 }
 
+ea_status slab_gave_up()
+{
+    return fail(EA_ERR_DEVICE, "a slab launch gave up waiting for a neighbouring slab (its workgroups were not all "
+                               "resident within seconds); the run's state is undefined until ea_reset");
+}
+
 // After a synchronisation: EA_ERR_DEVICE if a slab launch of the run gave up
 // waiting for a neighbouring slab (the run's state is then undefined until
 // ea_reset).
@@ -665,10 +676,7 @@ ea_status slab_check(ea_sim *s)
     if (!s->slab_used) return EA_OK;
     uint32_t e = 0;
     EA_HIP(hipMemcpy(&e, s->err_dev, 4, hipMemcpyDeviceToHost));
-    if (e)
-        return fail(EA_ERR_DEVICE, "a slab launch gave up waiting for a neighbouring slab (its workgroups were not "
-                                   "all resident within seconds); the run's state is undefined until ea_reset");
-    return EA_OK;
+    return e ? slab_gave_up() : EA_OK;
 }
 
 // Shell sums of dense overlap rows (ea_shells.h) for any L up to 256.
@@ -927,6 +935,7 @@ ea_status ea_create_ex(const ea_config *cfg, ea_sim **out)
     s->snap_t.assign((size_t)s->n_slots, 0);
     s->snap_taken.assign((size_t)s->n_slots, 0);
     s->host_meas.assign(lay.meas_count, 0);
+    s->meas_before.assign(lay.meas_count, 0);
     host_thresholds(cfg->T, s->thr);
     s->pcut = (uint64_t)std::floor(std::ldexp(cfg->p, 32));
 
@@ -962,7 +971,6 @@ ea_status ea_create_ex(const ea_config *cfg, ea_sim **out)
     s->t_dev = (uint32_t *)(s->buf + lay.off_ctl + kCtlTime);
     s->err_dev = (uint32_t *)(s->buf + lay.off_ctl + kCtlErr);
     s->xbuf = lay.xbuf_entries ? (unsigned long long *)(s->buf + lay.off_xbuf) : nullptr;
-    hipLaunchKernelGGL(ea::zero_u32_kernel, dim3(1), dim3(64), 0, s->stream, s->err_dev, (size_t)1);
 
     ea_status st = launch_init(s);
     if (st != EA_OK) {
@@ -1004,7 +1012,6 @@ ea_status ea_reset(ea_sim *s, uint64_t seed, uint32_t sample)
     if (s->graph) (void)hipGraphDestroy(s->graph);
     s->graph_exec = nullptr;
     s->graph = nullptr;
-    hipLaunchKernelGGL(ea::zero_u32_kernel, dim3(1), dim3(64), 0, s->stream, s->err_dev, (size_t)1);
     return launch_init(s);
 }
 
@@ -1168,21 +1175,23 @@ ea_status ea_measure(ea_sim *s, ea_obs *out)
     ea::Geom g = s->geom();
     const size_t c4_base = ea::M_AUTO + 2 * (size_t)kMaxSlots;
     const size_t n_count = c4_base + 3 * (size_t)(y.R + 1);
-    hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for(n_count)), dim3(256), 0, s->stream, s->meas, n_count);
     const int slots = out->autocorr ? s->n_slots : 0;
-    EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::measure_kernel<WW>), dim3(blocks_for(2 * (size_t)g.plane)),
-                                           dim3(256), 0, s->stream, s->lat, g, s->snaps, slots, s->meas));
-    if (out->c4) {
-        dim3 grid(blocks_for(2 * (size_t)g.rows), 3 * (unsigned)ea::c4_chunks(y.R), 1);
-        EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::c4_kernel<WW>), grid, dim3(256), 0, s->stream,
-                                               s->lat, g, s->meas + c4_base));
-    }
+    const int nb = (int)std::min<unsigned>(blocks_for(2 * (size_t)g.plane, ea::kMeasThreads), ea::kMeasBlocks);
+    const dim3 grid((unsigned)(nb * (1 + slots) + (out->c4 ? 3 * y.L : 0)));
+    EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::measure_kernel<WW>), grid, dim3(ea::kMeasThreads), 0, s->stream,
+                                           s->lat, g, s->snaps, nb, slots, s->meas, (int)c4_base, s->err_dev));
     EA_HIP(hipGetLastError());
     EA_HIP(hipMemcpyAsync(s->host_meas.data(), s->meas, n_count * sizeof(unsigned long long),
                           hipMemcpyDeviceToHost, s->stream));
     EA_HIP(hipStreamSynchronize(s->stream));
-    ea_status est = slab_check(s);
-    if (est != EA_OK) return est;
+    const bool gave_up = s->host_meas[c4_base] != 0;
+    s->host_meas[c4_base] = 0;
+    for (size_t i = 0; i < n_count; ++i) {  // this measurement's counts
+        const unsigned long long now = s->host_meas[i];
+        s->host_meas[i] -= s->meas_before[i];
+        s->meas_before[i] = now;
+    }
+    if (gave_up) return slab_gave_up();
 
     const int64_t N = (int64_t)y.L * y.L * y.L;
     const unsigned long long *m = s->host_meas.data();

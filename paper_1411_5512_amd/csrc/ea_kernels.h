@@ -33,11 +33,18 @@ __device__ __forceinline__ size_t plane_off(const Geom &g, int a, int c)
 // uniformly random spins.  One thread per (row, word) of one colour; grid.y
 // selects what is drawn: 0..2 the coupling planes of direction d, 3..4 the
 // spins of replica 0 / 1; grid.z the colour.
+// The first block also clears the caller's error word and n_clear counters
+// (err may be null).
 template <int W>
 __global__ __launch_bounds__(256) void init_kernel(Lattice lat, Geom g, uint32_t k0, uint32_t k1,
-                                                   uint32_t sample, uint64_t pcut)
+                                                   uint32_t sample, uint64_t pcut, uint32_t *err,
+                                                   unsigned long long *clear, int n_clear)
 {
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
+    if (err && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
+        if (threadIdx.x == 0) *err = 0u;
+        for (int i = threadIdx.x; i < n_clear; i += blockDim.x) clear[i] = 0ull;
+    }
     if (tid >= g.plane) return;
     const int what = blockIdx.y;
     const int c = blockIdx.z;
@@ -242,23 +249,6 @@ __device__ __forceinline__ void wave_add(unsigned long long *dst, uint32_t v)
     if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, (unsigned long long)v);
 }
 
-// The same for a whole 256-thread block: one atomic per block instead of
-// one per wave, since every wave of a launch adds into the same few counters
-// and atomics on one address serialise.  Every thread of the block calls it,
-// the same number of times (it synchronises the block).
-__device__ __forceinline__ void block_add(unsigned long long *dst, uint32_t v)
-{
-    __shared__ uint32_t part[256 / 64];
-    v = wave_sum(v);
-    __syncthreads();  // the previous call has read part
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t t = part[0] + part[1] + part[2] + part[3];
-        if (t) atomicAdd(dst, (unsigned long long)t);
-    }
-}
-
 // Counter layout of one measurement (all uint64):
 //   [0,1] unsatisfied bonds of replica 0/1
 //   [2,3] spins with S = -1, replica 0/1
@@ -267,53 +257,6 @@ __device__ __forceinline__ void block_add(unsigned long long *dst, uint32_t v)
 // followed by the C4 block: [c4_base + d (R+1) + rho] sites with q(s) != q(s + rho e_d).
 enum { M_UNSAT = 0, M_DOWN = 2, M_QDIFF = 4, M_AUTO = 5 };
 
-// One thread per (colour, row, word) of the whole lattice: grid.x covers
-// 2 * plane threads.  snaps = [slot][replica][colour][plane].
-template <int W>
-__global__ __launch_bounds__(256) void measure_kernel(Lattice lat, Geom g, const uint32_t *snaps,
-                                                      int n_slots, unsigned long long *acc)
-{
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = gid < 2 * g.plane;
-    const int c = live ? gid / g.plane : 0;
-    const int tid = live ? gid - c * g.plane : 0;
-    const int row = tid / g.RW;
-    const int w = tid - row * g.RW;
-    const int y = row % g.L;
-    const int z = row / g.L;
-    const int par = (y + z + c) & 1;
-    const int wp = w == g.RW - 1 ? 0 : w + 1;
-    const int row_yp = wrap(y + 1, g.L) + g.L * z;
-    const int row_zp = y + g.L * wrap(z + 1, g.L);
-    const int base = row * g.RW;
-
-    uint32_t S[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const uint32_t *own = lat.spins + plane_off(g, r, c);
-        const uint32_t *oth = lat.spins + plane_off(g, r, c ^ 1);
-        S[r] = live ? own[base + w] : 0u;
-        uint32_t unsat = 0;
-        if (live) {
-            const uint32_t O = oth[base + w], Op = oth[base + wp];
-            const uint32_t xp = par ? take_plus1<W>(O, Op) : O;
-            unsat = __popc(S[r] ^ xp ^ lat.bonds[plane_off(g, 0, c) + base + w]) +
-                    __popc(xor3(S[r], oth[row_yp * g.RW + w], lat.bonds[plane_off(g, 1, c) + base + w])) +
-                    __popc(xor3(S[r], oth[row_zp * g.RW + w], lat.bonds[plane_off(g, 2, c) + base + w]));
-        }
-        block_add(acc + M_UNSAT + r, unsat);
-        block_add(acc + M_DOWN + r, __popc(S[r]));
-    }
-    block_add(acc + M_QDIFF, __popc(S[0] ^ S[1]));
-    for (int k = 0; k < n_slots; ++k) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const uint32_t ref = live ? snaps[((size_t)k * 2 + r) * 2 * g.plane + plane_off(g, 0, c) + tid] : 0u;
-            block_add(acc + M_AUTO + 2 * k + r, __popc(S[r] ^ ref));
-        }
-    }
-}
-
 // q = S_0 xor S_1 of word w of a packed row.
 __device__ __forceinline__ uint32_t q_word(const Lattice &lat, const Geom &g, int c, int row, int w)
 {
@@ -321,62 +264,174 @@ __device__ __forceinline__ uint32_t q_word(const Lattice &lat, const Geom &g, in
     return lat.spins[plane_off(g, 0, c) + i] ^ lat.spins[plane_off(g, 1, c) + i];
 }
 
-// C4 block (eq. 3): one thread per (colour, row) and chunk of kC4Rho
-// consecutive displacements rho along one axis d; grid.y = d nchunk + chunk,
-// nchunk = ceil((R + 1) / kC4Rho).  The thread reads each of its q words once
-// and compares it with the partner word of every rho of its chunk, then each
-// rho's count is summed over the wave.  The partner of site (x,y,z) is
-// (x,y,z) + rho e_d, of colour c ^ (rho & 1).  Along y and z it sits at the
-// same half index of the partner row; along x, on a row with x = 2 xh + par,
-// its half index is xh + rho/2 (rho even) or xh + (rho-1)/2 + par (rho odd),
-// modulo R.
-constexpr int kC4Rho = 8;
+// A measurement in one launch.  Its blocks, in order:
+//   nb blocks           unsatisfied bonds, down spins, the overlap
+//   n_slots * nb        the autocorrelation with slot k
+//   3 L (c4 wanted)     the axis correlations: L blocks per axis, one plane
+//                       of lines each
+// The counters are added to, never cleared: the caller subtracts what they
+// held before (a clearing launch costs as much as the measurement of a small
+// lattice).  The slabs' error word rides along in the C4 block's rho = 0
+// entry, whose count is 0 by definition, so that one copy brings everything.
+//
+// Bounds, at L = 256: 2 x 10 MB read and 2 x 10^8 XOR-popcounts.  One block
+// row per displacement and block sums for every quantity took 700 + 170 us
+// there (60 + 24 us at L = 128); now each line is read once into LDS and each
+// thread keeps one displacement.  A whole ea_measure call, before and now:
+// L = 16 39 -> 28 us, L = 64 62 -> 35, L = 128 108 -> 46, L = 256 830 -> 102.
+constexpr int kMeasThreads = 256;
+constexpr int kMeasBlocks = 512;  // at most, per quantity: more only adds atomics on the same counters
 
-__host__ __device__ constexpr int c4_chunks(int R) { return (R + kC4Rho) / kC4Rho; }
-
+// 32 bits of the periodic q row (c, row) of R bits, from bit `start` (< 2R) on.
 template <int W>
-__global__ __launch_bounds__(256) void c4_kernel(Lattice lat, Geom g, unsigned long long *acc)
+__device__ __forceinline__ uint32_t q_bits(const Lattice &lat, const Geom &g, int c, int row, int start)
 {
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = gid < 2 * g.rows;
-    const int nchunk = c4_chunks(g.R);
-    const int d = blockIdx.y / nchunk;
-    const int r0 = (blockIdx.y - d * nchunk) * kC4Rho;
-    uint32_t diff[kC4Rho];
+    int pos = start >= g.R ? start - g.R : start;
+    uint32_t out = 0;
+    for (int have = 0; have < 32;) {
+        const int w = pos / W, off = pos - w * W;
+        out |= (q_word(lat, g, c, row, w) >> off) << have;
+        have += W - off;
+        pos = (w + 1) * W;
+        if (pos == g.R) pos = 0;
+    }
+    return out;
+}
+
+__device__ __forceinline__ int meas_row_words(int R) { return (R + 31) / 32; }
+// Words of a row repeated far enough for every shift up to R / 2 + 1.
+__device__ __forceinline__ int meas_shift_words(int R) { return (R + R / 2 + 66) / 32 + 1; }
+
+// One plane of L lines along axis D (0 x, 1 y, 2 z): the q words of both
+// colours go to LDS -- along x every row, repeated periodically; along y and
+// z column-wise, twice, so that the line shifted by rho is contiguous -- and
+// thread (part, rho) counts displacement rho = 1 .. R over its part of the
+// plane.  The partner of site (x,y,z) is (x,y,z) + rho e_d, of colour
+// c ^ (rho & 1).  Along y and z it sits at the same half index of the partner
+// row; along x, on a row with x = 2 xh + par, its half index is xh + rho/2
+// (rho even) or xh + (rho-1)/2 + par (rho odd), modulo R.
+template <int W>
+__device__ __forceinline__ void measure_axis(const Lattice &lat, const Geom &g, int D, int o, uint32_t *lds,
+                                             uint32_t *sums, unsigned long long *acc)
+{
+    const int tid = (int)threadIdx.x, L = g.L, R = g.R;
+    const int nw = meas_row_words(R);
+    const uint32_t last = (R & 31) ? (1u << (R & 31)) - 1u : 0xffffffffu;  // sites of a row's last word
+    const int parts = kMeasThreads / R, part = tid / R, rho = 1 + tid - part * R;
+    const int odd = rho & 1;
+    for (int i = tid; i < R; i += kMeasThreads) sums[i] = 0u;
+    uint32_t diff = 0;
+    if (D == 0) {
+        // lds[c][y][nx]: plane z = o
+        const int nx = meas_shift_words(R);
+        for (int i = tid; i < 2 * L * nx; i += kMeasThreads) {
+            const int j = i % nx, k = i / nx, y = k % L, c = k / L;
+            lds[i] = q_bits<W>(lat, g, c, y + L * o, (32 * j) % R);
+        }
+        __syncthreads();
+        if (part < parts)
+            for (int y = part; y < L; y += parts) {
 #pragma unroll
-    for (int k = 0; k < kC4Rho; ++k) diff[k] = 0u;
-    if (live) {
-        const int c = gid / g.rows;
-        const int row = gid - c * g.rows;
-        const int y = row % g.L;
-        const int z = row / g.L;
-        const int par = (y + z + c) & 1;
-        for (int w = 0; w < g.RW; ++w) {
-            const uint32_t own = q_word(lat, g, c, row, w);
-#pragma unroll
-            for (int k = 0; k < kC4Rho; ++k) {
-                const int rho = r0 + k;
-                if (rho > g.R) break;  // uniform: the chunk's tail past R
-                const int cp = c ^ (rho & 1);
-                if (d == 0) {
-                    const int kx = (rho & 1) ? (rho - 1) / 2 + par : rho / 2;
-                    const int start = (w * W + kx) % g.R;
-                    const int wi = start / W;
-                    const int off = start - wi * W;
-                    const uint32_t lo = q_word(lat, g, cp, row, wi);
-                    const uint32_t hi = q_word(lat, g, cp, row, wi + 1 == g.RW ? 0 : wi + 1);
-                    const uint32_t win = off == 0 ? lo : (((lo >> off) | (hi << (W - off))) & word_mask<W>());
-                    diff[k] += __popc(own ^ win);
-                } else {
-                    const int prow = d == 1 ? (y + rho) % g.L + g.L * z : y + g.L * ((z + rho) % g.L);
-                    diff[k] += __popc(own ^ q_word(lat, g, cp, prow, w));
+                for (int c = 0; c < 2; ++c) {
+                    const int sh = (rho >> 1) + (odd ? (y + o + c) & 1 : 0);
+                    const uint32_t *own = lds + (c * L + y) * nx;
+                    const uint32_t *other = lds + ((c ^ odd) * L + y) * nx + (sh >> 5);
+                    uint32_t prev = other[0];
+                    for (int j = 0; j < nw; ++j) {
+                        const uint32_t next = other[j + 1];
+                        const uint32_t win = __builtin_amdgcn_alignbit(next, prev, (uint32_t)sh & 31u);
+                        diff += __popc((own[j] ^ win) & (j + 1 == nw ? last : 0xffffffffu));
+                        prev = next;
+                    }
                 }
             }
+    } else {
+        // lds[c][word][2L]: along y the plane z = o, along z the plane y = o
+        for (int i = tid; i < 2 * nw * L; i += kMeasThreads) {
+            const int j = i % nw, k = i / nw, n = k % L, c = k / L;
+            const int row = D == 1 ? n + L * o : o + L * n;
+            const uint32_t v = q_bits<W>(lat, g, c, row, 32 * j) & (j + 1 == nw ? last : 0xffffffffu);
+            uint32_t *dst = lds + (c * nw + j) * 2 * L + n;
+            dst[0] = v;
+            dst[L] = v;
         }
+        __syncthreads();
+        if (part < parts)
+            for (int cj = 0; cj < 2 * nw; ++cj) {
+                const int c = cj >= nw ? 1 : 0, j = cj - c * nw;
+                const uint32_t *own = lds + (c * nw + j) * 2 * L;
+                const uint32_t *other = lds + ((c ^ odd) * nw + j) * 2 * L + rho;
+                for (int n = part; n < L; n += parts) diff += __popc(own[n] ^ other[n]);
+            }
     }
+    if (part < parts) atomicAdd(sums + rho - 1, diff);
+    __syncthreads();
+    for (int i = tid; i < R; i += kMeasThreads)
+        if (sums[i]) atomicAdd(acc + D * (R + 1) + 1 + i, (unsigned long long)sums[i]);
+}
+
+template <int W>
+__global__ __launch_bounds__(kMeasThreads) void measure_kernel(Lattice lat, Geom g, const uint32_t *snaps, int nb,
+                                                               int n_slots, unsigned long long *acc, int c4_base,
+                                                               const uint32_t *err)
+{
+    // 2 colours x 256 rows x 9 words (x), 2 x 4 words x 512 (y, z)
+    __shared__ uint32_t lds[2 * 256 * 9];
+    __shared__ uint32_t sums[128];
+    const int tid = (int)threadIdx.x;
+    int b = (int)blockIdx.x;
+    if (b >= nb * (1 + n_slots)) {
+        b -= nb * (1 + n_slots);
+        measure_axis<W>(lat, g, b / g.L, b % g.L, lds, sums, acc + c4_base);
+        return;
+    }
+    const int k = b / nb - 1;  // -1: the configuration itself, else a slot
+    b -= (k + 1) * nb;
+    uint32_t cnt[5] = {0u, 0u, 0u, 0u, 0u};
+    if (k < 0) {
+        if (b == 0 && tid == 0) acc[c4_base] = *err;
+        for (int gid = b * kMeasThreads + tid; gid < 2 * g.plane; gid += nb * kMeasThreads) {
+            const int c = gid >= g.plane ? 1 : 0;
+            const int at = gid - c * g.plane;
+            const int row = at / g.RW;
+            const int w = at - row * g.RW;
+            const int z = row / g.L, y = row - z * g.L;
+            const int par = (y + z + c) & 1;
+            const int wp = w == g.RW - 1 ? at - w : at + 1;
+            const int yp = y == g.L - 1 ? at - (g.L - 1) * g.RW : at + g.RW;
+            const int zp = z == g.L - 1 ? at - (g.L - 1) * g.L * g.RW : at + g.L * g.RW;
+            const uint32_t Bx = lat.bonds[plane_off(g, 0, c) + at], By = lat.bonds[plane_off(g, 1, c) + at],
+                           Bz = lat.bonds[plane_off(g, 2, c) + at];
+            uint32_t S[2];
 #pragma unroll
-    for (int k = 0; k < kC4Rho; ++k)
-        if (r0 + k <= g.R) block_add(acc + d * (g.R + 1) + r0 + k, diff[k]);
+            for (int r = 0; r < 2; ++r) {
+                const uint32_t *oth = lat.spins + plane_off(g, r, c ^ 1);
+                S[r] = lat.spins[plane_off(g, r, c) + at];
+                const uint32_t O = oth[at];
+                const uint32_t xp = par ? take_plus1<W>(O, oth[wp]) : O;
+                cnt[M_UNSAT + r] += __popc(xor3(S[r], xp, Bx)) + __popc(xor3(S[r], oth[yp], By)) +
+                                    __popc(xor3(S[r], oth[zp], Bz));
+                cnt[M_DOWN + r] += __popc(S[r]);
+            }
+            cnt[M_QDIFF] += __popc(S[0] ^ S[1]);
+        }
+    } else {
+        const uint32_t *ref = snaps + (size_t)k * 4 * (size_t)g.plane;
+        for (int r = 0; r < 2; ++r)
+            for (int i = b * kMeasThreads + tid; i < 2 * g.plane; i += nb * kMeasThreads)
+                cnt[r] += __popc(lat.spins[plane_off(g, r, 0) + i] ^ ref[plane_off(g, r, 0) + i]);
+    }
+    // one atomic per block and quantity
+    if (tid < 5) sums[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const uint32_t v = wave_sum(cnt[i]);
+        if ((tid & 63) == 0 && v) atomicAdd(sums + i, v);
+    }
+    __syncthreads();
+    const int n = k < 0 ? 5 : 2, first = k < 0 ? 0 : M_AUTO + 2 * k;
+    if (tid < n && sums[tid]) atomicAdd(acc + first + tid, (unsigned long long)sums[tid]);
 }
 
 // --------------------------------------------------------------------------
