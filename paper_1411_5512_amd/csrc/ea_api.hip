@@ -292,6 +292,7 @@ struct ea_sim {
     // shells, and the FFT route's complex array
     unsigned long long *c4_scratch = nullptr;
     void *fft_work = nullptr;
+    void *io = nullptr;  // conversion buffer of lattices without a slab exchange area (io_buffer)
     // event ordering this run's stream with a group sweep (created on first use)
     hipEvent_t group_event = nullptr;
     // persistent slab path: plan (slabs per replica: 0 automatic, -1 off;
@@ -993,6 +994,7 @@ void ea_destroy(ea_sim *s)
     if (s->graph) (void)hipGraphDestroy(s->graph);
     if (s->c4_scratch) (void)hipFree(s->c4_scratch);
     if (s->fft_work) (void)hipFree(s->fft_work);
+    if (s->io) (void)hipFree(s->io);
     if (s->group_event) (void)hipEventDestroy(s->group_event);
     if (s->own_buf && s->buf) (void)hipFree(s->buf);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -1511,79 +1513,129 @@ ea_status ea_tune_plain(int32_t L, int32_t force, int32_t *chosen_rw, ea_tune_ch
     return EA_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Device bytes in which a run's int8 arrays are converted: the slab exchange
+// area, which is idle between launches (and cleared before the next one), or
+// for lattices without one a buffer kept from the first call on.
+ea_status io_buffer(ea_sim *s, char **buf, size_t *bytes)
+{
+    if (s->xbuf) {
+        s->xbuf_clean = false;
+        *buf = (char *)s->xbuf;
+        *bytes = 8 * s->lay.xbuf_entries;
+        return EA_OK;
+    }
+    *bytes = (size_t)s->lay.L * s->lay.L * s->lay.L;
+    if (!s->io) {
+        const hipError_t e = hipMalloc(&s->io, *bytes);
+        if (e != hipSuccess) {
+            s->io = nullptr;
+            return fail(EA_ERR_NOMEM, "hipMalloc(conversion buffer, %zu bytes): %s", *bytes, hipGetErrorString(e));
+        }
+    }
+    *buf = (char *)s->io;
+    return EA_OK;
+}
+
+// Packed planes to the caller's array and back, nd bytes per site, as many
+// rows at a time as the buffer holds.  Both wait for the stream.
+template <int ND>
+ea_status copy_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
+{
+    char *buf = nullptr;
+    size_t cap = 0;
+    ea_status st = io_buffer(s, &buf, &cap);
+    if (st != EA_OK) return st;
+    const Layout &y = s->lay;
+    const ea::Geom g = s->geom();
+    const size_t row_bytes = (size_t)ND * (size_t)y.L;
+    const int step = (int)std::min<size_t>((size_t)y.rows, cap / row_bytes);
+    for (int row = 0; row < y.rows; row += step) {
+        const int n = std::min(step, y.rows - row);
+        EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::to_pm1_kernel<WW, ND>), dim3(blocks_for((size_t)n * (y.L / 8))),
+                                              dim3(256), 0, s->stream, planes, g, row, n, (uint2 *)buf));
+        EA_HIP(hipGetLastError());
+        EA_HIP(hipMemcpyAsync(pm1 + (size_t)row * row_bytes, buf, (size_t)n * row_bytes, hipMemcpyDeviceToHost,
+                              s->stream));
+    }
+    EA_HIP(hipStreamSynchronize(s->stream));
+    return EA_OK;
+}
+
+template <int ND>
+ea_status copy_pm1_in(ea_sim *s, uint32_t *planes, const int8_t *pm1)
+{
+    char *buf = nullptr;
+    size_t cap = 0;
+    ea_status st = io_buffer(s, &buf, &cap);
+    if (st != EA_OK) return st;
+    const Layout &y = s->lay;
+    const ea::Geom g = s->geom();
+    const size_t row_bytes = (size_t)ND * (size_t)y.L;
+    const int step = (int)std::min<size_t>((size_t)y.rows, cap / row_bytes);
+    for (int row = 0; row < y.rows; row += step) {
+        const int n = std::min(step, y.rows - row);
+        EA_HIP(hipMemcpyAsync(buf, pm1 + (size_t)row * row_bytes, (size_t)n * row_bytes, hipMemcpyHostToDevice,
+                              s->stream));
+        EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::from_pm1_kernel<WW, ND>), dim3(blocks_for((size_t)n * y.RW)),
+                                              dim3(256), 0, s->stream, planes, g, row, n, (const uint2 *)buf));
+        EA_HIP(hipGetLastError());
+    }
+    EA_HIP(hipStreamSynchronize(s->stream));
+    return EA_OK;
+}
+
+// Index of the first of n values that is not +-1, or n.
+size_t first_not_pm1(const int8_t *v, size_t n)
+{
+    for (size_t at = 0; at < n;) {
+        const size_t end = std::min(n, at + 4096);
+        unsigned bad = 0;
+        for (size_t i = at; i < end; ++i) bad |= (unsigned)((v[i] != 1) & (v[i] != -1));
+        if (bad)
+            for (size_t i = at; i < end; ++i)
+                if (v[i] != 1 && v[i] != -1) return i;
+        at = end;
+    }
+    return n;
+}
+
+}  // namespace
+
+extern "C" {
+
 ea_status ea_get_spins(ea_sim *s, int32_t r, int8_t *pm1)
 {
     if (!s || !pm1) return fail(EA_ERR_ARG, "NULL argument");
     if (r < 0 || r > 1) return fail(EA_ERR_ARG, "replica %d not 0 or 1", r);
-    const Layout &y = s->lay;
-    std::vector<uint32_t> words(2 * (size_t)y.plane);
-    EA_HIP(hipMemcpyAsync(words.data(), s->lat.spins + (size_t)r * 2 * y.plane, words.size() * 4,
-                          hipMemcpyDeviceToHost, s->stream));
-    EA_HIP(hipStreamSynchronize(s->stream));
-    ea_status est = slab_check(s);
-    if (est != EA_OK) return est;
-    const int64_t N = (int64_t)y.L * y.L * y.L;
-    for (int64_t i = 0; i < N; ++i) {
-        SiteAddr a = address_of(y, i);
-        const uint32_t bit = (words[(size_t)a.c * y.plane + a.word] >> a.bit) & 1u;
-        pm1[i] = bit ? (int8_t)-1 : (int8_t)1;
-    }
-    return EA_OK;
+    ea_status st = copy_pm1_out<1>(s, s->lat.spins + (size_t)r * 2 * s->lay.plane, pm1);
+    return st != EA_OK ? st : slab_check(s);
 }
 
 ea_status ea_set_spins(ea_sim *s, int32_t r, const int8_t *pm1)
 {
     if (!s || !pm1) return fail(EA_ERR_ARG, "NULL argument");
     if (r < 0 || r > 1) return fail(EA_ERR_ARG, "replica %d not 0 or 1", r);
-    const Layout &y = s->lay;
-    const int64_t N = (int64_t)y.L * y.L * y.L;
-    std::vector<uint32_t> words(2 * (size_t)y.plane, 0u);
-    for (int64_t i = 0; i < N; ++i) {
-        if (pm1[i] != 1 && pm1[i] != -1) return fail(EA_ERR_ARG, "spin %lld is %d, not +-1", (long long)i, pm1[i]);
-        SiteAddr a = address_of(y, i);
-        if (pm1[i] == -1) words[(size_t)a.c * y.plane + a.word] |= 1u << a.bit;
-    }
-    EA_HIP(hipMemcpyAsync(s->lat.spins + (size_t)r * 2 * y.plane, words.data(), words.size() * 4,
-                          hipMemcpyHostToDevice, s->stream));
-    EA_HIP(hipStreamSynchronize(s->stream));
-    return EA_OK;
+    const size_t n = (size_t)s->lay.L * s->lay.L * s->lay.L, bad = first_not_pm1(pm1, n);
+    if (bad < n) return fail(EA_ERR_ARG, "spin %lld is %d, not +-1", (long long)bad, pm1[bad]);
+    return copy_pm1_in<1>(s, s->lat.spins + (size_t)r * 2 * s->lay.plane, pm1);
 }
 
 ea_status ea_get_bonds(ea_sim *s, int8_t *pm1)
 {
     if (!s || !pm1) return fail(EA_ERR_ARG, "NULL argument");
-    const Layout &y = s->lay;
-    std::vector<uint32_t> words(y.bond_words);
-    EA_HIP(hipMemcpyAsync(words.data(), s->lat.bonds, words.size() * 4, hipMemcpyDeviceToHost, s->stream));
-    EA_HIP(hipStreamSynchronize(s->stream));
-    const int64_t N = (int64_t)y.L * y.L * y.L;
-    for (int64_t i = 0; i < N; ++i) {
-        SiteAddr a = address_of(y, i);
-        for (int d = 0; d < 3; ++d) {
-            const uint32_t bit = (words[((size_t)d * 2 + a.c) * y.plane + a.word] >> a.bit) & 1u;
-            pm1[3 * i + d] = bit ? (int8_t)-1 : (int8_t)1;
-        }
-    }
-    return EA_OK;
+    return copy_pm1_out<3>(s, s->lat.bonds, pm1);
 }
 
 ea_status ea_set_bonds(ea_sim *s, const int8_t *pm1)
 {
     if (!s || !pm1) return fail(EA_ERR_ARG, "NULL argument");
-    const Layout &y = s->lay;
-    const int64_t N = (int64_t)y.L * y.L * y.L;
-    std::vector<uint32_t> words(y.bond_words, 0u);
-    for (int64_t i = 0; i < N; ++i) {
-        SiteAddr a = address_of(y, i);
-        for (int d = 0; d < 3; ++d) {
-            const int8_t v = pm1[3 * i + d];
-            if (v != 1 && v != -1) return fail(EA_ERR_ARG, "coupling %lld is %d, not +-1", (long long)(3 * i + d), v);
-            if (v == -1) words[((size_t)d * 2 + a.c) * y.plane + a.word] |= 1u << a.bit;
-        }
-    }
-    EA_HIP(hipMemcpyAsync(s->lat.bonds, words.data(), words.size() * 4, hipMemcpyHostToDevice, s->stream));
-    EA_HIP(hipStreamSynchronize(s->stream));
-    return EA_OK;
+    const size_t n = 3 * (size_t)s->lay.L * s->lay.L * s->lay.L, bad = first_not_pm1(pm1, n);
+    if (bad < n) return fail(EA_ERR_ARG, "coupling %lld is %d, not +-1", (long long)bad, pm1[bad]);
+    return copy_pm1_in<3>(s, s->lat.bonds, pm1);
 }
 
 }  // extern "C"

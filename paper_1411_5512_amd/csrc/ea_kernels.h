@@ -549,6 +549,114 @@ __global__ __launch_bounds__(256) void c4_shell_kernel(const unsigned long long 
     }
 }
 
+// --------------------------------------------------------------------------
+// The caller's int8 +-1 arrays in canonical order.  Eight consecutive x of a
+// row are four half indices of each colour (even x: colour (y + z) & 1), and
+// since words hold whole 4-site blocks, one nibble of one word per colour.
+// Memory bound: 1 byte written or read per site (the conversion on the host,
+// one division-laden address per site, took 80 ms per replica at L = 256).
+
+// Bits 0..3 of even and odd as the bytes +1 / -1 of eight consecutive x.
+__device__ __forceinline__ uint2 pm1_bytes(uint32_t even, uint32_t odd)
+{
+    uint32_t half[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t e = even >> (2 * i), o = odd >> (2 * i);
+        const uint32_t bits = (e & 1u) | (o & 1u) << 8 | (e & 2u) << 15 | (o & 2u) << 23;
+        half[i] = 0x01010101u + bits * 0xFEu;
+    }
+    return make_uint2(half[0], half[1]);
+}
+
+// The reverse: bit i set iff byte 2 i (even) or 2 i + 1 (odd) is negative.
+__device__ __forceinline__ uint32_t pm1_nibble(uint2 b, int odd)
+{
+    const uint32_t lo = b.x >> (odd ? 15 : 7), hi = b.y >> (odd ? 15 : 7);
+    return (lo & 1u) | (lo >> 15 & 2u) | (hi & 1u) << 2 | (hi >> 15 & 2u) << 2;
+}
+
+// Spins (ND = 1, planes = [colour][plane] of one replica) or couplings (ND =
+// 3, planes = [direction][colour][plane]) of rows [row0, row0 + rows) to
+// out[ND per site], from row row0 on.  One thread per eight x of a row.
+template <int W, int ND>
+__global__ __launch_bounds__(256) void to_pm1_kernel(const uint32_t *planes, Geom g, int row0, int rows, uint2 *out)
+{
+    const int per_row = g.L / 8, t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t >= rows * per_row) return;
+    const int row = row0 + t / per_row, k = t % per_row;  // sites xh = 4k .. 4k + 3 of each colour
+    const int y = row % g.L, z = row / g.L, w = 4 * k / W, shift = 4 * k - w * W;
+    const size_t at = (size_t)row * g.RW + (size_t)w;
+    uint2 v[ND];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+        const uint32_t even = planes[plane_off(g, d, (y + z) & 1) + at] >> shift;
+        const uint32_t odd = planes[plane_off(g, d, (y + z + 1) & 1) + at] >> shift;
+        v[d] = pm1_bytes(even, odd);
+    }
+    if constexpr (ND == 1) {
+        out[t] = v[0];
+    } else {
+        // byte 3 x + d of the 24 is byte x of direction d
+        uint32_t b[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            b[i] = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int x = (4 * i + j) / 3, d = (4 * i + j) % 3;
+                b[i] |= ((x < 4 ? v[d].x >> (8 * x) : v[d].y >> (8 * (x - 4))) & 0xffu) << (8 * j);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) out[(size_t)3 * t + i] = make_uint2(b[2 * i], b[2 * i + 1]);
+    }
+}
+
+// The reverse, one thread per packed word of both colours: rows [row0, row0 +
+// rows) of `in` (values +-1, checked by the caller) to the planes.
+template <int W, int ND>
+__global__ __launch_bounds__(256) void from_pm1_kernel(uint32_t *planes, Geom g, int row0, int rows, const uint2 *in)
+{
+    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t >= rows * g.RW) return;
+    const int lrow = t / g.RW, w = t - lrow * g.RW, row = row0 + lrow;
+    const int y = row % g.L, z = row / g.L;
+    uint32_t bits[ND][2];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) bits[d][0] = bits[d][1] = 0u;
+#pragma unroll
+    for (int j = 0; j < W / 4; ++j) {
+        const size_t src = (size_t)lrow * (g.L / 8) + (size_t)(w * (W / 4) + j);
+        if constexpr (ND == 1) {
+            const uint2 b = in[src];
+            bits[0][0] |= pm1_nibble(b, 0) << (4 * j);
+            bits[0][1] |= pm1_nibble(b, 1) << (4 * j);
+        } else {
+            uint32_t b[6];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const uint2 q = in[3 * src + i];
+                b[2 * i] = q.x;
+                b[2 * i + 1] = q.y;
+            }
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+#pragma unroll
+                for (int d = 0; d < ND; ++d) {
+                    const int i = 3 * x + d;
+                    bits[d][x & 1] |= (b[i / 4] >> (8 * (i % 4) + 7) & 1u) << (4 * j + x / 2);
+                }
+        }
+    }
+    const size_t at = (size_t)row * g.RW + (size_t)w;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+        planes[plane_off(g, d, (y + z) & 1) + at] = bits[d][0];
+        planes[plane_off(g, d, (y + z + 1) & 1) + at] = bits[d][1];
+    }
+}
+
 // Plain word copy (snapshots) and fill (clearing counters); kernels rather
 // than runtime memset/memcpy so that the same work can sit in a graph.
 __global__ __launch_bounds__(256) void copy_words_kernel(uint32_t *dst, const uint32_t *src, size_t n)

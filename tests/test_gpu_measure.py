@@ -28,6 +28,7 @@ def test_measurement_equals_its_definition(ea_gpu, L, rw):
     g = ea_gpu.Sim(L, 0.4, 0.9, seed=L, n_slots=2, words_per_row=rw)
     J = rng.choice(pm, size=3 * L ** 3)
     g.set_bonds(J)
+    assert np.array_equal(g.bonds(), J)
     Jd = J.reshape(L, L, L, 3).transpose(3, 0, 1, 2)
     refs = [None, None]
 
@@ -37,6 +38,7 @@ def test_measurement_equals_its_definition(ea_gpu, L, rw):
         S = [a, a * np.where(rng.random(L ** 3) < 0.2, -1, 1).astype(np.int8)]
         for r in (0, 1):
             g.set_spins(r, S[r])
+            assert np.array_equal(g.spins(r), S[r])
         return [s.reshape(L, L, L) for s in S]
 
     def check(S):
@@ -59,3 +61,28 @@ def test_measurement_equals_its_definition(ea_gpu, L, rw):
     refs[1] = None
     check(put())
     g.close()
+
+
+@pytest.mark.parametrize("L,rw", [(16, 0), (64, 0), (128, 16), (256, 0)])
+def test_state_access_between_sweeps_changes_nothing(ea_gpu, L, rw):
+    """Reading and writing back the state between sweeps (its conversion uses
+    the slab exchange area) leaves the trajectory bit for bit as it is."""
+    a, b = (ea_gpu.Sim(L, 0.3, 0.8, seed=7, words_per_row=rw) for _ in range(2))
+    for _ in range(3):
+        a.sweep(5)
+        b.sweep(5)
+        for r in (0, 1):
+            S = a.spins(r)
+            a.set_spins(r, S)
+        a.set_bonds(a.bonds())
+    b.sweep(4)
+    a.sweep(4)
+    for r in (0, 1):
+        assert np.array_equal(a.spins(r), b.spins(r))
+    bad = a.spins(0)
+    bad[-1] = 0
+    with pytest.raises(ea_gpu.EAError, match="not \\+-1"):
+        a.set_spins(0, bad)
+    assert np.array_equal(a.spins(0), b.spins(0))
+    a.close()
+    b.close()
