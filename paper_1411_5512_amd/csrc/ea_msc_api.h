@@ -137,6 +137,29 @@ ea_status msc_build_graph(ea_msc *s)
     return EA_OK;
 }
 
+// Blocks per axis and word set of the C4 kernel: up to one tile each, 128 (with
+// three axes and two word sets three blocks per compute unit; each ends with
+// 32 R atomics, so more blocks cost more than they spread), and enough that a
+// thread's counter of 16 (2^kC4High - 1) words cannot overflow.
+unsigned msc_c4_blocks(const ea::MscGeom &g, const int (&tiles)[3])
+{
+    int want = 128;
+    const int parts = ea::kC4Threads / g.R, rows = (2 * ea::kC4Lines + parts - 1) / parts;  // lines of a tile per thread
+    for (int D = 0; D < 3; ++D) {
+        const int per_tile = rows * ((ea::msc_line(g, D) + 15) / 16);  // ripples per thread
+        const int max_tiles = ((1 << ea::kC4High) - 1) / per_tile;     // per block
+        want = std::max(want, (tiles[D] + max_tiles - 1) / max_tiles);
+    }
+    return (unsigned)std::min(want, std::max(tiles[0], std::max(tiles[1], tiles[2])));
+}
+
+size_t msc_c4_lds(const ea::MscGeom &g)
+{
+    size_t words = 33 * (size_t)g.R;  // the counts
+    for (int D = 0; D < 3; ++D) words = std::max(words, (size_t)2 * ea::kC4Lines * (size_t)ea::msc_line_ext(g, D));
+    return 4 * words;
+}
+
 // Bit of sample b at canonical site (x, y, z) in a word set's plane pair:
 // word index within colour c's plane and bit position.
 struct MscBit {
@@ -337,15 +360,13 @@ ea_status ea_msc_measure(ea_msc *s, ea_obs *out)
     if (any_c4) {
         hipLaunchKernelGGL(ea::msc_q_kernel, dim3(blocks_for(s->spin_words / 2)), dim3(256), 0, s->stream, s->lat, g,
                            s->G, s->q);
-        const unsigned nblk_c4 = (unsigned)std::min<size_t>(blocks_for(2 * (size_t)g.P), 64);
-        const dim3 grid_c4(nblk_c4, (unsigned)(g.R + 1), (unsigned)s->G);
-        const size_t axis = (size_t)(g.R + 1) * s->G * 32;  // counters of one axis
-        EA_DISPATCH_M(s->M, hipLaunchKernelGGL((ea::msc_c4_kernel<MM, 0>), grid_c4, dim3(256), 0, s->stream, s->q,
-                                                g, s->G, c4_acc));
-        EA_DISPATCH_M(s->M, hipLaunchKernelGGL((ea::msc_c4_kernel<MM, 1>), grid_c4, dim3(256), 0, s->stream, s->q,
-                                                g, s->G, c4_acc + axis));
-        EA_DISPATCH_M(s->M, hipLaunchKernelGGL((ea::msc_c4_kernel<MM, 2>), grid_c4, dim3(256), 0, s->stream, s->q,
-                                                g, s->G, c4_acc + 2 * axis));
+        const int nt[3] = {(int)blocks_for((size_t)g.L * g.Lz, ea::kC4Lines),
+                           (int)blocks_for((size_t)g.R * g.Lz, ea::kC4Lines),
+                           (int)blocks_for((size_t)g.R * g.L, ea::kC4Lines)};
+        const dim3 grid_c4(msc_c4_blocks(g, nt), 3, (unsigned)s->G);
+        const size_t lds = msc_c4_lds(g);
+        EA_DISPATCH_M(s->M, hipLaunchKernelGGL((ea::msc_c4_kernel<MM>), grid_c4, dim3(ea::kC4Threads), lds, s->stream,
+                                                s->q, g, s->G, nt[0], nt[1], nt[2], c4_acc));
     }
     EA_HIP(hipGetLastError());
     EA_HIP(hipMemcpyAsync(s->host_meas.data(), s->meas, s->n_count * sizeof(unsigned long long),
