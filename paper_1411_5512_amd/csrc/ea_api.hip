@@ -698,14 +698,15 @@ ea_status launch_shell_rows(const unsigned long long *qd, int L, int n_shells, u
 
 // Route of the full-vector C4 shells (ea_set_shell_route).
 std::atomic<int32_t> g_shell_route{EA_SHELLS_AUTO};
-// automatic route: FFT for L = 2^k or 3 2^k from this side on (at L = 32 the
-// direct kernel is faster: 0.07 against 0.10 ms per call)
-constexpr int kFftAutoMinL = 64;
+// automatic route: FFT from this side on.  A call, direct against FFT: L = 32
+// 66 / 103 us, L = 40 84 / 117, L = 48 123 / 103, L = 56 239 / 123, L = 72 865 /
+// 141, L = 136 22 ms / 0.35, L = 248 773 ms / 1.9.
+constexpr int kFftAutoMinL = 48;
 
 bool shells_by_fft(int L)
 {
     const int32_t r = g_shell_route.load();
-    if (!ea::fft_side(L) || r == EA_SHELLS_DIRECT) return false;
+    if (r == EA_SHELLS_DIRECT) return false;
     return r == EA_SHELLS_FFT || L >= kFftAutoMinL;
 }
 
@@ -754,8 +755,30 @@ void launch_fft_passes(const ea::FftArgs &a, hipStream_t stream)
     hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftSquareZ>), grid, block, 0, stream, a);
     hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftInvY>), half, block, 0, stream, a);
     hipLaunchKernelGGL((ea::fft_bin_kernel<L>), bins, block, 0, stream, a);
-    hipLaunchKernelGGL((ea::fft_shell_sum_kernel<L>), dim3(blocks_for((size_t)(H + 1) * (H + 1) * (H + 1))),
-                       dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(ea::fft_shell_sum_kernel, dim3(blocks_for((size_t)(H + 1) * (H + 1) * (H + 1))), dim3(256), 0,
+                       stream, a, L);
+}
+
+// The same passes at a side with an odd factor above 3.
+void launch_fft_general(const ea::FftArgs &a, int L, hipStream_t stream)
+{
+    ea::FftGeneral f{};
+    f.L = L;
+    f.P = ea::fft_general_p(L);
+    f.m = L / f.P;
+    f.B = ea::fft_lines_per_tile(L);
+    f.LP = L + 1;
+    const int H = L / 2;
+    const dim3 grid((unsigned)(L * L / f.B)), block(ea::kFftThreads);
+    const dim3 half((unsigned)((H + 1) * (L / f.B)));  // tiles of the planes z <= L/2
+    const dim3 bins((unsigned)((H + 1) * ((H + ea::kFftBinY) / ea::kFftBinY)));
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftFwdBitsX>), grid, block, 0, stream, a, f);
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftFwdY>), grid, block, 0, stream, a, f);
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftSquareZ>), grid, block, 0, stream, a, f);
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftInvY>), half, block, 0, stream, a, f);
+    hipLaunchKernelGGL(ea::fft_general_bin_kernel, bins, block, 0, stream, a, f);
+    hipLaunchKernelGGL(ea::fft_shell_sum_kernel, dim3(blocks_for((size_t)(H + 1) * (H + 1) * (H + 1))), dim3(256), 0,
+                       stream, a, L);
 }
 
 // Shell sums of dense overlap rows (dw words per row) through the FFT route
@@ -783,7 +806,7 @@ ea_status launch_fft_shells(const unsigned long long *qd, int dw, int L, int n_s
     case 48: launch_fft_passes<48>(a, stream); break;
     case 96: launch_fft_passes<96>(a, stream); break;
     case 192: launch_fft_passes<192>(a, stream); break;
-    default: return fail(EA_ERR_ARG, "the FFT route of full-vector C4 needs L = 2^k or 3 2^k in 8..256 (L=%d)", L);
+    default: launch_fft_general(a, L, stream); break;
     }
     EA_HIP(hipGetLastError());
     return EA_OK;
@@ -1240,16 +1263,19 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
     ea::Geom g = s->geom();
     EA_DISPATCH_W(s->lay.W, hipLaunchKernelGGL((ea::dense_q_kernel<WW>), dim3(blocks_for(q_words)), dim3(256), 0,
                                                s->stream, s->lat, g, dw, qd));
-    const bool fft = shells_by_fft(L);
-    if (fft) {
-        if (!s->fft_work) {
-            hipError_t e = hipMalloc(&s->fft_work, fft_work_bytes(L));
-            if (e != hipSuccess) {
-                s->fft_work = nullptr;
+    bool fft = shells_by_fft(L);
+    if (fft && !s->fft_work) {
+        hipError_t e = hipMalloc(&s->fft_work, fft_work_bytes(L));
+        if (e != hipSuccess) {
+            s->fft_work = nullptr;
+            if (!ea::fft_general_side(L))
                 return fail(EA_ERR_NOMEM, "hipMalloc(c4 FFT work, %zu bytes): %s", fft_work_bytes(L),
                             hipGetErrorString(e));
-            }
+            (void)hipGetLastError();
+            fft = false;  // sides that once had only the direct route keep it where memory is short
         }
+    }
+    if (fft) {
         ea_status st = launch_fft_shells(qd, dw, L, n_shells, shells, s->fft_work, s->stream);
         if (st != EA_OK) return st;
     } else if (nw <= 2) {

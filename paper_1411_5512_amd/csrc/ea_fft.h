@@ -1,6 +1,7 @@
 // ea_fft.h -- full-vector C4 shells (eq. 3 over every displacement r)
 // through the Wiener-Khinchin theorem, for L = 2^k (8 .. 256) and L = 3 2^k
-// (24 .. 192): with F the 3D DFT of q = S_0 S_1, the unnormalised inverse DFT
+// (24 .. 192), and in a run-time form at the end of this file for the other
+// multiples of 8: with F the 3D DFT of q = S_0 S_1, the unnormalised inverse DFT
 // of |F|^2 is N sum_x q(x) q(x + r) for every r at once.  Five passes over a
 // complex fp64 array of L^3 elements, each transforming whole lines of one
 // axis in LDS, replace the direct kernel's L^6 / 64 word operations by
@@ -472,18 +473,17 @@ __global__ __launch_bounds__(kFftThreads) void fft_bin_kernel(FftArgs a)
 // |z| values adds T over the triple's distinct orderings (all of which lie in
 // the shell p^2 + q^2 + r^2) in one atomic, a sixth as many as one per
 // ordering.  One thread per point of the (L/2 + 1)^3 cube; the others return.
-template <int L>
-__global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a)
+__global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a, int L)
 {
-    constexpr int H1 = L / 2 + 1;
-    const long long *T = fft_sums<L>(a.z);
+    const int H1 = L / 2 + 1;
+    const long long *T = reinterpret_cast<const long long *>(a.z + (size_t)H1 * L * L);  // fft_sums
     const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (t >= H1 * H1 * H1) return;
     const int p = t % H1, q = (t / H1) % H1, r = t / (H1 * H1);
     if (p > q || q > r) return;
     const int k = p * p + q * q + r * r;
     if (k >= a.n_shells) return;
-    auto at = [T](int i, int y, int z) { return T[((size_t)z * H1 + (size_t)y) * H1 + (size_t)i]; };
+    auto at = [T, H1](int i, int y, int z) { return T[((size_t)z * H1 + (size_t)y) * H1 + (size_t)i]; };
     long long sum = at(p, q, r);
     if (p == q && q == r) {
     } else if (p == q) {  // (p, p, r): also (p, r, p), (r, p, p)
@@ -494,6 +494,199 @@ __global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a)
         sum += at(p, r, q) + at(q, p, r) + at(q, r, p) + at(r, p, q) + at(r, q, p);
     }
     atomicAdd(a.shells + k, (unsigned long long)sum);
+}
+
+// --------------------------------------------------------------------------
+// The other sides, L = m P with m odd (5 .. 31) and P = 8, 16 or 32: the same
+// passes with L at run time and each transform in two direct steps.  With
+// position a P + b (a < m, b < P), forward: for every b the m-point sums over
+// a, times exp(-2 pi i b k / L), at k P + b; then for every k the P-point sums
+// over b, at k P + j -- X[k + m j] in an order of its own, which the inverse
+// takes as it is: P-point over j, conjugate twiddle, m-point over k.  m + P
+// complex multiply-adds an element and transform instead of L; the LDS reads
+// of a wave's inputs bound it.  A call against the direct count: L = 72 0.14 ms
+// (0.87), L = 136 0.35 (22), L = 200 0.86 (187), L = 248 1.9 (773).
+struct FftGeneral {
+    int L, m, P, B, LP;  // side = m P; lines per tile; LDS stride of a line
+};
+
+constexpr int kFftGeneralPer = 8;                              // elements per thread, at most
+constexpr int kFftGeneralLds = kFftTile + kFftTile / 8;        // B lines of L + 1 elements: B (L + 1) <= 2048 + B
+
+__host__ __device__ constexpr int fft_general_p(int L) { return L % 32 == 0 ? 32 : (L % 16 == 0 ? 16 : 8); }
+
+// Sides of this form: multiples of 8 up to 256 that fft_side leaves out.
+constexpr bool fft_general_side(int L)
+{
+    return L >= 8 && L <= 256 && L % 8 == 0 && !fft_side(L);
+}
+
+// Sum over i < n of s[base + i stride] w^(i step), w = exp(-+2 pi i / L).
+template <bool INV>
+__device__ __forceinline__ double2 fft_sum(const double2 *s, int n, int stride, const double2 *tw, int step, int L)
+{
+    double2 acc = s[0];
+    int t = 0;
+    for (int i = 1; i < n; ++i) {
+        t += step;
+        t -= t >= L ? L : 0;
+        const double2 x = s[i * stride], w = tw[t];
+        acc = cadd(acc, INV ? cmulc(x, w) : cmul(x, w));
+    }
+    return acc;
+}
+
+// The transform of the first n elements (whole lines) of the tile, in LDS;
+// begins and ends with a barrier.  A step's outputs wait in registers until
+// every thread has read its inputs.
+template <bool INV>
+__device__ __forceinline__ void fft_general_lines(double2 *s, const double2 *tw, const FftGeneral &f, int n, int tid)
+{
+    const int L = f.L, m = f.m, P = f.P;
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+        const bool over_a = (half == 0) != INV;  // the m-point step: first forward, last backward
+        double2 out[kFftGeneralPer];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kFftGeneralPer; ++e) {
+            const int j = tid + e * kFftThreads;
+            if (j >= n) break;
+            const int line = j / L, i = j - line * L, hi = i / P, lo = i - hi * P;
+            const double2 *p = s + line * f.LP;
+            if (over_a) {
+                // output (hi = k or a, lo = b): over the other m-index
+                double2 v = fft_sum<INV>(p + lo, m, P, tw, hi * P, L);
+                if constexpr (!INV) v = cmul(v, tw[lo * hi]);
+                out[e] = v;
+            } else {
+                // output (hi = k, lo = j or b) over the other P-index
+                double2 v = fft_sum<INV>(p + hi * P, P, 1, tw, lo * m, L);
+                if constexpr (INV) v = cmulc(v, tw[lo * hi]);
+                out[e] = v;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kFftGeneralPer; ++e) {
+            const int j = tid + e * kFftThreads;
+            if (j >= n) break;
+            const int line = j / L;
+            s[line * f.LP + (j - line * L)] = out[e];
+        }
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void fft_general_twiddles(double2 *tw, int L, int tid)
+{
+    for (int i = tid; i < L; i += kFftThreads) {
+        double sn, cs;
+        sincospi(2.0 * (double)i / (double)L, &sn, &cs);
+        tw[i] = make_double2(cs, -sn);
+    }
+}
+
+// Passes kFftFwdBitsX .. kFftInvY (fft_pass_kernel): one tile of B lines per
+// workgroup, the same tiles and order in memory.
+template <int OP>
+__global__ __launch_bounds__(kFftThreads) void fft_general_pass_kernel(FftArgs a, FftGeneral f)
+{
+    __shared__ double2 s[kFftGeneralLds];
+    __shared__ double2 tw[256];
+    const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
+    const int L = f.L, B = f.B, tile = B * L, xb = L / B;
+    // element j of the tile: line b, index i along the axis, place in memory
+    auto element = [&](int j, int &b, int &i, size_t &pos) {
+        if (OP == kFftFwdBitsX) {
+            b = j / L;
+            i = j - b * L;
+            pos = (size_t)w * tile + (size_t)j;
+        } else {
+            i = j / B;
+            b = j - i * B;
+            const int o = w / xb, x = (w - o * xb) * B + b;
+            pos = OP == kFftSquareZ ? ((size_t)i * L + (size_t)o) * L + (size_t)x
+                                    : ((size_t)o * L + (size_t)i) * L + (size_t)x;
+        }
+    };
+    fft_general_twiddles(tw, L, tid);
+    for (int j = tid; j < tile; j += kFftThreads) {
+        int b, i;
+        size_t pos;
+        element(j, b, i, pos);
+        double2 v;
+        if constexpr (OP == kFftFwdBitsX) {
+            const size_t row = (size_t)w * B + (size_t)b;
+            const unsigned long long word = a.qd[row * (size_t)a.dw + (size_t)(i >> 6)];
+            v = make_double2((word >> (i & 63)) & 1ull ? -1.0 : 1.0, 0.0);
+        } else {
+            v = a.z[pos];
+        }
+        s[b * f.LP + i] = v;
+    }
+    if constexpr (OP == kFftInvY) {
+        fft_general_lines<true>(s, tw, f, tile, tid);
+    } else {
+        fft_general_lines<false>(s, tw, f, tile, tid);
+        if constexpr (OP == kFftSquareZ) {
+            for (int j = tid; j < tile; j += kFftThreads) {
+                double2 *p = s + (j / L) * f.LP + (j % L);
+                const double2 v = *p;
+                *p = make_double2(v.x * v.x + v.y * v.y, 0.0);
+            }
+            fft_general_lines<true>(s, tw, f, tile, tid);
+        }
+    }
+    for (int j = tid; j < tile; j += kFftThreads) {
+        int b, i;
+        size_t pos;
+        element(j, b, i, pos);
+        if (OP == kFftSquareZ && i > L / 2) continue;
+        a.z[pos] = s[b * f.LP + i];
+    }
+}
+
+// fft_bin_kernel: a workgroup takes kFftBinY values y <= L/2 of one plane z <=
+// L/2 with their mirror rows, transforms them along x and stores the rounded
+// sums T(|x|, |y|, |z|), laid out as fft_sums places them.
+__global__ __launch_bounds__(kFftThreads) void fft_general_bin_kernel(FftArgs a, FftGeneral f)
+{
+    __shared__ double2 s[kFftGeneralLds];
+    __shared__ double2 tw[256];
+    const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
+    const int L = f.L, H = L / 2, nl = 2 * kFftBinY, yb = (H + kFftBinY) / kFftBinY;
+    const int z = w / yb, y0 = (w - z * yb) * kFftBinY;
+    const double inv_n = (double)L * L * L;
+    fft_general_twiddles(tw, L, tid);
+    for (int j = tid; j < nl * L; j += kFftThreads) {
+        const int line = j / L, x = j - line * L, y = y0 + (line >> 1);
+        const bool mirror = (line & 1) != 0;
+        double2 v = make_double2(0.0, 0.0);
+        if (y <= H && (!mirror || (y != 0 && y != H)))
+            v = a.z[((size_t)z * L + (size_t)(mirror ? L - y : y)) * L + (size_t)x];
+        s[line * f.LP + x] = v;
+    }
+    fft_general_lines<true>(s, tw, f, nl * L, tid);
+    const long long weight = (z == 0 || z == H) ? 1 : 2;
+    long long *T = reinterpret_cast<long long *>(a.z + (size_t)(H + 1) * L * L);
+    for (int t = tid; t < kFftBinY * (H + 1); t += kFftThreads) {
+        const int j = t / (H + 1), i = t - j * (H + 1), y = y0 + j;
+        if (y > H) continue;
+        long long sum = 0;
+        bool bad = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {  // bit 0: x -> L - x, bit 1: y -> L - y
+            if ((e & 1) && (i == 0 || i == H)) continue;
+            if ((e & 2) && (y == 0 || y == H)) continue;
+            const double v = s[(2 * j + (e >> 1)) * f.LP + ((e & 1) ? L - i : i)].x / inv_n;
+            const double r = rint(v);
+            bad |= !(fabs(v - r) <= 0.25);  // NaN included
+            sum += (long long)r;
+        }
+        if (bad) atomicOr(a.err, 1u);
+        T[((size_t)z * (H + 1) + (size_t)y) * (H + 1) + (size_t)i] = sum * weight;
+    }
 }
 
 }  // namespace ea

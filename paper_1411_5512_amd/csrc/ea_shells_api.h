@@ -5,9 +5,8 @@
 
 namespace {
 
-// Sum the shells from the dense rows (FFT route for L = 2^k or 3 2^k unless
-// ea_set_shell_route says otherwise, else the rows kernel), copy them to the
-// host and wait.
+// Sum the shells from the dense rows (FFT route if it has its work area, else
+// the rows kernel), copy them to the host and wait.
 ea_status shells_to_host(const unsigned long long *qd, int dw, unsigned long long *shells, void *fft_work, int L,
                          int n_shells, int64_t *out, hipStream_t stream)
 {
@@ -28,9 +27,15 @@ ea_status shell_scratch(ShellScratch &sc, int L, int n_shells, unsigned long lon
 {
     *dw = 2 * ((L + 63) / 64);
     const size_t q_words = (size_t)L * L * (size_t)*dw;
-    const size_t fft_bytes = shells_by_fft(L) ? fft_work_bytes(L) : 0;
+    size_t fft_bytes = shells_by_fft(L) ? fft_work_bytes(L) : 0;
     const size_t words = q_words + (size_t)n_shells, head = (8 * words + 255) / 256 * 256;
     ea_status st = sc.reserve(head + fft_bytes);
+    if (st != EA_OK && fft_bytes && ea::fft_general_side(L)) {
+        // sides that once had only the direct route keep it where memory is short
+        (void)hipGetLastError();
+        fft_bytes = 0;
+        st = sc.reserve(head);
+    }
     if (st != EA_OK) return st;
     unsigned long long *base = (unsigned long long *)sc.p;
     *qd = base;
