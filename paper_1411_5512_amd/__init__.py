@@ -224,20 +224,11 @@ class Sim:
 
     def measure(self, c4: bool = True, autocorr: bool = True) -> Obs:
         o = abi.Obs()
-        tw = np.zeros(max(self.n_slots, 1), dtype=np.uint64)
-        ac = np.zeros((2, max(self.n_slots, 1)), dtype=np.int64)
-        c4a = np.zeros((3, self.L // 2 + 1), dtype=np.int64)
-        if autocorr and self.n_slots > 0:
-            o.n_tw = self.n_slots
-            o.tw = abi.ptr(tw, ctypes.c_uint64)
-            o.autocorr = abi.ptr(ac, ctypes.c_int64)
-        if c4:
-            o.rmax = self.L // 2
-            o.c4 = abi.ptr(c4a, ctypes.c_int64)
+        tw, ac, c4a = _obs_buffers(self.L, self.n_slots if autocorr else 0, c4, o)
         abi.check(abi.lib().ea_measure(self._h, ctypes.byref(o)))
-        ns = self.n_slots
-        return Obs(int(o.t), np.array(o.unsat[:], dtype=np.int64), np.array(o.mag[:], dtype=np.int64),
-                   int(o.overlap), tw[:ns].copy(), ac[:, :ns].copy(), c4a if c4 else None)
+        if not autocorr:
+            tw, ac = np.zeros(self.n_slots, dtype=np.uint64), np.zeros((2, self.n_slots), dtype=np.int64)
+        return _obs_from(o, self.n_slots, tw, ac, c4a, c4)
 
     def c4_shells(self, n_shells: int | None = None) -> np.ndarray:
         """Full-vector C4 sums by minimum-image squared distance (see
@@ -354,10 +345,7 @@ class Msc:
         bufs = [_obs_buffers(self.L, self.n_slots if autocorr else 0, c4, objs[b]) for b in range(B)]
         abi.check(abi.lib().ea_msc_measure(self._h, objs))
         ns = self.n_slots if autocorr else 0
-        return [Obs(int(objs[b].t), np.array(objs[b].unsat[:], dtype=np.int64),
-                    np.array(objs[b].mag[:], dtype=np.int64), int(objs[b].overlap),
-                    bufs[b][0][:ns].copy(), bufs[b][1][:, :ns].copy(), bufs[b][2] if c4 else None)
-                for b in range(B)]
+        return [_obs_from(objs[b], ns, *bufs[b], c4) for b in range(B)]
 
     def c4_shells(self, sample: int, n_shells: int | None = None) -> np.ndarray:
         """Full-vector C4 sums by minimum-image squared distance of one
@@ -437,22 +425,22 @@ def _job_struct(job, keep):
 
 
 def _obs_buffers(L, n_tw, c4, o):
-    tw = np.zeros(max(n_tw, 1), dtype=np.uint64)
-    ac = np.zeros((2, max(n_tw, 1)), dtype=np.int64)
+    tw = np.zeros(n_tw, dtype=np.uint64)
+    ac = np.zeros((2, n_tw), dtype=np.int64)
     c4a = np.zeros((3, L // 2 + 1), dtype=np.int64)
     if n_tw:
         o.n_tw = n_tw
-        o.tw = abi.ptr(tw, ctypes.c_uint64)
-        o.autocorr = abi.ptr(ac, ctypes.c_int64)
+        o.tw = (ctypes.c_uint64 * n_tw).from_buffer(tw)
+        o.autocorr = (ctypes.c_int64 * (2 * n_tw)).from_buffer(ac)
     if c4:
         o.rmax = L // 2
-        o.c4 = abi.ptr(c4a, ctypes.c_int64)
+        o.c4 = (ctypes.c_int64 * c4a.size).from_buffer(c4a)
     return tw, ac, c4a
 
 
 def _obs_from(o, n_tw, tw, ac, c4a, c4):
-    return Obs(int(o.t), np.array(o.unsat[:], dtype=np.int64), np.array(o.mag[:], dtype=np.int64),
-               int(o.overlap), tw[:n_tw].copy(), ac[:, :n_tw].copy(), c4a if c4 else None)
+    return Obs(int(o.t), np.array(o.unsat, dtype=np.int64), np.array(o.mag, dtype=np.int64), int(o.overlap), tw, ac,
+               c4a if c4 else None)
 
 
 class Batch:

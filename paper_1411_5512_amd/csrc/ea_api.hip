@@ -12,6 +12,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
@@ -83,6 +84,52 @@ void debug_permute(T *v, size_t n)
 }
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
+
+// Pinned host memory in slots of one size, shared by the handles of the
+// process: a copy to pageable memory goes through the runtime's own staging
+// and waits twice as long.  A handle takes a slot at its first synchronising
+// call and gives it back when it is destroyed; at most 8 chunks of 56 slots
+// (2 MiB) are ever allocated, and they are kept for later handles.
+class PinnedSlots {
+public:
+    static constexpr size_t kBytes = 4608;
+    // nullptr when all are taken or no chunk can be allocated
+    char *take()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (free_.empty() && chunks_ < kChunks) {
+            void *p = nullptr;
+            if (hipHostMalloc(&p, kBytes * kPerChunk, hipHostMallocPortable) == hipSuccess) {
+                ++chunks_;
+                for (size_t i = 0; i < kPerChunk; ++i) free_.push_back((char *)p + i * kBytes);
+            } else {
+                (void)hipGetLastError();
+            }
+        }
+        if (free_.empty()) return nullptr;
+        char *p = free_.back();
+        free_.pop_back();
+        return p;
+    }
+    void give(char *p)
+    {
+        if (!p) return;
+        std::lock_guard<std::mutex> lk(mu_);
+        free_.push_back(p);
+    }
+
+private:
+    static constexpr size_t kPerChunk = 56, kChunks = 8;
+    std::mutex mu_;
+    std::vector<char *> free_;
+    size_t chunks_ = 0;
+};
+
+PinnedSlots &pinned_slots()
+{
+    static PinnedSlots *slots = new PinnedSlots();  // never destroyed: handles may outlive static storage
+    return *slots;
+}
 
 // Words per row: the fewest words of at most 32 bits such that every word
 // holds a whole number of 4-site random-word blocks.
@@ -284,6 +331,8 @@ struct ea_sim {
     unsigned long long *meas = nullptr;
     uint32_t *t_dev = nullptr;  // device copy of the sweep counter base
     std::vector<unsigned long long> host_meas, meas_before;  // the counters now and at the measurement before
+    char *slot = nullptr;     // pinned staging (pinned_slots), or null
+    bool slot_asked = false;
     // captured graph of kGraphSweeps sweeps (built on first use)
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
@@ -319,6 +368,17 @@ struct ea_sim {
 };
 
 namespace {
+
+// The handle's pinned slot, taken on the first call (null if there is none).
+char *pinned(ea_sim *s)
+{
+    if (!s->slot_asked) {
+        s->slot_asked = true;
+        s->slot = pinned_slots().take();
+    }
+    return s->slot;
+}
+constexpr size_t kSlotErr = PinnedSlots::kBytes - 64;  // the error word's place in a slot; data before it
 
 uint32_t key_lo(const ea_sim *s) { return (uint32_t)(s->seed & 0xffffffffu); }
 uint32_t key_hi(const ea_sim *s) { return (uint32_t)(s->seed >> 32); }
@@ -458,10 +518,11 @@ int slab_emax(int L, int n_runs, int B, int g)
 }
 
 
-
 std::mutex g_slab_mu;
 int g_slab_cus = 0, g_slab_lds_limit = 0;
 bool g_slab_attr[33] = {};
+constexpr size_t kSlabPlansKept = 1024;
+std::map<std::array<int, 5>, SlabPlan> g_slab_plans;  // (L, words per row, runs, requested slabs, ghosts) -> plan
 
 template <bool SPAN>
 const void *slab_kernel_fn(int W)
@@ -535,14 +596,26 @@ ea_status slab_choose(int L, int rw, int n_runs, int K_req, int g_req, SlabPlan 
     int n_cu = 0, lds_limit = 0;
     ea_status st = slab_device(L / 2 / rw, &n_cu, &lds_limit);
     if (st != EA_OK) return st;
+    // the choice depends on nothing else, and takes longer (250 us at L = 128)
+    // than the launch it is made for
+    const std::array<int, 5> key = {L, rw, n_runs, K_req, g_req};
+    {
+        std::lock_guard<std::mutex> lk(g_slab_mu);
+        auto it = g_slab_plans.find(key);
+        if (it != g_slab_plans.end()) {
+            *plan = it->second;
+            return EA_OK;
+        }
+    }
     const long P = 2L * n_runs * L;
     double best = 0.0;
     bool found = false;
     auto consider = [&](int B, int g) {
         SlabPlan p;
-        if (!slab_plan_fits(L, rw, n_runs, B, g, n_cu, lds_limit, &p)) return;
         const double c = slab_model_us(L, rw, (int)((P + B - 1) / B), g);
-        if (!found || c < best) {
+        if (found && c >= best) return;
+        if (!slab_plan_fits(L, rw, n_runs, B, g, n_cu, lds_limit, &p)) return;
+        {
             best = c;
             *plan = p;
             found = true;
@@ -563,6 +636,9 @@ ea_status slab_choose(int L, int rw, int n_runs, int K_req, int g_req, SlabPlan 
     if (!found)
         return fail(EA_ERR_ARG, "no slab plan (K=%d, g=%d) fits %d run(s) of L=%d on %d compute units", K_req,
                     g_req, n_runs, L, n_cu);
+    std::lock_guard<std::mutex> lk(g_slab_mu);
+    if (g_slab_plans.size() >= kSlabPlansKept) g_slab_plans.clear();
+    g_slab_plans[key] = *plan;
     return EA_OK;
 }
 
@@ -576,12 +652,80 @@ ea_status slab_plan_of(const ea_sim *s, int n_runs, SlabPlan *plan)
     return slab_choose(s->lay.L, s->lay.RW, n_runs, s->slab_K, s->slab_g, plan);
 }
 
+// Launches whose workgroups wait for each other must not share the device with
+// another such launch unless both fit at once: two that are each resident in
+// part would wait until they give up.  Streams that may have one in flight
+// are listed with the workgroups it needs; a launch that does not fit beside
+// the others waits, on its stream, for them.  The caller holds g_flight_mu
+// from here until its launch is enqueued.
+struct Flight {
+    hipStream_t stream;
+    int device, blocks;
+};
+std::mutex g_flight_mu;
+std::vector<Flight> g_flights;
+
+bool flight_over(const Flight &f)
+{
+    const bool over = hipStreamQuery(f.stream) != hipErrorNotReady;
+    (void)hipGetLastError();
+    return over;
+}
+
+// ev: an event of the caller's handle, created if it is needed.
+ea_status admit_flight(hipStream_t stream, int device, int blocks, int n_cu, hipEvent_t *ev)
+{
+    int others = 0;
+    Flight *own = nullptr;
+    for (Flight &f : g_flights) {
+        if (f.device != device) continue;
+        if (f.stream == stream) own = &f;
+        else others += f.blocks;
+    }
+    if (own) own->blocks = blocks >= own->blocks || flight_over(*own) ? blocks : own->blocks;
+    if (others + blocks > n_cu) {
+        for (size_t i = 0; i < g_flights.size();) {
+            const Flight f = g_flights[i];
+            if (f.device != device || f.stream == stream) {
+                ++i;
+            } else if (flight_over(f)) {
+                g_flights.erase(g_flights.begin() + (long)i);
+            } else {
+                if (!*ev) EA_HIP(hipEventCreateWithFlags(ev, hipEventDisableTiming));
+                EA_HIP(hipEventRecord(*ev, f.stream));
+                EA_HIP(hipStreamWaitEvent(stream, *ev, 0));
+                ++i;
+            }
+        }
+    }
+    if (!own) g_flights.push_back(Flight{stream, device, blocks});
+    return EA_OK;
+}
+
+// Before a stream is destroyed (and after it has been waited for).
+void forget_flights(hipStream_t stream)
+{
+    std::lock_guard<std::mutex> lk(g_flight_mu);
+    g_flights.erase(std::remove_if(g_flights.begin(), g_flights.end(),
+                                   [stream](const Flight &f) { return f.stream == stream; }),
+                    g_flights.end());
+}
+
+ea_status group_event(ea_sim *s)
+{
+    if (!s->group_event) EA_HIP(hipEventCreateWithFlags(&s->group_event, hipEventDisableTiming));
+    return EA_OK;
+}
+
 // Advance runs[0..n) (same L and packing, at most kGroupMax) by n sweeps with
 // slab launches on the first run's stream.
 ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPlan &plan)
 {
     ea_sim *lead = runs[0];
     const Layout &y = lead->lay;
+    std::lock_guard<std::mutex> flight(g_flight_mu);
+    ea_status st = admit_flight(lead->stream, lead->device, plan.B, g_slab_cus, &lead->group_event);
+    if (st != EA_OK) return st;
     for (int i = 0; i < n; ++i) {
         ea_sim *m = runs[i];
         if (!m->xbuf_clean) {  // entries of no earlier epoch
@@ -619,6 +763,7 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
         a.emax = plan.emax;
         a.tables = tables;
         a.n_half = 2 * chunk;
+        a.n_runs = n;
         a.err = lead->err_dev;
         a.order = debug_grid_order();
         a.poison = debug_poison_word();
@@ -635,6 +780,7 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
             d.spins = m->lat.spins;
             d.bonds = m->lat.bonds;
             d.xbuf = m->xbuf;
+            d.err = m->err_dev;
             d.k0 = key_lo(m);
             d.k1 = key_hi(m);
             d.sample = m->sample;
@@ -656,10 +802,6 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
         EA_HIP(hipGetLastError());
         done += chunk;
     }
-    // the launch-wide error word is the lead's; the others copy it
-    for (int i = 1; i < n; ++i)
-        hipLaunchKernelGGL(ea::or_word_kernel, dim3(1), dim3(64), 0, lead->stream, runs[i]->err_dev, lead->err_dev);
-    EA_HIP(hipGetLastError());
     return EA_OK;
 }
 
@@ -669,15 +811,19 @@ ea_status slab_gave_up()
                                "resident within seconds); the run's state is undefined until ea_reset");
 }
 
-// After a synchronisation: EA_ERR_DEVICE if a slab launch of the run gave up
+// Wait for the run's stream; EA_ERR_DEVICE if a slab launch of the run gave up
 // waiting for a neighbouring slab (the run's state is then undefined until
 // ea_reset).
-ea_status slab_check(ea_sim *s)
+ea_status sync_and_check(ea_sim *s)
 {
-    if (!s->slab_used) return EA_OK;
     uint32_t e = 0;
-    EA_HIP(hipMemcpy(&e, s->err_dev, 4, hipMemcpyDeviceToHost));
-    return e ? slab_gave_up() : EA_OK;
+    uint32_t *to = &e;
+    if (s->slab_used) {
+        if (char *slot = pinned(s)) to = (uint32_t *)(slot + kSlotErr);
+        EA_HIP(hipMemcpyAsync(to, s->err_dev, 4, hipMemcpyDeviceToHost, s->stream));
+    }
+    EA_HIP(hipStreamSynchronize(s->stream));
+    return s->slab_used && *to ? slab_gave_up() : EA_OK;
 }
 
 // Shell sums of dense overlap rows (ea_shells.h) for any L up to 256.
@@ -1012,12 +1158,16 @@ ea_status ea_create_ex(const ea_config *cfg, ea_sim **out)
 void ea_destroy(ea_sim *s)
 {
     if (!s) return;
-    if (s->stream) (void)hipStreamSynchronize(s->stream);
+    if (s->stream) {
+        (void)hipStreamSynchronize(s->stream);
+        if (s->slab_used) forget_flights(s->stream);
+    }
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     if (s->graph) (void)hipGraphDestroy(s->graph);
     if (s->c4_scratch) (void)hipFree(s->c4_scratch);
     if (s->fft_work) (void)hipFree(s->fft_work);
     if (s->io) (void)hipFree(s->io);
+    pinned_slots().give(s->slot);
     if (s->group_event) (void)hipEventDestroy(s->group_event);
     if (s->own_buf && s->buf) (void)hipFree(s->buf);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -1079,16 +1229,6 @@ ea_status ea_sweep(ea_sim *s, uint64_t n)
     s->t += n;
     return EA_OK;
 }
-
-namespace {
-
-ea_status group_event(ea_sim *s)
-{
-    if (!s->group_event) EA_HIP(hipEventCreateWithFlags(&s->group_event, hipEventDisableTiming));
-    return EA_OK;
-}
-
-}  // namespace
 
 ea_status ea_sweep_group(ea_sim *const *sims, int32_t n_sims, uint64_t n)
 {
@@ -1206,14 +1346,16 @@ ea_status ea_measure(ea_sim *s, ea_obs *out)
     EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::measure_kernel<WW>), grid, dim3(ea::kMeasThreads), 0, s->stream,
                                            s->lat, g, s->snaps, nb, slots, s->meas, (int)c4_base, s->err_dev));
     EA_HIP(hipGetLastError());
-    EA_HIP(hipMemcpyAsync(s->host_meas.data(), s->meas, n_count * sizeof(unsigned long long),
-                          hipMemcpyDeviceToHost, s->stream));
+    const size_t n_bytes = n_count * sizeof(unsigned long long);
+    unsigned long long *got = s->host_meas.data();
+    if (char *slot = n_bytes <= kSlotErr ? pinned(s) : nullptr) got = (unsigned long long *)slot;
+    EA_HIP(hipMemcpyAsync(got, s->meas, n_bytes, hipMemcpyDeviceToHost, s->stream));
     EA_HIP(hipStreamSynchronize(s->stream));
-    const bool gave_up = s->host_meas[c4_base] != 0;
-    s->host_meas[c4_base] = 0;
+    const bool gave_up = got[c4_base] != 0;
+    got[c4_base] = 0;
     for (size_t i = 0; i < n_count; ++i) {  // this measurement's counts
-        const unsigned long long now = s->host_meas[i];
-        s->host_meas[i] -= s->meas_before[i];
+        const unsigned long long now = got[i];
+        s->host_meas[i] = now - s->meas_before[i];
         s->meas_before[i] = now;
     }
     if (gave_up) return slab_gave_up();
@@ -1421,8 +1563,7 @@ ea_status ea_set_time(ea_sim *s, uint64_t t)
 ea_status ea_sync(ea_sim *s)
 {
     if (!s) return fail(EA_ERR_ARG, "sim is NULL");
-    EA_HIP(hipStreamSynchronize(s->stream));
-    return slab_check(s);
+    return sync_and_check(s);
 }
 
 ea_status ea_set_slab_plan(ea_sim *s, int32_t slabs, int32_t ghost)
@@ -1571,13 +1712,22 @@ ea_status io_buffer(ea_sim *s, char **buf, size_t *bytes)
 template <int ND>
 ea_status copy_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
 {
-    char *buf = nullptr;
+    const Layout &y = s->lay;
+    const ea::Geom g = s->geom();
+    const size_t row_bytes = (size_t)ND * (size_t)y.L, n_bytes = row_bytes * (size_t)y.rows;
+    char *buf = n_bytes <= kSlotErr ? pinned(s) : nullptr;
+    if (buf) {
+        // small arrays are written to pinned host memory by the kernel itself
+        EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::to_pm1_kernel<WW, ND>), dim3(blocks_for((size_t)y.rows * (y.L / 8))),
+                                              dim3(256), 0, s->stream, planes, g, 0, y.rows, (uint2 *)buf));
+        EA_HIP(hipGetLastError());
+        ea_status st = sync_and_check(s);
+        std::memcpy(pm1, buf, n_bytes);
+        return st;
+    }
     size_t cap = 0;
     ea_status st = io_buffer(s, &buf, &cap);
     if (st != EA_OK) return st;
-    const Layout &y = s->lay;
-    const ea::Geom g = s->geom();
-    const size_t row_bytes = (size_t)ND * (size_t)y.L;
     const int step = (int)std::min<size_t>((size_t)y.rows, cap / row_bytes);
     for (int row = 0; row < y.rows; row += step) {
         const int n = std::min(step, y.rows - row);
@@ -1587,8 +1737,7 @@ ea_status copy_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
         EA_HIP(hipMemcpyAsync(pm1 + (size_t)row * row_bytes, buf, (size_t)n * row_bytes, hipMemcpyDeviceToHost,
                               s->stream));
     }
-    EA_HIP(hipStreamSynchronize(s->stream));
-    return EA_OK;
+    return sync_and_check(s);
 }
 
 template <int ND>
@@ -1637,8 +1786,7 @@ ea_status ea_get_spins(ea_sim *s, int32_t r, int8_t *pm1)
 {
     if (!s || !pm1) return fail(EA_ERR_ARG, "NULL argument");
     if (r < 0 || r > 1) return fail(EA_ERR_ARG, "replica %d not 0 or 1", r);
-    ea_status st = copy_pm1_out<1>(s, s->lat.spins + (size_t)r * 2 * s->lay.plane, pm1);
-    return st != EA_OK ? st : slab_check(s);
+    return copy_pm1_out<1>(s, s->lat.spins + (size_t)r * 2 * s->lay.plane, pm1);
 }
 
 ea_status ea_set_spins(ea_sim *s, int32_t r, const int8_t *pm1)

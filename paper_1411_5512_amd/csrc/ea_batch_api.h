@@ -53,8 +53,12 @@ struct BatchJobHost {
     uint32_t *err = nullptr;  // device word a split pair sets when it gives up waiting
     char *base = nullptr;     // device region of this job
     uint64_t t_host = 0;      // sweeps done (host mirror)
+    std::vector<unsigned long long> obs_host;  // the counters of every measurement, once fetched
+    bool obs_fetched = false; // since the last launch or reset
     bool started = false;     // a span has run (events at t = 0 are taken)
 };
+
+constexpr size_t kObsFetchBytes = 1 << 20;  // results of one job fetched in one copy, at most
 
 bool batch_L_ok(int L) { return L >= 8 && L <= ea::kBatchMaxL && L % 8 == 0; }
 
@@ -238,6 +242,7 @@ ea_status init_job_device(BatchJobHost &h, hipStream_t stream)
     EA_HIP(hipGetLastError());
     h.t_host = 0;
     h.started = false;
+    h.obs_fetched = false;
     return EA_OK;
 }
 
@@ -474,8 +479,10 @@ struct ea_batch {
     ea::BatchUnit *d_units_graph = nullptr;  // whole-run units read by the captured graph
     uint32_t *d_err = nullptr;                // set by a split pair that gave up waiting
     std::vector<ea::BatchUnit> units;
+    int device = 0;                       // the device current at ea_batch_create
+    int split_units = 0;                  // units of split replicas, which wait for each other (admit_flight)
+    hipEvent_t flight_event = nullptr;
     size_t lds_bytes = 0;
-    std::vector<unsigned long long> h_obs;  // staging for ea_batch_result
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
 };
@@ -774,6 +781,8 @@ ea_status batch_create_cfg(const ea_job *jobs, int32_t n_jobs, void *stream, con
         return fail(EA_ERR_DEVICE, "job table upload: %s", hipGetErrorString(e));
     }
     order_units(ptrs, span, b->units);
+    (void)hipGetDevice(&b->device);
+    for (const ea::BatchUnit &u : b->units) b->split_units += b->jobs[(size_t)u.job].parts == 2 ? 1 : 0;
     st = ea_batch_reset(b);
     if (st != EA_OK) {
         ea_batch_destroy(b);
@@ -795,6 +804,23 @@ ea_status reset_batch_device(ea_batch *b)
     }
     return EA_OK;
 }
+
+// Held while a launch with split replicas is enqueued (admit_flight).
+struct BatchFlight {
+    std::unique_lock<std::mutex> lk;
+    ea_status st = EA_OK;
+    explicit BatchFlight(ea_batch *b)
+    {
+        if (!b->split_units) return;
+        int n_cu = 0;
+        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess) {
+            st = fail(EA_ERR_DEVICE, "hipDeviceGetAttribute failed");
+            return;
+        }
+        lk = std::unique_lock<std::mutex>(g_flight_mu);
+        st = admit_flight(b->stream, b->device, b->split_units, n_cu, &b->flight_event);
+    }
+};
 
 // After a synchronised run: did a split pair give up waiting?
 ea_status check_batch_err(ea_batch *b)
@@ -875,6 +901,8 @@ void ea_batch_destroy(ea_batch *b)
 {
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
+    if (b->split_units) forget_flights(b->stream);
+    if (b->flight_event) (void)hipEventDestroy(b->flight_event);
     if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->buf) (void)hipFree(b->buf);
@@ -904,12 +932,17 @@ ea_status ea_batch_run(ea_batch *b, uint64_t t_stop)
     debug_order_units(b->jobs.data(), launch);
     EA_HIP(hipMemcpyAsync(b->d_units, launch.data(), sizeof(ea::BatchUnit) * launch.size(),
                           hipMemcpyHostToDevice, b->stream));
-    hipLaunchKernelGGL(ea::batch_kernel, dim3((unsigned)launch.size()), dim3(ea::kBatchThreads), b->lds_bytes,
-                       b->stream, b->d_jobs, b->d_units, debug_poison_word(), (int)(b->lds_bytes / 4));
-    EA_HIP(hipGetLastError());
+    {
+        BatchFlight flight(b);
+        if (flight.st != EA_OK) return flight.st;
+        hipLaunchKernelGGL(ea::batch_kernel, dim3((unsigned)launch.size()), dim3(ea::kBatchThreads), b->lds_bytes,
+                           b->stream, b->d_jobs, b->d_units, debug_poison_word(), (int)(b->lds_bytes / 4));
+        EA_HIP(hipGetLastError());
+    }
     for (auto &h : b->jobs) {
         h.t_host = std::max<uint64_t>(h.t_host, std::min<uint64_t>(t_stop, h.job.n_sweeps));
         h.started = true;
+        h.obs_fetched = false;
     }
     // the unit table is read by the kernel: keep the host copy stable until it ran
     EA_HIP(hipStreamSynchronize(b->stream));
@@ -955,11 +988,16 @@ ea_status ea_batch_replay(ea_batch *b)
 {
     if (!b) return fail(EA_ERR_ARG, "batch is NULL");
     if (!b->graph_exec) return fail(EA_ERR_STATE, "ea_batch_capture first");
-    EA_HIP(hipGraphLaunch(b->graph_exec, b->stream));
+    {
+        BatchFlight flight(b);
+        if (flight.st != EA_OK) return flight.st;
+        EA_HIP(hipGraphLaunch(b->graph_exec, b->stream));
+    }
     EA_HIP(hipStreamSynchronize(b->stream));
     for (auto &h : b->jobs) {
         h.t_host = h.job.n_sweeps;
         h.started = true;
+        h.obs_fetched = false;
     }
     return check_batch_err(b);
 }
@@ -976,15 +1014,22 @@ ea_status ea_batch_result(ea_batch *b, int32_t job, int32_t k, ea_obs *out)
 {
     if (!b || !out) return fail(EA_ERR_ARG, "NULL argument");
     if (job < 0 || job >= (int32_t)b->jobs.size()) return fail(EA_ERR_ARG, "job %d out of range", job);
-    const BatchJobHost &h = b->jobs[(size_t)job];
+    BatchJobHost &h = b->jobs[(size_t)job];
     if (k < 0 || k >= h.job.n_meas) return fail(EA_ERR_ARG, "measurement %d out of range", k);
     if (h.meas_t[(size_t)k] > h.t_host || !h.started)
         return fail(EA_ERR_STATE, "measurement %d (t=%u) not reached", k, h.meas_t[(size_t)k]);
-    b->h_obs.resize((size_t)h.obs_stride);
-    EA_HIP(hipMemcpyAsync(b->h_obs.data(), h.base + h.off_obs + 8 * (size_t)k * (size_t)h.obs_stride,
-                          8 * (size_t)h.obs_stride, hipMemcpyDeviceToHost, b->stream));
-    EA_HIP(hipStreamSynchronize(b->stream));
-    return fill_obs(h, b->h_obs.data(), k, out);
+    // a caller reads a job's measurements one after the other: one copy brings
+    // them all (15 us a copy, whatever its size here), unless they are many
+    const size_t stride = (size_t)h.obs_stride, all = (size_t)h.job.n_meas * stride;
+    const bool whole = 8 * all <= kObsFetchBytes;
+    if (!whole || !h.obs_fetched) {
+        h.obs_host.resize(whole ? all : stride);
+        EA_HIP(hipMemcpyAsync(h.obs_host.data(), h.base + h.off_obs + (whole ? 0 : 8 * (size_t)k * stride),
+                              8 * h.obs_host.size(), hipMemcpyDeviceToHost, b->stream));
+        EA_HIP(hipStreamSynchronize(b->stream));
+        h.obs_fetched = whole;
+    }
+    return fill_obs(h, h.obs_host.data() + (whole ? (size_t)k * stride : 0), k, out);
 }
 
 ea_status ea_batch_parts(ea_batch *b, int32_t job, int32_t *parts)

@@ -47,6 +47,7 @@ struct SlabRunDev {
     uint32_t *spins;          // [replica][colour][plane]: state before and after the launch
     const uint32_t *bonds;    // [direction][colour][plane]
     unsigned long long *xbuf; // [replica][slot][colour][L planes][PL] exchange entries
+    uint32_t *err;            // the run's error word
     uint32_t k0, k1, sample, thr1, thr2, thr3;
     uint32_t t0;              // sweep index of the launch's first half-step
     uint32_t serial;          // epoch of cycle m is serial + m + 1
@@ -65,7 +66,8 @@ struct SlabLaunch {
     int32_t emax;        // LDS planes per array: the extended regions of a workgroup's pieces
     int32_t tables;      // 2: a workgroup's second piece (another run) has its own select table
     uint32_t n_half;     // half-steps in this launch (the first is half 0 of sweep t0)
-    uint32_t *err;       // set when a wait timed out; every workgroup then ends
+    int32_t n_runs;
+    uint32_t *err;       // the first run's error word: set when a wait timed out; every workgroup then ends
     uint32_t order;      // debug order of the shares (debug_block); 0 = workgroup b takes share b
     uint32_t poison;     // debug LDS fill before the loads (debug_poison); 0 = off
 };
@@ -98,6 +100,13 @@ __device__ __forceinline__ int slab_pieces(const SlabLaunch &a, int b, SlabPiece
 }
 
 extern __shared__ uint32_t slab_lds[];
+
+// A wait timed out: every run of the launch is told.
+__device__ __forceinline__ void slab_fail(const SlabLaunch &a)
+{
+    for (int i = 0; i < a.n_runs; ++i)
+        __hip_atomic_store(a.runs[i].err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __device__ __forceinline__ uint32_t slab_err_seen(uint32_t *err)
 {
@@ -244,9 +253,12 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
         flag[1] = 0;
     }
     __syncthreads();
-    if (flag[0]) return;
+    if (flag[0]) {  // an earlier launch of the first run gave up: its companions' states do not advance either
+        if (tid == 0) slab_fail(a);
+        return;
+    }
     if (np > 1 && (g > 1 || !SPAN)) {  // the host plans two-piece shares for SPAN launches at depth 1 only
-        if (tid == 0) __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) slab_fail(a);
         return;
     }
 
@@ -333,7 +345,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                         if (need_lo && (uint32_t)(vl >> 32) != ep_prev) ok &= slab_poll(gl, ep_prev, a.err, vl);
                         if (need_hi && (uint32_t)(vu >> 32) != ep_prev) ok &= slab_poll(gu, ep_prev, a.err, vu);
                         if (!ok) {
-                            __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            slab_fail(a);
                             __hip_atomic_store(flag + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         }
                         if (need_lo) sw.Zm = (uint32_t)vl;
@@ -441,7 +453,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 }
             }
             if (!ok) {
-                __hip_atomic_store(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                slab_fail(a);
                 flag[1] = 1;
             }
             __syncthreads();
@@ -461,13 +473,6 @@ __global__ __launch_bounds__(kSlabThreads) void slab_sweep_kernel(SlabLaunch a)
                 run.spins[((size_t)pc.r * 2 + c) * plane + dst] = lspin[(c * EM + e) * PL + c0];
         }
     }
-}
-
-// dst |= src (one word): hands the launch-wide error word to the other runs
-// of a group launch without clearing an error they already had.
-__global__ void or_word_kernel(uint32_t *dst, const uint32_t *src)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst |= *src;
 }
 
 }  // namespace ea
