@@ -589,7 +589,10 @@ ea_status tune_probe(int L, const TuneCfg &cfg, std::vector<long long> &results,
 {
     const int n = 64;
     const uint64_t N = (uint64_t)L * L * L;
-    const uint64_t sweeps = std::max<uint64_t>(8, (1ull << 22) / N);
+    // Long enough that the half-steps decide: with 16 sweeps at L = 64 (0.3 of
+    // a probe's 0.6 ms) the start and the events chose half the threads, which
+    // ran a mixed batch of 256 samples in 392 ms instead of 373.
+    const uint64_t sweeps = std::max<uint64_t>(64, (1ull << 22) / N);
     std::vector<uint64_t> meas = {sweeps / 2, sweeps}, tw = {sweeps / 4};
     std::vector<ea_job> jobs((size_t)n);
     for (int i = 0; i < n; ++i) {

@@ -263,31 +263,128 @@ __device__ __forceinline__ void batch_done(uint32_t done)
         __hip_atomic_store(batch_progress + (threadIdx.x >> 6), done, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// The thread's index, opaque, so that what is computed from it stays where it
+// is used instead of being kept (and spilled) across the sweep loop.
+__device__ __forceinline__ int local_tid()
+{
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 // Copy this replica's two colour planes between LDS and a global array.
 template <class S>
 __device__ __forceinline__ void batch_store_spins(uint32_t *dst, int nt)
 {
-    for (int i = (int)threadIdx.x; i < 2 * S::POS; i += nt) dst[i] = batch_lds[i];
+    for (int i = local_tid(); i < 2 * S::POS; i += nt) dst[i] = batch_lds[i];
+}
+
+// Load a replica's spins (two colour planes) and the couplings into LDS.
+template <class S>
+__device__ __forceinline__ void batch_load(const BatchJobDev &J, const uint32_t *spins)
+{
+    const int nt = J.nt, tid = local_tid();
+    for (int i = tid; i < 2 * S::POS; i += nt) batch_lds[i] = spins[i];
+    for (int i = tid; i < 6 * S::POS; i += nt) batch_lds[2 * S::POS + i] = J.bonds[i];
+}
+
+// The overlap and C4 (eqs. 2, 3) of measurement m from both published
+// configurations, by one workgroup: the overlap words of every row (R <= 32
+// sites of a colour: one word) go to LDS, lines along y and then along z laid
+// out twice end to end, and each thread keeps one displacement rho = 1 .. R
+// and a part of the lines.  Overwrites the workgroup's lattice in LDS.
+// Bound by LDS reads and population counts, 6 L^2 R of each; a measurement
+// of L = 64 (1024 threads) takes 150 us with all its parts.  Reading both
+// words of every pair from memory, with one wave sum per displacement, it
+// took 400, forty half-steps.
+template <int L, int RW>
+__device__ void batch_pair(const BatchJobDev &J, int m)
+{
+    using S = Shape<L, RW>;
+    constexpr int W = S::W, POS = S::POS, R = S::R, ROWS = L * L;
+    constexpr uint32_t MASK = word_mask<R>();
+    // a slab (L >= kSplitMinL) holds four words per row, then two planes' halo
+    static_assert(R <= 32 && 4 * ROWS + 3 * R <= (L >= kSplitMinL ? 4 * ROWS + 2 * L : 8 * ROWS),
+                  "lines and counts fit the lattice part of LDS");
+    const int nt = J.nt, tid = local_tid();
+    const uint32_t *q0 = J.mspins + (size_t)m * 4 * POS;
+    const uint32_t *q1 = q0 + 2 * POS;
+    uint32_t *lines = batch_lds, *counts = batch_lds + 4 * ROWS;
+    for (int i = tid; i < 3 * R; i += nt) counts[i] = 0u;
+    const int parts = nt / R, part = tid / R, rho = 1 + tid - part * R, odd = rho & 1;
+    uint32_t qdiff = 0, diff[3] = {0u, 0u, 0u};
+#pragma unroll 1
+    for (int d = 1; d <= 2; ++d) {  // lines along y, then along z
+#pragma unroll 1
+        for (int i = tid; i < 2 * ROWS; i += nt) {
+            const int c = i >= ROWS ? 1 : 0, row = i - c * ROWS, z = row / L, y = row - z * L;
+            uint32_t v = 0;
+#pragma unroll
+            for (int w = 0; w < RW; ++w)
+                v |= (q0[c * POS + row * RW + w] ^ q1[c * POS + row * RW + w]) << (w * W);
+            if (d == 1) qdiff += __popc(v);
+            uint32_t *dst = lines + (d == 1 ? (c * L + z) * 2 * L + y : (c * L + y) * 2 * L + z);
+            dst[0] = v;
+            dst[L] = v;
+        }
+        __syncthreads();
+        if (part < parts) {
+#pragma unroll 1
+            for (int k = part; k < 2 * L; k += parts) {
+                const int c = k >= L ? 1 : 0, o = k - c * L;
+                const uint32_t *own = lines + k * 2 * L;
+                const uint32_t *other = lines + ((c ^ odd) * L + o) * 2 * L;
+                uint32_t n = 0;
+#pragma unroll 4
+                for (int i = 0; i < L; ++i) n += __popc(own[i] ^ other[rho + i]);
+                diff[d == 1 ? 1 : 2] += n;
+                if (d == 1) {
+                    // along x: the row's own word or the other colour's, rotated
+                    n = 0;
+#pragma unroll 4
+                    for (int y = 0; y < L; ++y) {
+                        const int sh = (rho >> 1) + (odd & (y + o + c));
+                        const uint64_t p = (uint64_t)other[y] | (uint64_t)other[y] << R;
+                        n += __popc((own[y] ^ (uint32_t)(p >> sh)) & MASK);
+                    }
+                    diff[0] += n;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (part < parts)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) atomicAdd(counts + d * R + rho - 1, diff[d]);
+    unsigned long long *o = J.obs + (size_t)m * (size_t)J.obs_stride;
+    wave_add(o + M_QDIFF, qdiff);
+    __syncthreads();
+    unsigned long long *c4 = o + batch_c4_base(J.n_tw);
+    for (int i = tid; i < 3 * R; i += nt) {
+        const int d = i / R, k = i - d * R;
+        if (counts[i]) atomicAdd(c4 + d * (R + 1) + 1 + k, (unsigned long long)counts[i]);
+    }
+    __syncthreads();
 }
 
 // Publish this workgroup's part of replica r's configuration at measurement
 // m (rows [row0, row0 + rows) of both colours, taken from LDS spin words
 // batch_lds[c * src_stride + i]); the last workgroup of the job to arrive
-// computes the replica-pair observables, the overlap and C4 (eqs. 2, 3), from
-// the published copies.  flag_word is a free LDS word for a broadcast.
+// computes the replica-pair observables from the published copies.  True if
+// this was the one: its LDS lattice is gone and has to be loaded again.
+// flag_word is a free LDS word for a broadcast.
 template <int L, int RW>
-__device__ void batch_publish_and_pair(const BatchJobDev &J, int r, int m, int row0, int rows, int src_stride,
+__device__ bool batch_publish_and_pair(const BatchJobDev &J, int r, int m, int row0, int rows, int src_stride,
                                        int flag_word)
 {
     using S = Shape<L, RW>;
-    constexpr int W = S::W, POS = S::POS;
+    constexpr int POS = S::POS;
     const int nt = J.nt;
-    unsigned long long *o = J.obs + (size_t)m * (size_t)J.obs_stride;
     uint32_t *dst = J.mspins + ((size_t)m * 2 + (size_t)r) * 2 * POS;
-    const int n = rows * RW;
+    const int n = rows * RW, tid = local_tid();
 #pragma unroll 1
     for (int c = 0; c < 2; ++c)
-        for (int i = (int)threadIdx.x; i < n; i += nt) dst[c * POS + row0 * RW + i] = batch_lds[c * src_stride + i];
+        for (int i = tid; i < n; i += nt) dst[c * POS + row0 * RW + i] = batch_lds[c * src_stride + i];
     __threadfence();
     __syncthreads();
     uint32_t *flag = batch_lds + flag_word;
@@ -295,52 +392,10 @@ __device__ void batch_publish_and_pair(const BatchJobDev &J, int r, int m, int r
     __syncthreads();
     const bool last = *flag == (uint32_t)(2 * J.parts - 1);
     __syncthreads();
-    if (!last) return;
+    if (!last) return false;
     __threadfence();
-
-    const uint32_t *q0 = J.mspins + (size_t)m * 4 * POS;
-    const uint32_t *q1 = q0 + 2 * POS;
-    uint32_t qdiff = 0;
-    for (int i = (int)threadIdx.x; i < 2 * POS; i += nt) qdiff += __popc(q0[i] ^ q1[i]);
-    wave_add(o + M_QDIFF, qdiff);
-
-    unsigned long long *c4 = o + batch_c4_base(J.n_tw);
-#pragma unroll 1
-    for (int d = 0; d < 3; ++d) {
-#pragma unroll 1
-        for (int rho = 0; rho <= S::R; ++rho) {
-            uint32_t diff = 0;
-#pragma unroll 1
-            for (int c = 0; c < 2; ++c) {
-                const int cp = c ^ (rho & 1);
-#pragma unroll 1
-                for (int p = (int)threadIdx.x; p < POS; p += nt) {
-                    const int row = p / RW;
-                    const int w = p - row * RW;
-                    const int y = row % L;
-                    const int z = row / L;
-                    const uint32_t q = q0[c * POS + p] ^ q1[c * POS + p];
-                    uint32_t qp;
-                    if (d == 0) {
-                        const int par = (y + z + c) & 1;
-                        const int kx = (rho & 1) ? (rho - 1) / 2 + par : rho / 2;
-                        const int start = (w * W + kx) % S::R;
-                        const int wi = start / W;
-                        const int off = start - wi * W;
-                        const int wj = wi + 1 == RW ? 0 : wi + 1;
-                        const uint32_t lo = q0[cp * POS + row * RW + wi] ^ q1[cp * POS + row * RW + wi];
-                        const uint32_t hi = q0[cp * POS + row * RW + wj] ^ q1[cp * POS + row * RW + wj];
-                        qp = off == 0 ? lo : (((lo >> off) | (hi << (W - off))) & word_mask<W>());
-                    } else {
-                        const int prow = d == 1 ? (y + rho) % L + L * z : y + L * ((z + rho) % L);
-                        qp = q0[cp * POS + prow * RW + w] ^ q1[cp * POS + prow * RW + w];
-                    }
-                    diff += __popc(q ^ qp);
-                }
-            }
-            wave_add(c4 + d * (S::R + 1) + rho, diff);
-        }
-    }
+    batch_pair<L, RW>(J, m);
+    return true;
 }
 
 // Measurement at time t (index m) of replica r (whole replica in LDS).
@@ -356,7 +411,7 @@ __device__ void batch_measure(const BatchJobDev &J, int r, int m, int n_taken)
     for (int c = 0; c < 2; ++c) {
         const uint32_t *own = lds_spin<S>(c);
         const uint32_t *oth = lds_spin<S>(c ^ 1);
-        for (int p = (int)threadIdx.x; p < POS; p += nt) {
+        for (int p = local_tid(); p < POS; p += nt) {
             const int row = p / RW;
             const int w = p - row * RW;
             const int y = row % L;
@@ -380,10 +435,11 @@ __device__ void batch_measure(const BatchJobDev &J, int r, int m, int n_taken)
     for (int k = 0; k < n_taken; ++k) {
         const uint32_t *ref = J.snaps + ((size_t)k * 2 + (size_t)r) * 2 * POS;
         uint32_t diff = 0;
-        for (int i = (int)threadIdx.x; i < 2 * POS; i += nt) diff += __popc(batch_lds[i] ^ ref[i]);
+        for (int i = local_tid(); i < 2 * POS; i += nt) diff += __popc(batch_lds[i] ^ ref[i]);
         wave_add(o + M_AUTO + 2 * k + r, diff);
     }
-    batch_publish_and_pair<L, RW>(J, r, m, 0, L * L, POS, S::LATTICE_WORDS);
+    if (batch_publish_and_pair<L, RW>(J, r, m, 0, L * L, POS, S::LATTICE_WORDS))
+        batch_load<S>(J, J.mspins + ((size_t)m * 2 + (size_t)r) * 2 * POS);
 }
 
 // Sweeps t .. t_end - 1; done counts the half-steps of the unit so far.
@@ -415,9 +471,7 @@ __device__ void batch_run_unit(const BatchJobDev &J, int r, uint32_t t_stop, boo
     if ((int)threadIdx.x >= nt) return;  // whole surplus waves leave the barrier set
     const uint32_t t0 = J.t_now[r];
     if (!first && t0 >= t_stop) return;
-    const uint32_t *src = J.spins + (size_t)r * 2 * S::POS;
-    for (int i = (int)threadIdx.x; i < 2 * S::POS; i += nt) batch_lds[i] = src[i];
-    for (int i = (int)threadIdx.x; i < 6 * S::POS; i += nt) batch_lds[2 * S::POS + i] = J.bonds[i];
+    batch_load<S>(J, J.spins + (size_t)r * 2 * S::POS);
     if constexpr (SEL == SEL_LDS) fill_select_tables(batch_tables(), J.thr1, J.thr2, J.thr3, (int)threadIdx.x, nt);
     if (threadIdx.x < kBatchWaves) batch_progress[threadIdx.x] = 0;
     __syncthreads();
@@ -665,6 +719,25 @@ __device__ __forceinline__ bool slab_half_step(const BatchJobDev &J, int r, int 
     return true;
 }
 
+// Load one slab's part of a replica's spins ([colour][POS]) and of the
+// couplings into LDS.
+template <int L, int RW>
+__device__ __forceinline__ void slab_load(const BatchJobDev &J, int slab, const uint32_t *spins)
+{
+    using S = Slab<L, RW>;
+    const int nt = J.nt, z0 = slab * S::NZ, tid = local_tid();
+    const int zb = (z0 + L - 1) % L;  // the plane below the slab
+    for (int c = 0; c < 2; ++c)
+        for (int i = tid; i < S::SPOS; i += nt)
+            batch_lds[c * S::SPOS + i] = spins[(size_t)c * S::POS + (size_t)z0 * S::PL + i];
+    for (int dc = 0; dc < 6; ++dc)
+        for (int i = tid; i < S::SPOS; i += nt)
+            batch_lds[(2 + dc) * S::SPOS + i] = J.bonds[(size_t)dc * S::POS + (size_t)z0 * S::PL + i];
+    for (int c = 0; c < 2; ++c)
+        for (int i = tid; i < S::PL; i += nt)
+            batch_lds[S::HALO + c * S::PL + i] = J.bonds[(size_t)(4 + c) * S::POS + (size_t)zb * S::PL + i];
+}
+
 // Measurement m at time t of one slab: its partial sums, then its part of
 // the published configuration.  The partner's first plane (the +z neighbour
 // of this slab's last plane) comes from the exchange area; wave 0 has waited
@@ -683,7 +756,7 @@ __device__ void slab_measure(const BatchJobDev &J, int r, int slab, int m, int n
         const uint32_t *own = slab_spin<S>(c);
         const uint32_t *oth = slab_spin<S>(c ^ 1);
         const uint32_t *part_first = slab_xbuf<S>(J, r, slab ^ 1, (int)((t + 1) & 1u), c ^ 1, 0);
-        for (int p = (int)threadIdx.x; p < S::SPOS; p += nt) {
+        for (int p = local_tid(); p < S::SPOS; p += nt) {
             const int row = p / RW;
             const int w = p - row * RW;
             const int y = row % L;
@@ -709,10 +782,11 @@ __device__ void slab_measure(const BatchJobDev &J, int r, int slab, int m, int n
         uint32_t diff = 0;
 #pragma unroll 1
         for (int c = 0; c < 2; ++c)
-            for (int i = (int)threadIdx.x; i < S::SPOS; i += nt) diff += __popc(batch_lds[c * S::SPOS + i] ^ ref[c * S::POS + i]);
+            for (int i = local_tid(); i < S::SPOS; i += nt) diff += __popc(batch_lds[c * S::SPOS + i] ^ ref[c * S::POS + i]);
         wave_add(o + M_AUTO + 2 * k + r, diff);
     }
-    batch_publish_and_pair<L, RW>(J, r, m, z0 * L, S::NZ * L, S::SPOS, S::FLAG);
+    if (batch_publish_and_pair<L, RW>(J, r, m, z0 * L, S::NZ * L, S::SPOS, S::FLAG))
+        slab_load<L, RW>(J, slab, J.mspins + ((size_t)m * 2 + (size_t)r) * 2 * S::POS);
 }
 
 // Copy this slab's two colour parts between LDS and a [colour][POS] array.
@@ -721,7 +795,7 @@ __device__ __forceinline__ void slab_store(uint32_t *dst, int z0, int nt)
 {
 #pragma unroll 1
     for (int c = 0; c < 2; ++c)
-        for (int i = (int)threadIdx.x; i < S::SPOS; i += nt)
+        for (int i = local_tid(); i < S::SPOS; i += nt)
             dst[(size_t)c * S::POS + (size_t)z0 * S::PL + i] = batch_lds[c * S::SPOS + i];
 }
 
@@ -735,17 +809,7 @@ __device__ void batch_run_slab(const BatchJobDev &J, int r, int slab, uint32_t t
     const uint32_t t0 = J.t_now[r];
     if (!first && t0 >= t_stop) return;
     const int z0 = slab * S::NZ;
-    const int zb = (z0 + L - 1) % L;  // the plane below the slab
-    const uint32_t *src = J.spins + (size_t)r * 2 * S::POS;
-    for (int c = 0; c < 2; ++c)
-        for (int i = (int)threadIdx.x; i < S::SPOS; i += nt)
-            batch_lds[c * S::SPOS + i] = src[(size_t)c * S::POS + (size_t)z0 * S::PL + i];
-    for (int dc = 0; dc < 6; ++dc)
-        for (int i = (int)threadIdx.x; i < S::SPOS; i += nt)
-            batch_lds[(2 + dc) * S::SPOS + i] = J.bonds[(size_t)dc * S::POS + (size_t)z0 * S::PL + i];
-    for (int c = 0; c < 2; ++c)
-        for (int i = (int)threadIdx.x; i < S::PL; i += nt)
-            batch_lds[S::HALO + c * S::PL + i] = J.bonds[(size_t)(4 + c) * S::POS + (size_t)zb * S::PL + i];
+    slab_load<L, RW>(J, slab, J.spins + (size_t)r * 2 * S::POS);
     if constexpr (SEL == SEL_LDS) fill_select_tables(batch_tables(), J.thr1, J.thr2, J.thr3, (int)threadIdx.x, nt);
     uint32_t *abort_flag = batch_lds + S::FLAG + 1;
     if (threadIdx.x == 0) *abort_flag = 0;
