@@ -757,17 +757,20 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
         ea::SlabLaunch a{};
         a.L = y.L;
         a.RW = y.RW;
-        a.g = plan.g;
+        // A launch needs at least one exchange: a slab that ends without having
+        // waited for its neighbours would write its planes back while they may
+        // still be loading them as ghosts.
+        a.n_half = 2 * chunk;
+        a.g = a.n_half > (uint32_t)plan.g ? plan.g : 1;
         a.B = plan.B;
         a.P = 2 * n * y.L;
         a.emax = plan.emax;
         a.tables = tables;
-        a.n_half = 2 * chunk;
         a.n_runs = n;
         a.err = lead->err_dev;
         a.order = debug_grid_order();
         a.poison = debug_poison_word();
-        const uint64_t n_cycles = (a.n_half + (uint64_t)plan.g - 1) / (uint64_t)plan.g;
+        const uint64_t n_cycles = (a.n_half + (uint64_t)a.g - 1) / (uint64_t)a.g;
         for (int i = 0; i < n; ++i) {
             ea_sim *m = runs[i];
             if ((m->xserial & 0xffffffffull) + n_cycles + 2 >= (1ull << 32)) {
