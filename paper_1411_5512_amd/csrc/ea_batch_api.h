@@ -185,6 +185,7 @@ ea::BatchJobDev make_job_dev(const BatchJobHost &h)
     d.thr1 = h.thr[0];
     d.thr2 = h.thr[1];
     d.thr3 = h.thr[2];
+    d.pcut = h.pcut;
     d.n_meas = h.job.n_meas;
     d.n_tw = h.job.n_tw;
     d.obs_stride = h.obs_stride;
@@ -799,12 +800,16 @@ ea_status batch_create_cfg(const ea_job *jobs, int32_t n_jobs, void *stream, con
 // captured run starts with).
 ea_status reset_batch_device(ea_batch *b)
 {
-    hipLaunchKernelGGL(ea::zero_u32_kernel, dim3(1), dim3(64), 0, b->stream, b->d_err, (size_t)1);
-    EA_HIP(hipGetLastError());
+    int pos = 0;  // the longest plane
     for (auto &h : b->jobs) {
-        ea_status st = init_job_device(h, b->stream);
-        if (st != EA_OK) return st;
+        pos = std::max(pos, h.POS);
+        h.t_host = 0;
+        h.started = false;
+        h.obs_fetched = false;
     }
+    hipLaunchKernelGGL(ea::batch_reset_kernel, dim3((unsigned)b->jobs.size(), 10, blocks_for((size_t)pos)), dim3(256), 0,
+                       b->stream, b->d_jobs, b->d_err);
+    EA_HIP(hipGetLastError());
     return EA_OK;
 }
 

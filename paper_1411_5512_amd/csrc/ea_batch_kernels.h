@@ -61,6 +61,7 @@ struct BatchJobDev {
     int32_t sel;  // SEL_LDS or SEL_REG
     uint32_t k0, k1, sample;
     uint32_t thr1, thr2, thr3;
+    uint64_t pcut;
     int32_t n_meas, n_tw, obs_stride;
     uint32_t *spins;          // [replica][colour][POS]: state between launches
     const uint32_t *bonds;    // [direction][colour][POS]
@@ -918,6 +919,45 @@ __global__ __launch_bounds__(kBatchThreads) void batch_kernel(const BatchJobDev 
     case 64: batch_dispatch_L<64>(J, u.replica, u.slab, u.t_stop, first); break;
     default: break;
     }
+}
+
+// Every job's initial state in one launch: couplings, both replicas' spins,
+// and the counters, arrivals, times and publications cleared.  blockIdx.x =
+// job, blockIdx.y = plane (6 of couplings, 4 of spins), blockIdx.z = part of
+// it.  (With four launches per job, the launches were the time: 256 jobs 3000
+// us against 143 now, 16 jobs 238 against 21.)
+__global__ __launch_bounds__(256) void batch_reset_kernel(const BatchJobDev *__restrict__ jobs, uint32_t *err)
+{
+    const BatchJobDev &J = jobs[blockIdx.x];
+    const int plane = (int)blockIdx.y, at = (int)(blockIdx.z * blockDim.x + threadIdx.x);
+    const int step = (int)(gridDim.z * blockDim.x);
+    const int R = J.L / 2, W = R / J.rw, POS = J.L * J.L * J.rw;
+    const size_t n = (size_t)J.n_meas * (size_t)J.obs_stride;
+    for (size_t i = (size_t)(plane * step + at); i < n; i += (size_t)(10 * step)) J.obs[i] = 0ull;
+    if (plane == 0) {
+        // arrive[n_meas] and t_now[2] are contiguous
+        for (int i = at; i < J.n_meas + 2; i += step) J.arrive[i] = 0u;
+        if (at < 4) J.pub[at] = 0ull;
+        if (blockIdx.x == 0 && at == 0) *err = 0u;
+    }
+    if (at >= POS) return;
+    const int row = at / J.rw, w = at - row * J.rw, c = plane & 1;
+    const int what = plane < 6 ? plane >> 1 : 3 + ((plane - 6) >> 1);
+    const uint32_t quad0 = (uint32_t)((row * R + w * W) >> 2);
+    uint32_t bits = 0;
+    switch (W) {
+    case 4: bits = init_word<4>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    case 8: bits = init_word<8>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    case 12: bits = init_word<12>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    case 16: bits = init_word<16>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    case 20: bits = init_word<20>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    case 24: bits = init_word<24>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    case 28: bits = init_word<28>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    default: bits = init_word<32>(what, c, quad0, J.sample, J.k0, J.k1, J.pcut); break;
+    }
+    uint32_t *dst = plane < 6 ? const_cast<uint32_t *>(J.bonds) + (size_t)plane * POS
+                              : J.spins + (size_t)(plane - 6) * POS;
+    dst[at] = bits;
 }
 
 }  // namespace ea

@@ -30,9 +30,34 @@ __device__ __forceinline__ size_t plane_off(const Geom &g, int a, int c)
 
 // --------------------------------------------------------------------------
 // Initial state (Sec. II): couplings with P(J = -1) = p and two replicas of
-// uniformly random spins.  One thread per (row, word) of one colour; grid.y
-// selects what is drawn: 0..2 the coupling planes of direction d, 3..4 the
-// spins of replica 0 / 1; grid.z the colour.
+// uniformly random spins.
+
+// One packed word of colour c, from block quad0 on; what = 0..2: couplings of
+// that direction, 3..4: spins of replica 0 / 1.
+template <int W>
+__device__ __forceinline__ uint32_t init_word(int what, int c, uint32_t quad0, uint32_t sample, uint32_t k0,
+                                              uint32_t k1, uint64_t pcut)
+{
+    const bool is_bond = what < 3;
+    const uint32_t aux = is_bond ? (uint32_t)what : 0u;
+    const uint32_t rep = is_bond ? 0u : (uint32_t)(what - 3);
+    const uint32_t c2 = counter_word2(is_bond ? TAG_BOND : TAG_INIT, (uint32_t)c, rep);
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < W / 4; ++j) {
+        const Words4 u = philox10(aux, quad0 + (uint32_t)j, c2, sample, k0, k1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t bit = is_bond ? (uint32_t)((uint64_t)u.v[q] < pcut) : (u.v[q] >> 31);
+            bits |= bit << (4 * j + q);
+        }
+    }
+    return bits;
+}
+
+// One thread per (row, word) of one colour; grid.y selects what is drawn: 0..2
+// the coupling planes of direction d, 3..4 the spins of replica 0 / 1; grid.z
+// the colour.
 // The first block also clears the caller's error word and n_clear counters
 // (err may be null).
 template <int W>
@@ -52,19 +77,7 @@ __global__ __launch_bounds__(256) void init_kernel(Lattice lat, Geom g, uint32_t
     const int w = tid - row * g.RW;
     const uint32_t quad0 = (uint32_t)((row * g.R + w * W) >> 2);
     const bool is_bond = what < 3;
-    const uint32_t aux = is_bond ? (uint32_t)what : 0u;
-    const uint32_t rep = is_bond ? 0u : (uint32_t)(what - 3);
-    const uint32_t c2 = counter_word2(is_bond ? TAG_BOND : TAG_INIT, (uint32_t)c, rep);
-    uint32_t bits = 0;
-#pragma unroll
-    for (int j = 0; j < W / 4; ++j) {
-        const Words4 u = philox10(aux, quad0 + (uint32_t)j, c2, sample, k0, k1);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t bit = is_bond ? (uint32_t)((uint64_t)u.v[q] < pcut) : (u.v[q] >> 31);
-            bits |= bit << (4 * j + q);
-        }
-    }
+    const uint32_t bits = init_word<W>(what, c, quad0, sample, k0, k1, pcut);
     uint32_t *dst = is_bond ? lat.bonds + plane_off(g, what, c) : lat.spins + plane_off(g, what - 3, c);
     dst[tid] = bits;
 }
