@@ -174,8 +174,8 @@ ea_status ea_words_per_row(const ea_sim *sim, int32_t *rw);
  * (work ~ L^3 log L for L = 2^k or 3 2^k, ~ L^3 (m + P) for L = m P with
  * another odd factor m).  Synchronises; allocates a device
  * scratch buffer of 8 (2 L^2 ceil(L/64) + 3 (L/2)^2 + 1) bytes on the first
- * call, and on the first FFT-route call one of 16 L^3 + 256 bytes (256 MiB
- * at L = 256), both kept until ea_destroy.  EA_ERR_ARG for n_shells outside
+ * call, and on the first FFT-route call one of at most 8 L^2 (L + 16) + 256 bytes
+ * (136 MiB at L = 256), both kept until ea_destroy.  EA_ERR_ARG for n_shells outside
  * [1, 3 (L/2)^2 + 1]; EA_ERR_NOMEM if a scratch buffer cannot be allocated;
  * EA_ERR_DEVICE if a sum of the FFT route is not within 1/4 of an integer
  * (outside the fp64 error bound, which is below 1e-7 here). */
@@ -373,7 +373,7 @@ ea_status ea_batch_result(ea_batch *b, int32_t job, int32_t k, ea_obs *out);
  * job `job` at its measurement k, from the configuration of both replicas
  * that the batched kernel publishes at each measurement: out[n_shells].
  * Synchronises; allocates a scratch buffer of 8 (2 L^2 ceil(L/64) +
- * n_shells) bytes (16 L^3 more on the FFT route) on the first call, grown
+ * n_shells) bytes (up to 8 L^2 (L + 16) more on the FFT route) on the first call, grown
  * when a later call needs more, kept until ea_batch_destroy.  EA_ERR_ARG for a job or k out of
  * range or n_shells outside [1, 3 (L/2)^2 + 1]; EA_ERR_STATE if measurement
  * k has not been reached. */
@@ -538,8 +538,8 @@ ea_status ea_msc_measure(ea_msc *batch, ea_obs *out);
 
 /* Full-vector C4 shells (as ea_c4_shells) of sample `sample` (0 .. B-1) of
  * the batch at the current time: out[n_shells].  Synchronises; allocates a
- * scratch buffer of 8 (2 L^2 ceil(L/64) + n_shells) bytes (16 L^3 more on
- * the FFT route) on the first call, grown when a later call needs more, kept
+ * scratch buffer of 8 (2 L^2 ceil(L/64) + n_shells) bytes (up to 8 L^2
+ * (L + 16) more on the FFT route) on the first call, grown when a later call needs more, kept
  * until ea_msc_destroy.  EA_ERR_ARG for a sample out of range or n_shells outside
  * [1, 3 (L/2)^2 + 1]. */
 ea_status ea_msc_c4_shells(ea_msc *m, int32_t sample, int32_t n_shells, int64_t *out);

@@ -848,8 +848,8 @@ ea_status launch_shell_rows(const unsigned long long *qd, int L, int n_shells, u
 // Route of the full-vector C4 shells (ea_set_shell_route).
 std::atomic<int32_t> g_shell_route{EA_SHELLS_AUTO};
 // automatic route: FFT from this side on.  A call, direct against FFT: L = 32
-// 66 / 103 us, L = 40 84 / 117, L = 48 123 / 103, L = 56 239 / 123, L = 72 865 /
-// 141, L = 136 22 ms / 0.35, L = 248 773 ms / 1.9.
+// 57 / 79 us, L = 48 112 / 84, L = 72 876 / 109, L = 128 15.9 ms / 0.14, L = 136
+// 22 ms / 0.23, L = 256 863 ms / 0.37.
 constexpr int kFftAutoMinL = 48;
 
 bool shells_by_fft(int L)
@@ -890,19 +890,27 @@ struct ShellScratch {
 };
 
 // Device bytes of the FFT route: the complex array, then the error word.
-size_t fft_work_bytes(int L) { return 16 * (size_t)L * L * L + 256; }
+size_t fft_array_bytes(int L) { return 16 * (size_t)L * L * ea::fft_stride(L); }
+size_t fft_work_bytes(int L) { return fft_array_bytes(L) + 256; }
+
+// Workgroups of a pass along y or z, B lines each.
+template <int OP>
+unsigned fft_tiles(int L, int B)
+{
+    return (unsigned)((ea::fft_n_lines<OP>(L) + B - 1) / B);
+}
 
 template <int L>
 void launch_fft_passes(const ea::FftArgs &a, hipStream_t stream)
 {
     constexpr int H = L / 2, B = ea::FftShape<L>::B;
-    const dim3 grid((unsigned)(L * L / B)), block(ea::kFftThreads);
-    const dim3 half((unsigned)((H + 1) * (L / B)));  // tiles of the planes z <= L/2
+    const dim3 rows((unsigned)(L * L / (2 * B))), block(ea::kFftThreads);
     const dim3 bins((unsigned)((H + 1) * ((H + ea::kFftBinY) / ea::kFftBinY)));
-    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftFwdBitsX>), grid, block, 0, stream, a);
-    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftFwdY>), grid, block, 0, stream, a);
-    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftSquareZ>), grid, block, 0, stream, a);
-    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftInvY>), half, block, 0, stream, a);
+    hipLaunchKernelGGL((ea::fft_bits_kernel<L>), rows, block, 0, stream, a);
+    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftFwdY>), dim3(fft_tiles<ea::kFftFwdY>(L, B)), block, 0, stream, a);
+    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftSquareZ>), dim3(fft_tiles<ea::kFftSquareZ>(L, B)), block, 0,
+                       stream, a);
+    hipLaunchKernelGGL((ea::fft_pass_kernel<L, ea::kFftInvY>), dim3(fft_tiles<ea::kFftInvY>(L, B)), block, 0, stream, a);
     hipLaunchKernelGGL((ea::fft_bin_kernel<L>), bins, block, 0, stream, a);
     hipLaunchKernelGGL(ea::fft_shell_sum_kernel, dim3(blocks_for((size_t)(H + 1) * (H + 1) * (H + 1))), dim3(256), 0,
                        stream, a, L);
@@ -918,20 +926,22 @@ void launch_fft_general(const ea::FftArgs &a, int L, hipStream_t stream)
     f.B = ea::fft_lines_per_tile(L);
     f.LP = L + 1;
     const int H = L / 2;
-    const dim3 grid((unsigned)(L * L / f.B)), block(ea::kFftThreads);
-    const dim3 half((unsigned)((H + 1) * (L / f.B)));  // tiles of the planes z <= L/2
+    const dim3 rows((unsigned)(L * L / (2 * f.B))), block(ea::kFftThreads);
     const dim3 bins((unsigned)((H + 1) * ((H + ea::kFftBinY) / ea::kFftBinY)));
-    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftFwdBitsX>), grid, block, 0, stream, a, f);
-    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftFwdY>), grid, block, 0, stream, a, f);
-    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftSquareZ>), grid, block, 0, stream, a, f);
-    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftInvY>), half, block, 0, stream, a, f);
+    hipLaunchKernelGGL(ea::fft_general_bits_kernel, rows, block, 0, stream, a, f);
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftFwdY>), dim3(fft_tiles<ea::kFftFwdY>(L, f.B)), block, 0,
+                       stream, a, f);
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftSquareZ>), dim3(fft_tiles<ea::kFftSquareZ>(L, f.B)), block,
+                       0, stream, a, f);
+    hipLaunchKernelGGL((ea::fft_general_pass_kernel<ea::kFftInvY>), dim3(fft_tiles<ea::kFftInvY>(L, f.B)), block, 0,
+                       stream, a, f);
     hipLaunchKernelGGL(ea::fft_general_bin_kernel, bins, block, 0, stream, a, f);
     hipLaunchKernelGGL(ea::fft_shell_sum_kernel, dim3(blocks_for((size_t)(H + 1) * (H + 1) * (H + 1))), dim3(256), 0,
                        stream, a, L);
 }
 
 // Shell sums of dense overlap rows (dw words per row) through the FFT route
-// (ea_fft.h), added to `shells`; `work` holds fft_work_bytes(L) bytes.
+// (ea_fft.h), into `shells`; `work` holds fft_work_bytes(L) bytes.
 ea_status launch_fft_shells(const unsigned long long *qd, int dw, int L, int n_shells, unsigned long long *shells,
                             void *work, hipStream_t stream)
 {
@@ -941,9 +951,7 @@ ea_status launch_fft_shells(const unsigned long long *qd, int dw, int L, int n_s
     a.dw = dw;
     a.n_shells = n_shells;
     a.shells = shells;
-    unsigned long long *err = (unsigned long long *)((char *)work + 16 * (size_t)L * L * L);
-    a.err = (unsigned int *)err;
-    hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(1), dim3(256), 0, stream, err, (size_t)1);
+    a.err = (unsigned int *)((char *)work + fft_array_bytes(L));
     switch (L) {
     case 8: launch_fft_passes<8>(a, stream); break;
     case 16: launch_fft_passes<16>(a, stream); break;
@@ -961,14 +969,12 @@ ea_status launch_fft_shells(const unsigned long long *qd, int dw, int L, int n_s
     return EA_OK;
 }
 
-// After the stream has passed launch_fft_shells: EA_ERR_DEVICE if a sum was
-// not within 1/4 of an integer (it never is within the fp64 error bound).
-ea_status fft_shells_check(const void *work, int L, hipStream_t stream)
+// The sums of launch_fft_shells on the host: EA_ERR_DEVICE if one was not
+// within 1/4 of an integer (it never is within the fp64 error bound).
+ea_status fft_shells_check(const int64_t *shells, int L)
 {
-    uint32_t e = 0;
-    EA_HIP(hipMemcpyAsync(&e, (const char *)work + 16 * (size_t)L * L * L, 4, hipMemcpyDeviceToHost, stream));
-    EA_HIP(hipStreamSynchronize(stream));
-    if (e) return fail(EA_ERR_DEVICE, "full-vector C4 (FFT route, L=%d): a correlation sum was not an integer", L);
+    if ((unsigned long long)shells[0] == ea::kFftBad)
+        return fail(EA_ERR_DEVICE, "full-vector C4 (FFT route, L=%d): a correlation sum was not an integer", L);
     return EA_OK;
 }
 
@@ -1403,8 +1409,6 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
         }
     }
     unsigned long long *qd = s->c4_scratch, *shells = s->c4_scratch + q_words;
-    hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for((size_t)n_shells)), dim3(256), 0, s->stream, shells,
-                       (size_t)n_shells);
     ea::Geom g = s->geom();
     EA_DISPATCH_W(s->lay.W, hipLaunchKernelGGL((ea::dense_q_kernel<WW>), dim3(blocks_for(q_words)), dim3(256), 0,
                                                s->stream, s->lat, g, dw, qd));
@@ -1420,6 +1424,9 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
             fft = false;  // sides that once had only the direct route keep it where memory is short
         }
     }
+    if (!fft)
+        hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for((size_t)n_shells)), dim3(256), 0, s->stream, shells,
+                           (size_t)n_shells);
     if (fft) {
         ea_status st = launch_fft_shells(qd, dw, L, n_shells, shells, s->fft_work, s->stream);
         if (st != EA_OK) return st;
@@ -1435,9 +1442,8 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
     }
     EA_HIP(hipGetLastError());
     EA_HIP(hipMemcpyAsync(out, shells, 8 * (size_t)n_shells, hipMemcpyDeviceToHost, s->stream));
-    if (fft) return fft_shells_check(s->fft_work, L, s->stream);
     EA_HIP(hipStreamSynchronize(s->stream));
-    return EA_OK;
+    return fft ? fft_shells_check(out, L) : EA_OK;
 }
 
 ea_status ea_set_shell_route(int32_t route)

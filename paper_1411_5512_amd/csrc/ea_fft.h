@@ -3,16 +3,20 @@
 // (24 .. 192), and in a run-time form at the end of this file for the other
 // multiples of 8: with F the 3D DFT of q = S_0 S_1, the unnormalised inverse DFT
 // of |F|^2 is N sum_x q(x) q(x + r) for every r at once.  Five passes over a
-// complex fp64 array of L^3 elements, each transforming whole lines of one
-// axis in LDS, replace the direct kernel's L^6 / 64 word operations by
-// O(L^3 log L) flops and 128 bytes of HBM traffic per site.
+// complex fp64 array of L^2 rows of L/2 + 1 elements, each transforming whole lines
+// of one axis in LDS, replace the direct kernel's L^6 / 64 word operations by
+// O(L^3 log L) flops and 56 bytes of HBM traffic per site.  q is real, so
+// only the columns kx <= L/2 are kept between the passes along x, and those
+// two passes transform two real rows as one complex line.  At L = 128 the five
+// passes take 69 us (79 with all columns), a whole call 127 (158); each
+// workgroup's chain of load, transform and store bounds them, at about 2 TB/s.
 //
 // The forward transforms are decimation in frequency (natural order in,
 // digit-reversed order out along each axis: for L = 3P a radix-3 stage of
 // span P first, then radix-2 stages on each third) and the inverse ones
 // decimation in time (digit-reversed in, natural out: the same stages in the
-// opposite order); |F|^2 is taken pointwise in between, so no pass permutes
-// its data.  The autocorrelation is even, so the last two passes transform
+// opposite order); |F|^2 is taken pointwise in between, so only the passes
+// along x, which pair kx with L - kx, look an index up.  The autocorrelation is even, so the last two passes transform
 // only the planes z <= L/2.  The sums are integers of magnitude <= N and the
 // rounding error of the fp64 transforms is ~1e-16 log2(N) of the largest
 // |F|^2 (<= N^2), i.e. below 1e-7 after the division by N at L = 256: each
@@ -33,13 +37,15 @@ constexpr int kFftThreads = 256;
 enum FftOp { kFftFwdBitsX = 0, kFftFwdY = 1, kFftSquareZ = 2, kFftInvY = 3, kFftInvBinX = 4 };
 
 struct FftArgs {
-    double2 *z;                    // [L^3], element (x, y, z) at (z L + y) L + x
+    double2 *z;                    // element (kx <= L/2, y, z) at (z L + y) fft_stride(L) + kx
     const unsigned long long *qd;  // dense overlap rows (dense_q_kernel): row y + L z, dw words, bit x set iff q = -1
     int dw;
     int n_shells;
-    unsigned long long *shells;  // [n_shells] sums, added to (two's complement)
+    unsigned long long *shells;  // [n_shells] sums; [0] = kFftBad if *err
     unsigned int *err;           // set to 1 if a sum is not within 1/4 of an integer
 };
+
+constexpr unsigned long long kFftBad = 1ull << 63;
 
 constexpr bool fft_pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
 constexpr int fft_log2(int n) { return n <= 1 ? 0 : 1 + fft_log2(n / 2); }
@@ -326,146 +332,224 @@ __device__ __forceinline__ void fft_twiddles(double2 *tw, int tid)
     }
 }
 
-// Element j of a workgroup's tile: line b, index i along the axis, and its
-// position in the L^3 array.  Along x the tile is B consecutive rows (one
-// contiguous run); along y (z) it is B consecutive x of one z (y), so that a
-// wave reads runs of B consecutive elements.
-template <int L, int AXIS>
-__device__ __forceinline__ void fft_element(int w, int j, int &b, int &i, size_t &pos)
+// Elements from row to row: L/2 + 1 of them hold data.  A multiple of 128
+// bytes, so that the runs of eight columns that passes along y and z read and
+// write are whole cache lines (rows of L/2 + 1: the passes along y of L = 128
+// 14.9 and 13.4 us, now 13.0 and 11.2).
+__host__ __device__ constexpr int fft_stride(int L) { return (L / 2 + 8) / 8 * 8; }
+
+// Where the forward transform leaves X[k].
+template <int L>
+__device__ __forceinline__ int fft_place(int k)
 {
-    constexpr int B = FftShape<L>::B, XB = L / B;  // tiles per row
-    if constexpr (AXIS == 0) {
-        b = j / L;
-        i = j - b * L;
-        pos = (size_t)w * B * L + (size_t)j;
-    } else {
-        b = j % B;
-        i = j / B;
-        const int o = w / XB, x = (w - o * XB) * B + b;
-        pos = AXIS == 1 ? ((size_t)o * L + (size_t)i) * L + (size_t)x : ((size_t)i * L + (size_t)o) * L + (size_t)x;
+    using S = FftShape<L>;
+    const int r = S::R3 ? k % 3 : 0, j = S::R3 ? k / 3 : k;
+    return r * S::P + (int)(__brev((unsigned)j) >> (32 - S::LOG2P));
+}
+
+// Element i of line `line` of a pass along y (z): the lines are the columns
+// of every z (y), so consecutive lines are consecutive in memory.
+template <int OP>
+__device__ __forceinline__ size_t fft_element(int L, int line, int i)
+{
+    const int S = fft_stride(L), o = line / S, x = line - o * S;
+    return ((size_t)(OP == kFftSquareZ ? i * L + o : o * L + i)) * S + x;
+}
+
+// Lines of such a pass, padding included: kFftInvY needs only the planes z <= L/2 (and
+// kFftSquareZ stores only those): the autocorrelation is even, A(-r) = A(r),
+// so the shells follow from half of it (fft_bin_kernel).
+template <int OP>
+__host__ __device__ constexpr int fft_n_lines(int L)
+{
+    return (OP == kFftInvY ? L / 2 + 1 : L) * fft_stride(L);
+}
+
+// Does the line hold data (kx <= L/2, and inside the array)?
+template <int OP>
+__device__ __forceinline__ bool fft_line_ok(int L, int line)
+{
+    return line < fft_n_lines<OP>(L) && line % fft_stride(L) <= L / 2;
+}
+
+// The two real rows' columns k of a packed line: Zk = Z[k], Zm = Z[L - k].
+__device__ __forceinline__ double2 fft_unpack(double2 zk, double2 zm, bool second)
+{
+    return second ? make_double2(0.5 * (zk.y + zm.y), -0.5 * (zk.x - zm.x))
+                  : make_double2(0.5 * (zk.x + zm.x), 0.5 * (zk.y - zm.y));
+}
+
+// The tile of pass kFftFwdBitsX before its transform: 2 B rows, packed in
+// pairs as complex lines LP apart.  Their words come through LDS: read where
+// the sites are expanded they were a chain of loads (the pass at L = 128 took
+// 19 us).
+__device__ __forceinline__ void fft_bits(const FftArgs &a, int L, int B, int LP, double2 *s, int tid)
+{
+    __shared__ unsigned long long rows[256];
+    const int nw = (L + 63) / 64, n = 2 * B * nw;  // 64 at most
+    if (tid < n) rows[tid] = a.qd[((size_t)blockIdx.x * 2 * B + (size_t)(tid / nw)) * (size_t)a.dw + (size_t)(tid % nw)];
+    __syncthreads();
+    for (int j = tid; j < B * L; j += kFftThreads) {
+        const int line = j / L, i = j - line * L;
+        const unsigned long long *q = rows + 2 * line * nw + (i >> 6);
+        s[line * LP + i] =
+            make_double2((q[0] >> (i & 63)) & 1ull ? -1.0 : 1.0, (q[nw] >> (i & 63)) & 1ull ? -1.0 : 1.0);
     }
 }
 
-// Passes kFftFwdBitsX .. kFftInvY, one tile per workgroup: L^2 / B tiles,
-// except kFftInvY, which needs only the planes z <= L/2 ((L/2 + 1) L / B
-// tiles; kFftSquareZ stores only those): the autocorrelation is even, A(-r)
-// = A(r), so the shells follow from half of it (fft_bin_kernel).
+// The first pass also clears what the last ones add to.
+__device__ __forceinline__ void fft_clear(const FftArgs &a, int tid)
+{
+    for (int k = (int)blockIdx.x * kFftThreads + tid; k < a.n_shells; k += (int)gridDim.x * kFftThreads)
+        a.shells[k] = 0ull;
+    if (blockIdx.x == 0 && tid == 0) *a.err = 0u;
+}
+
+// Pass kFftFwdBitsX: 2 B rows per workgroup, transformed in pairs.
+template <int L>
+__global__ __launch_bounds__(kFftThreads) void fft_bits_kernel(FftArgs a)
+{
+    using S = FftShape<L>;
+    constexpr int B = S::B, H1 = L / 2 + 1;
+    __shared__ double2 s[B * S::LP];
+    __shared__ double2 tw[S::NTW];
+    const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
+    fft_clear(a, tid);
+    fft_bits(a, L, B, S::LP, s, tid);
+    fft_twiddles<L>(tw, tid);
+    __syncthreads();
+    fft_lines<L, B, false>(s, tw, tid);
+    for (int j = tid; j < 2 * B * H1; j += kFftThreads) {
+        const int row = j / H1, k = j - row * H1;
+        const double2 *p = s + (row >> 1) * S::LP;
+        a.z[((size_t)w * 2 * B + (size_t)row) * fft_stride(L) + (size_t)k] =
+            fft_unpack(p[fft_place<L>(k)], p[fft_place<L>(k == 0 ? 0 : L - k)], row & 1);
+    }
+}
+
+// Passes kFftFwdY .. kFftInvY, B lines per workgroup.  A thread's elements
+// all belong to one line; they are on their way while the twiddles are
+// computed.
 template <int L, int OP>
 __global__ __launch_bounds__(kFftThreads) void fft_pass_kernel(FftArgs a)
 {
     using S = FftShape<L>;
-    constexpr int B = S::B, TILE = B * L;
-    constexpr int AXIS = OP == kFftFwdBitsX ? 0 : (OP == kFftSquareZ ? 2 : 1);
-    static_assert(OP != kFftInvBinX, "the last pass is fft_bin_kernel");
+    constexpr int B = S::B, IS = kFftThreads / B, PER = (L + IS - 1) / IS;
+    static_assert(OP == kFftFwdY || OP == kFftSquareZ || OP == kFftInvY, "a pass along y or z");
+    static_assert(kFftThreads % B == 0, "one line per thread");
     __shared__ double2 s[B * S::LP];
     __shared__ double2 tw[S::NTW];
-    const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
+    const int tid = (int)threadIdx.x, b = tid % B, i0 = tid / B, line = (int)blockIdx.x * B + b;
+    const bool ok = fft_line_ok<OP>(L, line);
 
-    fft_twiddles<L>(tw, tid);
-    for (int j = tid; j < TILE; j += kFftThreads) {
-        int b, i;
-        size_t pos;
-        fft_element<L, AXIS>(w, j, b, i, pos);
-        double2 v;
-        if constexpr (OP == kFftFwdBitsX) {
-            const size_t row = (size_t)w * B + (size_t)b;
-            const unsigned long long word = a.qd[row * (size_t)a.dw + (size_t)(i >> 6)];
-            v = make_double2((word >> (i & 63)) & 1ull ? -1.0 : 1.0, 0.0);
-        } else {
-            v = a.z[pos];
-        }
-        s[b * S::LP + i] = v;
+    double2 v[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int i = i0 + e * IS;
+        v[e] = ok && i < L ? a.z[fft_element<OP>(L, line, i)] : make_double2(0.0, 0.0);
     }
+    fft_twiddles<L>(tw, tid);
+    double2 *p = s + b * S::LP;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+        if (i0 + e * IS < L) p[i0 + e * IS] = v[e];
     __syncthreads();
 
-    if constexpr (OP == kFftFwdBitsX || OP == kFftFwdY) {
-        fft_lines<L, B, false>(s, tw, tid);
-    } else if constexpr (OP == kFftSquareZ) {
-        fft_lines<L, B, false>(s, tw, tid);
-        for (int j = tid; j < TILE; j += kFftThreads) {
-            double2 *p = s + (j / L) * S::LP + (j % L);
-            const double2 v = *p;
-            *p = make_double2(v.x * v.x + v.y * v.y, 0.0);
-        }
-        __syncthreads();
+    if constexpr (OP == kFftInvY) {
         fft_lines<L, B, true>(s, tw, tid);
     } else {
-        fft_lines<L, B, true>(s, tw, tid);
+        fft_lines<L, B, false>(s, tw, tid);
+        if constexpr (OP == kFftSquareZ) {
+            for (int i = i0; i < L; i += IS) p[i] = make_double2(p[i].x * p[i].x + p[i].y * p[i].y, 0.0);
+            __syncthreads();
+            fft_lines<L, B, true>(s, tw, tid);
+        }
     }
-
-    for (int j = tid; j < TILE; j += kFftThreads) {
-        int b, i;
-        size_t pos;
-        fft_element<L, AXIS>(w, j, b, i, pos);
-        if (OP == kFftSquareZ && i > L / 2) continue;
-        a.z[pos] = s[b * S::LP + i];
-    }
+    if (!ok) return;
+    for (int i = i0; i < (OP == kFftSquareZ ? L / 2 + 1 : L); i += IS) a.z[fft_element<OP>(L, line, i)] = p[i];
 }
 
-constexpr int kFftBinY = 4;  // y values per workgroup of the last pass
+constexpr int kFftBinY = 8;  // y values per workgroup of the last pass
 
 // The sums T(i, y, z) of the last pass, one per |x| = i, |y|, |z| <= L/2,
 // at [(z (L/2 + 1) + y) (L/2 + 1) + i], in the planes z > L/2 of the complex
-// array (no pass reads those after kFftSquareZ; they hold 16 (L/2 - 1) L^2
-// bytes, more than the 8 (L/2 + 1)^3 needed).
-template <int L>
-__device__ __forceinline__ long long *fft_sums(double2 *z)
+// array (no pass reads those after kFftSquareZ; they hold at least 16 (L/2 - 1)
+// L (L/2 + 1) bytes, more than the 8 (L/2 + 1)^3 needed).
+__device__ __forceinline__ long long *fft_sums(double2 *z, int L)
 {
-    static_assert((size_t)16 * (L / 2 - 1) * L * L >= (size_t)8 * (L / 2 + 1) * (L / 2 + 1) * (L / 2 + 1),
-                  "the sums fit in the planes z > L/2");
-    return reinterpret_cast<long long *>(z + (size_t)(L / 2 + 1) * L * L);
+    return reinterpret_cast<long long *>(z + (size_t)(L / 2 + 1) * L * fft_stride(L));
+}
+
+// Columns k and L - k of the line that packs the rows (y, z) and (L - y, z):
+// b1 + i b2 and conj(b1) + i conj(b2).  Rows past L/2 and the mirror rows of
+// y = 0 and L/2 are taken as 0.
+__device__ __forceinline__ void fft_pack(const FftArgs &a, int L, int z, int y, int k, double2 &zk, double2 &zm)
+{
+    const int H = L / 2, S = fft_stride(L);
+    const double2 *at = a.z + (size_t)z * L * S + (size_t)k;
+    double2 b1 = make_double2(0.0, 0.0), b2 = b1;
+    if (y <= H) b1 = at[(size_t)y * S];
+    if (y > 0 && y < H) b2 = at[(size_t)(L - y) * S];
+    zk = make_double2(b1.x - b2.y, b1.y + b2.x);
+    zm = make_double2(b1.x + b2.y, b2.x - b1.y);
+}
+
+// T(i, y, z) from the transformed line p: the rounded sums at x = +-i of both
+// rows (the real and the imaginary part), twice for 0 < z < L/2, where the
+// row (L - y, L - z), not transformed, holds A(-x, y, z).
+__device__ __forceinline__ void fft_bin(const FftArgs &a, int L, const double2 *p, int i, int y, int z, double n)
+{
+    const int H = L / 2;
+    long long sum = 0;
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {  // bit 0: x -> L - x, bit 1: y -> L - y
+        if ((e & 1) && (i == 0 || i == H)) continue;
+        if ((e & 2) && (y == 0 || y == H)) continue;
+        const double2 c = p[(e & 1) ? L - i : i];
+        const double v = (e & 2 ? c.y : c.x) / n;
+        const double r = rint(v);
+        bad |= !(fabs(v - r) <= 0.25);  // NaN included
+        sum += (long long)r;
+    }
+    if (bad) atomicOr(a.err, 1u);
+    fft_sums(a.z, L)[((size_t)z * (H + 1) + (size_t)y) * (H + 1) + (size_t)i] = z == 0 || z == H ? sum : 2 * sum;
 }
 
 // The last transform pass, on the planes z = 0 .. L/2: a workgroup takes
-// kFftBinY values y <= L/2 of one z and, for each, the rows y and L - y (one
-// row if y is 0 or L/2), transforms them along x (DIT), and for every
-// |x| = i <= L/2 stores the rounded sums at x = +-i of both rows as T(i, y, z),
-// the sum over the minimum images (+-i, +-y, z).  A row (y, z) and the row
-// (L - y, L - z) hold A(x, y, z) and A(-x, y, z), so for 0 < z < L/2 the
-// sums count twice for the planes L - z that are not transformed.
+// kFftBinY values y <= L/2 of one z and for each the rows y and L - y as one
+// complex line, transforms them along x (DIT), and stores the sums over the
+// minimum images (+-i, +-y, z).
 template <int L>
 __global__ __launch_bounds__(kFftThreads) void fft_bin_kernel(FftArgs a)
 {
     using S = FftShape<L>;
-    constexpr int H = L / 2, LP = S::LP, NL = 2 * kFftBinY;
-    constexpr int YB = (H + 1 + kFftBinY - 1) / kFftBinY;  // workgroups per plane
-    constexpr double kInvN = 1.0 / ((double)L * L * L);     // exact for power-of-two L
+    constexpr int H = L / 2, LP = S::LP, NL = kFftBinY, PER = (NL * (H + 1) + kFftThreads - 1) / kFftThreads;
+    constexpr int YB = (H + 1 + NL - 1) / NL;  // workgroups per plane
     __shared__ double2 s[NL * LP];
     __shared__ double2 tw[S::NTW];
     const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
-    const int z = w / YB, y0 = (w - z * YB) * kFftBinY;
+    const int z = w / YB, y0 = (w - z * YB) * NL;
 
+    double2 zk[PER], zm[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int j = tid + e * kFftThreads, line = j / (H + 1), k = j - line * (H + 1);
+        if (line < NL) fft_pack(a, L, z, y0 + line, k, zk[e], zm[e]);
+    }
     fft_twiddles<L>(tw, tid);
-    // line 2j: row (y0 + j, z); line 2j + 1: row (L - y0 - j, z) if 0 < y0 + j < L/2
-    for (int j = tid; j < NL * L; j += kFftThreads) {
-        const int line = j / L, x = j - line * L, y = y0 + (line >> 1);
-        const bool mirror = (line & 1) != 0;
-        double2 v = make_double2(0.0, 0.0);
-        if (y <= H && (!mirror || (y != 0 && y != H)))
-            v = a.z[((size_t)z * L + (size_t)(mirror ? L - y : y)) * L + (size_t)x];
-        s[line * LP + x] = v;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int j = tid + e * kFftThreads, line = j / (H + 1), k = j - line * (H + 1);
+        if (line >= NL) break;
+        s[line * LP + fft_place<L>(k)] = zk[e];
+        if (k > 0 && k < H) s[line * LP + fft_place<L>(L - k)] = zm[e];
     }
     __syncthreads();
     fft_lines<L, NL, true>(s, tw, tid);
-
-    const long long weight = (z == 0 || z == H) ? 1 : 2;
-    long long *T = fft_sums<L>(a.z);
-    for (int t = tid; t < kFftBinY * (H + 1); t += kFftThreads) {
+    for (int t = tid; t < NL * (H + 1); t += kFftThreads) {
         const int j = t / (H + 1), i = t - j * (H + 1), y = y0 + j;
-        if (y > H) continue;
-        long long sum = 0;
-        bool bad = false;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {  // bit 0: x -> L - x, bit 1: y -> L - y
-            if ((e & 1) && (i == 0 || i == H)) continue;
-            if ((e & 2) && (y == 0 || y == H)) continue;
-            const double v = s[(2 * j + (e >> 1)) * LP + ((e & 1) ? L - i : i)].x * kInvN;
-            const double r = rint(v);
-            bad |= !(fabs(v - r) <= 0.25);  // NaN included
-            sum += (long long)r;
-        }
-        if (bad) atomicOr(a.err, 1u);
-        T[((size_t)z * (H + 1) + (size_t)y) * (H + 1) + (size_t)i] = sum * weight;
+        if (y <= H) fft_bin(a, L, s + j * LP, i, y, z, (double)L * L * L);
     }
 }
 
@@ -476,7 +560,7 @@ __global__ __launch_bounds__(kFftThreads) void fft_bin_kernel(FftArgs a)
 __global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a, int L)
 {
     const int H1 = L / 2 + 1;
-    const long long *T = reinterpret_cast<const long long *>(a.z + (size_t)H1 * L * L);  // fft_sums
+    const long long *T = fft_sums(a.z, L);
     const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (t >= H1 * H1 * H1) return;
     const int p = t % H1, q = (t / H1) % H1, r = t / (H1 * H1);
@@ -486,6 +570,7 @@ __global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a, int L)
     auto at = [T, H1](int i, int y, int z) { return T[((size_t)z * H1 + (size_t)y) * H1 + (size_t)i]; };
     long long sum = at(p, q, r);
     if (p == q && q == r) {
+        if (k == 0 && *a.err) sum = (long long)kFftBad;  // the only term of shell 0
     } else if (p == q) {  // (p, p, r): also (p, r, p), (r, p, p)
         sum += at(p, r, p) + at(r, p, p);
     } else if (q == r) {  // (p, q, q): also (q, p, q), (q, q, p)
@@ -504,8 +589,8 @@ __global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a, int L)
 // over b, at k P + j -- X[k + m j] in an order of its own, which the inverse
 // takes as it is: P-point over j, conjugate twiddle, m-point over k.  m + P
 // complex multiply-adds an element and transform instead of L; the LDS reads
-// of a wave's inputs bound it.  A call against the direct count: L = 72 0.14 ms
-// (0.87), L = 136 0.35 (22), L = 200 0.86 (187), L = 248 1.9 (773).
+// of a wave's inputs bound it.  A call against the direct count: L = 72 0.11 ms
+// (0.87), L = 136 0.23 (22).
 struct FftGeneral {
     int L, m, P, B, LP;  // side = m P; lines per tile; LDS stride of a line
 };
@@ -587,105 +672,80 @@ __device__ __forceinline__ void fft_general_twiddles(double2 *tw, int L, int tid
     }
 }
 
-// Passes kFftFwdBitsX .. kFftInvY (fft_pass_kernel): one tile of B lines per
-// workgroup, the same tiles and order in memory.
+__device__ __forceinline__ int fft_general_place(const FftGeneral &f, int k) { return (k % f.m) * f.P + k / f.m; }
+
+// Pass kFftFwdBitsX (fft_bits_kernel).
+__global__ __launch_bounds__(kFftThreads) void fft_general_bits_kernel(FftArgs a, FftGeneral f)
+{
+    __shared__ double2 s[kFftGeneralLds];
+    __shared__ double2 tw[256];
+    const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
+    const int L = f.L, B = f.B, H1 = L / 2 + 1;
+    fft_clear(a, tid);
+    fft_bits(a, L, B, f.LP, s, tid);
+    fft_general_twiddles(tw, L, tid);
+    fft_general_lines<false>(s, tw, f, B * L, tid);
+    for (int j = tid; j < 2 * B * H1; j += kFftThreads) {
+        const int row = j / H1, k = j - row * H1;
+        const double2 *p = s + (row >> 1) * f.LP;
+        a.z[((size_t)w * 2 * B + (size_t)row) * fft_stride(L) + (size_t)k] =
+            fft_unpack(p[fft_general_place(f, k)], p[fft_general_place(f, k == 0 ? 0 : L - k)], row & 1);
+    }
+}
+
+// Passes kFftFwdY .. kFftInvY (fft_pass_kernel).
 template <int OP>
 __global__ __launch_bounds__(kFftThreads) void fft_general_pass_kernel(FftArgs a, FftGeneral f)
 {
     __shared__ double2 s[kFftGeneralLds];
     __shared__ double2 tw[256];
-    const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
-    const int L = f.L, B = f.B, tile = B * L, xb = L / B;
-    // element j of the tile: line b, index i along the axis, place in memory
-    auto element = [&](int j, int &b, int &i, size_t &pos) {
-        if (OP == kFftFwdBitsX) {
-            b = j / L;
-            i = j - b * L;
-            pos = (size_t)w * tile + (size_t)j;
-        } else {
-            i = j / B;
-            b = j - i * B;
-            const int o = w / xb, x = (w - o * xb) * B + b;
-            pos = OP == kFftSquareZ ? ((size_t)i * L + (size_t)o) * L + (size_t)x
-                                    : ((size_t)o * L + (size_t)i) * L + (size_t)x;
-        }
-    };
+    const int L = f.L, B = f.B, is = kFftThreads / B;
+    const int tid = (int)threadIdx.x, b = tid % B, i0 = tid / B, line = (int)blockIdx.x * B + b;
+    const bool ok = fft_line_ok<OP>(L, line);
+    double2 v[kFftGeneralPer];
+#pragma unroll
+    for (int e = 0; e < kFftGeneralPer; ++e) {
+        const int i = i0 + e * is;
+        v[e] = ok && i < L ? a.z[fft_element<OP>(L, line, i)] : make_double2(0.0, 0.0);
+    }
     fft_general_twiddles(tw, L, tid);
-    for (int j = tid; j < tile; j += kFftThreads) {
-        int b, i;
-        size_t pos;
-        element(j, b, i, pos);
-        double2 v;
-        if constexpr (OP == kFftFwdBitsX) {
-            const size_t row = (size_t)w * B + (size_t)b;
-            const unsigned long long word = a.qd[row * (size_t)a.dw + (size_t)(i >> 6)];
-            v = make_double2((word >> (i & 63)) & 1ull ? -1.0 : 1.0, 0.0);
-        } else {
-            v = a.z[pos];
-        }
-        s[b * f.LP + i] = v;
-    }
+    double2 *p = s + b * f.LP;
+#pragma unroll
+    for (int e = 0; e < kFftGeneralPer; ++e)
+        if (i0 + e * is < L) p[i0 + e * is] = v[e];
     if constexpr (OP == kFftInvY) {
-        fft_general_lines<true>(s, tw, f, tile, tid);
+        fft_general_lines<true>(s, tw, f, B * L, tid);
     } else {
-        fft_general_lines<false>(s, tw, f, tile, tid);
+        fft_general_lines<false>(s, tw, f, B * L, tid);
         if constexpr (OP == kFftSquareZ) {
-            for (int j = tid; j < tile; j += kFftThreads) {
-                double2 *p = s + (j / L) * f.LP + (j % L);
-                const double2 v = *p;
-                *p = make_double2(v.x * v.x + v.y * v.y, 0.0);
-            }
-            fft_general_lines<true>(s, tw, f, tile, tid);
+            for (int i = i0; i < L; i += is) p[i] = make_double2(p[i].x * p[i].x + p[i].y * p[i].y, 0.0);
+            fft_general_lines<true>(s, tw, f, B * L, tid);
         }
     }
-    for (int j = tid; j < tile; j += kFftThreads) {
-        int b, i;
-        size_t pos;
-        element(j, b, i, pos);
-        if (OP == kFftSquareZ && i > L / 2) continue;
-        a.z[pos] = s[b * f.LP + i];
-    }
+    if (!ok) return;
+    for (int i = i0; i < (OP == kFftSquareZ ? L / 2 + 1 : L); i += is) a.z[fft_element<OP>(L, line, i)] = p[i];
 }
 
-// fft_bin_kernel: a workgroup takes kFftBinY values y <= L/2 of one plane z <=
-// L/2 with their mirror rows, transforms them along x and stores the rounded
-// sums T(|x|, |y|, |z|), laid out as fft_sums places them.
+// The last transform pass (fft_bin_kernel).
 __global__ __launch_bounds__(kFftThreads) void fft_general_bin_kernel(FftArgs a, FftGeneral f)
 {
     __shared__ double2 s[kFftGeneralLds];
     __shared__ double2 tw[256];
     const int tid = (int)threadIdx.x, w = (int)blockIdx.x;
-    const int L = f.L, H = L / 2, nl = 2 * kFftBinY, yb = (H + kFftBinY) / kFftBinY;
+    const int L = f.L, H = L / 2, yb = (H + kFftBinY) / kFftBinY;
     const int z = w / yb, y0 = (w - z * yb) * kFftBinY;
-    const double inv_n = (double)L * L * L;
     fft_general_twiddles(tw, L, tid);
-    for (int j = tid; j < nl * L; j += kFftThreads) {
-        const int line = j / L, x = j - line * L, y = y0 + (line >> 1);
-        const bool mirror = (line & 1) != 0;
-        double2 v = make_double2(0.0, 0.0);
-        if (y <= H && (!mirror || (y != 0 && y != H)))
-            v = a.z[((size_t)z * L + (size_t)(mirror ? L - y : y)) * L + (size_t)x];
-        s[line * f.LP + x] = v;
+    for (int j = tid; j < kFftBinY * (H + 1); j += kFftThreads) {
+        const int line = j / (H + 1), k = j - line * (H + 1);
+        double2 zk, zm;
+        fft_pack(a, L, z, y0 + line, k, zk, zm);
+        s[line * f.LP + fft_general_place(f, k)] = zk;
+        if (k > 0 && k < H) s[line * f.LP + fft_general_place(f, L - k)] = zm;
     }
-    fft_general_lines<true>(s, tw, f, nl * L, tid);
-    const long long weight = (z == 0 || z == H) ? 1 : 2;
-    long long *T = reinterpret_cast<long long *>(a.z + (size_t)(H + 1) * L * L);
+    fft_general_lines<true>(s, tw, f, kFftBinY * L, tid);
     for (int t = tid; t < kFftBinY * (H + 1); t += kFftThreads) {
         const int j = t / (H + 1), i = t - j * (H + 1), y = y0 + j;
-        if (y > H) continue;
-        long long sum = 0;
-        bool bad = false;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {  // bit 0: x -> L - x, bit 1: y -> L - y
-            if ((e & 1) && (i == 0 || i == H)) continue;
-            if ((e & 2) && (y == 0 || y == H)) continue;
-            const double v = s[(2 * j + (e >> 1)) * f.LP + ((e & 1) ? L - i : i)].x / inv_n;
-            const double r = rint(v);
-            bad |= !(fabs(v - r) <= 0.25);  // NaN included
-            sum += (long long)r;
-        }
-        if (bad) atomicOr(a.err, 1u);
-        T[((size_t)z * (H + 1) + (size_t)y) * (H + 1) + (size_t)i] = sum * weight;
+        if (y <= H) fft_bin(a, L, s + j * f.LP, i, y, z, (double)L * L * L);
     }
 }
 

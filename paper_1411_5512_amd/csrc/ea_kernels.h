@@ -454,27 +454,41 @@ __global__ __launch_bounds__(kMeasThreads) void measure_kernel(Lattice lat, Geom
 // [L, 2L) repeat them, in dw 64-bit words, so that the row shifted
 // cyclically by rx is the window of L bits starting at bit rx.
 
-// One thread per (row, word of the doubled row).
+// Bits 0 .. 31 of v moved to the even bits of the result.
+__device__ __forceinline__ unsigned long long even_bits(uint32_t v)
+{
+    unsigned long long x = v;
+    x = (x | x << 16) & 0x0000ffff0000ffffull;
+    x = (x | x << 8) & 0x00ff00ff00ff00ffull;
+    x = (x | x << 4) & 0x0f0f0f0f0f0f0f0full;
+    x = (x | x << 2) & 0x3333333333333333ull;
+    return (x | x << 1) & 0x5555555555555555ull;
+}
+
+// One thread per (row, word of the doubled row): the row's 32 sites of each
+// colour from R (j 32 / R) on, taken word by word and then interleaved.  Bound
+// by the launch: 3.2 us at L = 128; one site at a time took 15.
 template <int W>
 __global__ __launch_bounds__(256) void dense_q_kernel(Lattice lat, Geom g, int dw, unsigned long long *qd)
 {
     const int gid = blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= g.rows * dw) return;
-    const int row = gid / dw;
-    const int j = gid - row * dw;
-    const int y = row % g.L;
-    const int z = row / g.L;
+    const int row = gid / dw, j = gid - row * dw, z = row / g.L, y = row - z * g.L;
+    const int c0 = (y + z) & 1;  // colour of the even x
+    const int n = min(32, g.L - 32 * j);  // sites of either colour; the doubled row has L
     unsigned long long bits = 0;
-    for (int b = 0; b < 64; ++b) {
-        const int gbit = 64 * j + b;
-        if (gbit >= 2 * g.L) break;
-        const int x = gbit % g.L;
-        const int c = (x + y + z) & 1;
-        const int xh = x >> 1;
-        const size_t word = (size_t)row * g.RW + (size_t)(xh / W);
-        const int bit = xh % W;
-        const uint32_t s0 = lat.spins[plane_off(g, 0, c) + word], s1 = lat.spins[plane_off(g, 1, c) + word];
-        bits |= (unsigned long long)(((s0 ^ s1) >> bit) & 1u) << b;
+#pragma unroll
+    for (int odd = 0; odd < 2; ++odd) {
+        const size_t base = plane_off(g, 0, c0 ^ odd) + (size_t)row * g.RW;
+        const size_t to_s1 = plane_off(g, 1, 0) - plane_off(g, 0, 0);
+        uint32_t v = 0;
+        for (int i = 0; i < n;) {
+            const int h = (32 * j + i) % g.R, w = h / W, off = h - w * W, take = min(W - off, n - i);
+            const uint32_t q = lat.spins[base + w] ^ lat.spins[base + to_s1 + w];
+            v |= ((q >> off) & (0xffffffffu >> (32 - take))) << i;
+            i += take;
+        }
+        bits |= even_bits(v) << odd;
     }
     qd[gid] = bits;
 }

@@ -15,13 +15,12 @@ ea_status shells_to_host(const unsigned long long *qd, int dw, unsigned long lon
                        : launch_shell_rows(qd, L, n_shells, shells, stream);
     if (st != EA_OK) return st;
     EA_HIP(hipMemcpyAsync(out, shells, 8 * (size_t)n_shells, hipMemcpyDeviceToHost, stream));
-    if (fft) return fft_shells_check(fft_work, L, stream);
     EA_HIP(hipStreamSynchronize(stream));
-    return EA_OK;
+    return fft ? fft_shells_check(out, L) : EA_OK;
 }
 
 // The call's scratch in the handle's buffer: the dense rows, the shells and
-// (FFT route) the complex array; the shells zeroed on `stream`.
+// (FFT route) the complex array; without it the shells zeroed on `stream`.
 ea_status shell_scratch(ShellScratch &sc, int L, int n_shells, unsigned long long **qd, unsigned long long **shells,
                         void **fft_work, int *dw, hipStream_t stream)
 {
@@ -41,9 +40,11 @@ ea_status shell_scratch(ShellScratch &sc, int L, int n_shells, unsigned long lon
     *qd = base;
     *shells = base + q_words;
     *fft_work = fft_bytes ? (void *)((char *)sc.p + head) : nullptr;
-    hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for((size_t)n_shells)), dim3(256), 0, stream, *shells,
-                       (size_t)n_shells);
-    EA_HIP(hipGetLastError());
+    if (!fft_bytes) {  // the FFT's first pass clears them itself
+        hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for((size_t)n_shells)), dim3(256), 0, stream, *shells,
+                           (size_t)n_shells);
+        EA_HIP(hipGetLastError());
+    }
     return EA_OK;
 }
 
