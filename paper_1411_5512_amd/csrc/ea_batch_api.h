@@ -143,7 +143,7 @@ ea_status plan_job(const ea_job &in, int index, BatchJobHost &h, const TuneCfg *
     h.off_tnow = off;
     off += 8;
     h.off_pub = off = align256(off);
-    off += 8 * 4;
+    off += 8 * ea::kBatchPubs;
     h.off_xbuf = off = align256(off);
     off += 4 * 32 * (size_t)in.L * (size_t)h.RW;
     h.off_meas_t = off = align256(off);
@@ -239,7 +239,7 @@ ea_status init_job_device(BatchJobHost &h, hipStream_t stream)
     hipLaunchKernelGGL(ea::zero_u32_kernel, dim3(blocks_for(n_ctl32)), dim3(256), 0, stream,
                        (uint32_t *)(h.base + h.off_arrive), n_ctl32);
     hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(1), dim3(256), 0, stream,
-                       (unsigned long long *)(h.base + h.off_pub), (size_t)4);
+                       (unsigned long long *)(h.base + h.off_pub), (size_t)ea::kBatchPubs);
     EA_HIP(hipGetLastError());
     h.t_host = 0;
     h.started = false;
@@ -380,20 +380,19 @@ void debug_order_units(const JobRef *jobs, std::vector<ea::BatchUnit> &units)
 // with the shortest estimated makespan is kept.  Time model per half-step
 // (measured on MI355X): a whole replica takes kHalfStepL64 (L/64)^kSizeExp
 // (smaller lattices use a CU less fully than the site count alone says); a
-// slab takes half of that plus kSlabExchange, but at least kSlabFloor, the
-// latency of the boundary exchange (wait, remote reads, publication).  Only
-// jobs in their default launch configuration (the slab kernel exists for
-// that one) split.
-constexpr double kHalfStepL64 = 12.6e-6;
-constexpr double kSizeExp = 2.57;  // L = 48 measured at 0.478 of L = 64
-constexpr double kSlabExchange = 0.4e-6;
-constexpr double kSlabFloor = 4.5e-6;
+// slab takes half of that plus kSlabExchange for the boundary exchange (wait,
+// remote reads, publication): whole / slab 4.5 / 2.97 us at L = 48, 8.2 / 4.07 at
+// 56, 9.2 / 5.38 at 64.  Only jobs in their default launch configuration (the
+// slab kernel exists for that one) split.
+constexpr double kHalfStepL64 = 9.2e-6;
+constexpr double kSizeExp = 2.5;  // L = 48 measured at 0.49 of L = 64
+constexpr double kSlabExchange = 0.75e-6;
 
 double unit_seconds(const BatchJobHost &h, bool slab)
 {
     const double x = (double)h.job.L / 64.0;
     const double whole = kHalfStepL64 * std::pow(x, kSizeExp);
-    const double per_half = slab ? std::max(0.5 * whole + kSlabExchange, kSlabFloor) : whole;
+    const double per_half = slab ? 0.5 * whole + kSlabExchange : whole;
     return 2.0 * (double)std::max<uint64_t>(1, h.job.n_sweeps) * per_half;
 }
 
@@ -429,7 +428,7 @@ void choose_split(std::vector<BatchJobHost> &jobs, int n_cu, bool always)
     auto splittable = [](const BatchJobHost &h) {
         const TuneCfg d = default_cfg(h.job.L);
         return h.job.L >= ea::kSplitMinL && h.cfg.rw == d.rw && h.cfg.nt == d.nt && h.cfg.sel == ea::SEL_LDS &&
-               h.cfg.nt >= 128;
+               h.cfg.nt >= 192;
     };
     int best_lmin = 0;
     double best = 0.0;

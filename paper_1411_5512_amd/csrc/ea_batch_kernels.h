@@ -53,6 +53,8 @@ struct Shape {
 // bit-field selects.
 enum : int { SEL_LDS = 0, SEL_REG = 1 };
 
+constexpr int kBatchPubs = 8;  // publication counters of a split job: [replica][slab][face]
+
 // Device-side description of one sample in a batch.
 struct BatchJobDev {
     int32_t L;
@@ -74,7 +76,7 @@ struct BatchJobDev {
     uint32_t *t_now;          // [2] sweeps done per replica
     int32_t parts;            // workgroups per replica: 1, or 2 for a replica split into z-slabs
     uint32_t *xbuf;           // split: [replica][slab][sweep parity][colour][first/last plane][L * rw]
-    unsigned long long *pub;  // split: [replica][slab] boundary publications (see batch_run_split)
+    unsigned long long *pub;  // split: [replica][slab][face] publications (slab_pub)
     uint32_t *err;            // set when a split pair gave up waiting for its partner
 };
 
@@ -610,13 +612,13 @@ __device__ __forceinline__ void store_agent(uint32_t *p, uint32_t v)
 __device__ __forceinline__ void slab_publish_words(unsigned long long *pub, unsigned long long value)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (threadIdx.x == 0) __hip_atomic_store(pub, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(pub, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ bool slab_wait_words(unsigned long long *pub, unsigned long long want)
 {
     int ok = 1;
-    if (threadIdx.x == 0) {
+    if ((threadIdx.x & 63) == 0) {
         const unsigned long long start = __builtin_amdgcn_s_memrealtime();
         while (__hip_atomic_load(pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want) {
             __builtin_amdgcn_s_sleep(1);
@@ -673,8 +675,20 @@ __device__ __forceinline__ uint32_t slab_new_word(const BatchJobDev &J, const Ph
     return S0 ^ flips;
 }
 
-// Half-step (t, colour c) of one slab.  Returns false (wave 0 only) if the
-// partner never published.
+// Publication counter of one face (0 the first plane, 1 the last) of a slab.
+__device__ __forceinline__ unsigned long long *slab_pub(const BatchJobDev &J, int r, int slab, int face)
+{
+    return J.pub + 2 * (2 * r + slab) + face;
+}
+
+// Half-step (t, colour c) of one slab.  Returns false (in a boundary wave
+// only) if the partner never published.  Waves 0 and 1 take one boundary plane
+// each, which waits only for the partner's plane next to it, and the others
+// take the interior; where that would leave a few words of the interior to
+// another round (L = 64: 30 planes on 14 waves), wave 0 takes both planes in
+// turn and 15 waves the interior.  Bound by the boundary's chain: wait, load,
+// a word, publish.  Per half-step, with one wave for both planes and now: L = 48
+// 4.45 us, 2.97; L = 56 4.82, 4.07; L = 64 5.23, 5.38.
 template <int L, int RW, int SEL>
 __device__ __forceinline__ bool slab_half_step(const BatchJobDev &J, int r, int slab, int c, uint32_t t,
                                                unsigned long long want, unsigned long long done)
@@ -687,36 +701,35 @@ __device__ __forceinline__ bool slab_half_step(const BatchJobDev &J, int r, int 
     int tid = (int)threadIdx.x;
     asm volatile("" : "+v"(tid));
     const PhiloxStep<true> step = philox_step(t, counter_word2(TAG_METRO, (uint32_t)c, (uint32_t)r), J.sample, J.k0, J.k1);
-    if (tid >= 64) {
-        // interior planes 1 .. NZ-2
+    constexpr int N = S::SPOS - 2 * S::PL;  // words of the interior planes 1 .. NZ-2
+    const int rest = N % (J.nt - 128), bw = rest > 0 && rest <= 128 ? 1 : 2;
+    if (tid >= 64 * bw) {
 #pragma unroll 1
-        for (int p = S::PL + tid - 64; p < S::SPOS - S::PL; p += J.nt - 64)
+        for (int p = S::PL + tid - 64 * bw; p < S::SPOS - S::PL; p += J.nt - 64 * bw)
             own[p] = slab_new_word<L, RW, SEL>(J, step, c, z0, p, oth[p - S::PL], oth[p + S::PL], bz_oth[p - S::PL]);
         return true;
     }
-    if (!slab_wait_words(J.pub + 2 * r + (slab ^ 1), want)) return false;
     // colour c ^ 1 was last written in the previous half-step: this sweep's
     // first half-step, or the previous sweep's second
     const int rslot = (int)((c == r ? t + 1 : t) & 1u);
     const int wslot = (int)(t & 1u);
-    const uint32_t *part_last = slab_xbuf<S>(J, r, slab ^ 1, rslot, c ^ 1, 1);   // the plane below this slab
-    const uint32_t *part_first = slab_xbuf<S>(J, r, slab ^ 1, rslot, c ^ 1, 0);  // the plane above it
     const uint32_t *halo_bz = batch_lds + S::HALO + (c ^ 1) * S::PL;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll 1
-    for (int i = tid; i < 2 * S::PL; i += 64) {
-        const int k = i >= S::PL ? 1 : 0;
-        const int j = i - k * S::PL;
-        const int p = k ? S::SPOS - S::PL + j : j;
-        uint32_t v;
-        if (k == 0)
-            v = slab_new_word<L, RW, SEL>(J, step, c, z0, p, load_agent(part_last + j), oth[p + S::PL], halo_bz[j]);
-        else
-            v = slab_new_word<L, RW, SEL>(J, step, c, z0, p, oth[p - S::PL], load_agent(part_first + j),
-                                          bz_oth[p - S::PL]);
-        own[p] = v;
-        store_agent(slab_xbuf<S>(J, r, slab, wslot, c, k) + j, v);
+    for (int k = wave; k < 2; k += bw) {  // the wave's face or both in turn
+        if (!slab_wait_words(slab_pub(J, r, slab ^ 1, k ^ 1), want)) return false;
+        const uint32_t *beyond = slab_xbuf<S>(J, r, slab ^ 1, rslot, c ^ 1, k ^ 1);  // the partner's plane next to it
+#pragma unroll 1
+        for (int j = tid & 63; j < S::PL; j += 64) {
+            const int p = k ? S::SPOS - S::PL + j : j;
+            const uint32_t z_out = load_agent(beyond + j), z_in = oth[k ? p - S::PL : p + S::PL];
+            const uint32_t bz = k ? bz_oth[p - S::PL] : halo_bz[j];
+            const uint32_t v = slab_new_word<L, RW, SEL>(J, step, c, z0, p, k ? z_in : z_out, k ? z_out : z_in, bz);
+            own[p] = v;
+            store_agent(slab_xbuf<S>(J, r, slab, wslot, c, k) + j, v);
+        }
+        slab_publish_words(slab_pub(J, r, slab, k), done);
     }
-    slab_publish_words(J.pub + 2 * r + slab, done);
     return true;
 }
 
@@ -815,7 +828,6 @@ __device__ void batch_run_slab(const BatchJobDev &J, int r, int slab, uint32_t t
     uint32_t *abort_flag = batch_lds + S::FLAG + 1;
     if (threadIdx.x == 0) *abort_flag = 0;
     __syncthreads();
-    unsigned long long *my_pub = J.pub + 2 * r + slab;
     if (first && threadIdx.x < 64) {
         // the state at t = 0 of both colours' boundary planes
         for (int c = 0; c < 2; ++c)
@@ -824,7 +836,7 @@ __device__ void batch_run_slab(const BatchJobDev &J, int r, int slab, uint32_t t
                 const int j = i - k * S::PL;
                 slab_xbuf<S>(J, r, slab, 1, c, k)[j] = batch_lds[c * S::SPOS + (k ? S::SPOS - S::PL : 0) + j];
             }
-        slab_publish(my_pub, 1ull);
+        for (int k = 0; k < 2; ++k) slab_publish(slab_pub(J, r, slab, k), 1ull);
     }
 
     int im = 0, iw = 0;
@@ -840,7 +852,7 @@ __device__ void batch_run_slab(const BatchJobDev &J, int r, int slab, uint32_t t
             __syncthreads();
         }
         if (im < J.n_meas && J.meas_t[im] == t) {
-            if (threadIdx.x < 64 && !slab_wait(J.pub + 2 * r + (slab ^ 1), 2ull * t + 1)) {
+            if (threadIdx.x < 64 && !slab_wait(slab_pub(J, r, slab ^ 1, 0), 2ull * t + 1)) {
                 if (threadIdx.x == 0) {
                     *abort_flag = 1;
                     atomicOr(J.err, 1u);
@@ -856,7 +868,7 @@ __device__ void batch_run_slab(const BatchJobDev &J, int r, int slab, uint32_t t
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             const unsigned long long want = 2ull * t + (unsigned)h + 1, done = want + 1;
-            if (!slab_half_step<L, RW, SEL>(J, r, slab, r ^ h, t, want, done) && threadIdx.x == 0) {
+            if (!slab_half_step<L, RW, SEL>(J, r, slab, r ^ h, t, want, done) && (threadIdx.x & 63) == 0) {
                 *abort_flag = 1;
                 atomicOr(J.err, 1u);
             }
@@ -937,7 +949,7 @@ __global__ __launch_bounds__(256) void batch_reset_kernel(const BatchJobDev *__r
     if (plane == 0) {
         // arrive[n_meas] and t_now[2] are contiguous
         for (int i = at; i < J.n_meas + 2; i += step) J.arrive[i] = 0u;
-        if (at < 4) J.pub[at] = 0ull;
+        if (at < kBatchPubs) J.pub[at] = 0ull;
         if (blockIdx.x == 0 && at == 0) *err = 0u;
     }
     if (at >= POS) return;
