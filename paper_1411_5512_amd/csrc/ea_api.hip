@@ -331,6 +331,7 @@ struct ea_sim {
     unsigned long long *meas = nullptr;
     uint32_t *t_dev = nullptr;  // device copy of the sweep counter base
     std::vector<unsigned long long> host_meas, meas_before;  // the counters now and at the measurement before
+    bool meas_known = false;  // meas_before holds what the device counters hold
     char *slot = nullptr;     // pinned staging (pinned_slots), or null
     bool slot_asked = false;
     // captured graph of kGraphSweeps sweeps (built on first use)
@@ -414,9 +415,12 @@ ea_status launch_init_lattice(const ea::Lattice &lat, const ea::Geom &g, int W, 
 // Initial state, error word and measurement counters.
 ea_status launch_init(ea_sim *s)
 {
+    s->meas_known = false;
     std::fill(s->meas_before.begin(), s->meas_before.end(), 0);
-    return launch_init_lattice(s->lat, s->geom(), s->lay.W, s->seed, s->sample, s->pcut, s->stream, s->err_dev,
-                               s->meas, (int)s->lay.meas_count);
+    ea_status st = launch_init_lattice(s->lat, s->geom(), s->lay.W, s->seed, s->sample, s->pcut, s->stream, s->err_dev,
+                                       s->meas, (int)s->lay.meas_count);
+    s->meas_known = st == EA_OK;
+    return st;
 }
 
 // Half-step launches with at least this many threads (four waves per SIMD
@@ -1352,6 +1356,11 @@ ea_status ea_measure(ea_sim *s, ea_obs *out)
     const int slots = out->autocorr ? s->n_slots : 0;
     const int nb = (int)std::min<unsigned>(blocks_for(2 * (size_t)g.plane, ea::kMeasThreads), ea::kMeasBlocks);
     const dim3 grid((unsigned)(nb * (1 + slots) + (out->c4 ? 3 * y.L : 0)));
+    if (!s->meas_known) {  // an earlier call failed between its launch and its copy
+        hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for(n_count)), dim3(256), 0, s->stream, s->meas, n_count);
+        std::fill(s->meas_before.begin(), s->meas_before.end(), 0);
+    }
+    s->meas_known = false;
     EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::measure_kernel<WW>), grid, dim3(ea::kMeasThreads), 0, s->stream,
                                            s->lat, g, s->snaps, nb, slots, s->meas, (int)c4_base, s->err_dev));
     EA_HIP(hipGetLastError());
@@ -1367,6 +1376,7 @@ ea_status ea_measure(ea_sim *s, ea_obs *out)
         s->host_meas[i] = now - s->meas_before[i];
         s->meas_before[i] = now;
     }
+    s->meas_known = true;
     if (gave_up) return slab_gave_up();
 
     const int64_t N = (int64_t)y.L * y.L * y.L;
