@@ -43,6 +43,19 @@ ea_status fail(ea_status st, const char *fmt, ...)
             return fail(EA_ERR_DEVICE, "%s failed: %s", #call, hipGetErrorString(e_)); \
     } while (0)
 
+// hipMalloc; a failure is the caller's to report, and must not stay pending on
+// the thread, where the next launch's check would find it.
+template <class P>
+hipError_t device_alloc(P **p, size_t bytes)
+{
+    const hipError_t e = hipMalloc((void **)p, bytes);
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+    }
+    return e;
+}
+
 constexpr int kMaxSlots = 64;
 constexpr int kMaxL = 256;
 
@@ -883,11 +896,9 @@ struct ShellScratch {
         if (p) (void)hipFree(p);
         p = nullptr;
         bytes = 0;
-        const hipError_t e = hipMalloc(&p, n);
-        if (e != hipSuccess) {
-            p = nullptr;
+        const hipError_t e = device_alloc(&p, n);
+        if (e != hipSuccess)
             return fail(EA_ERR_NOMEM, "hipMalloc(C4 shell scratch, %zu bytes): %s", n, hipGetErrorString(e));
-        }
         bytes = n;
         return EA_OK;
     }
@@ -1140,7 +1151,7 @@ ea_status ea_create_ex(const ea_config *cfg, ea_sim **out)
     if (cfg->dev_buf) {
         s->buf = (char *)cfg->dev_buf;
     } else {
-        e = hipMalloc((void **)&s->buf, lay.total);
+        e = device_alloc(&s->buf, lay.total);
         if (e != hipSuccess) {
             ea_destroy(s);
             return fail(EA_ERR_NOMEM, "hipMalloc(%zu): %s", lay.total, hipGetErrorString(e));
@@ -1412,11 +1423,8 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
     const int dw = 2 * nw;
     const size_t q_words = (size_t)L * L * dw;
     if (!s->c4_scratch) {
-        hipError_t e = hipMalloc((void **)&s->c4_scratch, 8 * (q_words + (size_t)max_shells));
-        if (e != hipSuccess) {
-            s->c4_scratch = nullptr;
-            return fail(EA_ERR_NOMEM, "hipMalloc(c4 scratch): %s", hipGetErrorString(e));
-        }
+        hipError_t e = device_alloc(&s->c4_scratch, 8 * (q_words + (size_t)max_shells));
+        if (e != hipSuccess) return fail(EA_ERR_NOMEM, "hipMalloc(c4 scratch): %s", hipGetErrorString(e));
     }
     unsigned long long *qd = s->c4_scratch, *shells = s->c4_scratch + q_words;
     ea::Geom g = s->geom();
@@ -1424,13 +1432,11 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
                                                s->stream, s->lat, g, dw, qd));
     bool fft = shells_by_fft(L);
     if (fft && !s->fft_work) {
-        hipError_t e = hipMalloc(&s->fft_work, fft_work_bytes(L));
+        hipError_t e = device_alloc(&s->fft_work, fft_work_bytes(L));
         if (e != hipSuccess) {
-            s->fft_work = nullptr;
             if (!ea::fft_general_side(L))
                 return fail(EA_ERR_NOMEM, "hipMalloc(c4 FFT work, %zu bytes): %s", fft_work_bytes(L),
                             hipGetErrorString(e));
-            (void)hipGetLastError();
             fft = false;  // sides that once had only the direct route keep it where memory is short
         }
     }
@@ -1716,11 +1722,9 @@ ea_status io_buffer(ea_sim *s, char **buf, size_t *bytes)
     }
     *bytes = (size_t)s->lay.L * s->lay.L * s->lay.L;
     if (!s->io) {
-        const hipError_t e = hipMalloc(&s->io, *bytes);
-        if (e != hipSuccess) {
-            s->io = nullptr;
+        const hipError_t e = device_alloc(&s->io, *bytes);
+        if (e != hipSuccess)
             return fail(EA_ERR_NOMEM, "hipMalloc(conversion buffer, %zu bytes): %s", *bytes, hipGetErrorString(e));
-        }
     }
     *buf = (char *)s->io;
     return EA_OK;

@@ -751,7 +751,7 @@ ea_status batch_create_cfg(const ea_job *jobs, int32_t n_jobs, void *stream, con
         }
         b->own_stream = true;
     }
-    e = hipMalloc((void **)&b->buf, b->bytes);
+    e = device_alloc(&b->buf, b->bytes);
     if (e != hipSuccess) {
         ea_batch_destroy(b);
         return fail(EA_ERR_NOMEM, "hipMalloc(%zu): %s", b->bytes, hipGetErrorString(e));

@@ -266,7 +266,7 @@ ea_status ea_msc_create(const ea_msc_config *cfg, ea_msc **out)
     if (cfg->dev_buf) {
         s->buf = (char *)cfg->dev_buf;
     } else {
-        e = hipMalloc((void **)&s->buf, y.total);
+        e = device_alloc(&s->buf, y.total);
         if (e != hipSuccess) {
             ea_msc_destroy(s);
             return fail(EA_ERR_NOMEM, "hipMalloc(%zu): %s", y.total, hipGetErrorString(e));

@@ -710,7 +710,7 @@ ea_status ea_server_create(const ea_server_opts *opts, ea_server **out)
     }
     const size_t table_bytes = align256(sizeof(ea::BatchJobDev) * (size_t)opts->max_resident) +
                                align256(sizeof(ea::BatchUnit) * 2 * (size_t)opts->max_resident);
-    e = hipMalloc((void **)&s->pool_buf, align256(opts->hbm_budget) + table_bytes);
+    e = device_alloc(&s->pool_buf, align256(opts->hbm_budget) + table_bytes);
     if (e != hipSuccess) {
         ea_server_destroy(s);
         return fail(EA_ERR_NOMEM, "hipMalloc(%zu): %s", opts->hbm_budget, hipGetErrorString(e));

@@ -31,7 +31,6 @@ ea_status shell_scratch(ShellScratch &sc, int L, int n_shells, unsigned long lon
     ea_status st = sc.reserve(head + fft_bytes);
     if (st != EA_OK && fft_bytes && ea::fft_general_side(L)) {
         // sides that once had only the direct route keep it where memory is short
-        (void)hipGetLastError();
         fft_bytes = 0;
         st = sc.reserve(head);
     }

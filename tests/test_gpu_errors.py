@@ -41,3 +41,15 @@ def test_measurement_after_one_that_failed(ea_gpu, L):
     s.sweep(7)
     _same(s.measure(), want)
     s.close()
+
+
+def test_allocation_failure_does_not_stay_pending(ea_gpu):
+    """A call that reports EA_ERR_NOMEM leaves no error for the next one."""
+    s = ea_gpu.Sim(16, 0.4, 0.8, seed=1)
+    want = s.measure()
+    with pytest.raises(ea_gpu.abi.EAError):
+        ea_gpu.Server(hbm_budget=1 << 58)
+    _same(s.measure(), want)
+    s.sweep(1)
+    s.sync()
+    s.close()
