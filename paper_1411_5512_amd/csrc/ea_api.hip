@@ -671,61 +671,96 @@ ea_status slab_plan_of(const ea_sim *s, int n_runs, SlabPlan *plan)
 
 // Launches whose workgroups wait for each other must not share the device with
 // another such launch unless both fit at once: two that are each resident in
-// part would wait until they give up.  Streams that may have one in flight
-// are listed with the workgroups it needs; a launch that does not fit beside
-// the others waits, on its stream, for them.  The caller holds g_flight_mu
-// from here until its launch is enqueued.
+// part would wait until they give up.  Every stream that has had one is listed
+// with an event recorded directly behind its last, so that a launch waits for
+// launches only, never for what a caller queued after them, and nothing is
+// asked of a stream that someone may be capturing.
 struct Flight {
     hipStream_t stream;
-    int device, blocks;
+    int device, blocks;  // workgroups of the launches in flight there, 0 once they are known to be over
+    hipEvent_t done;
 };
 std::mutex g_flight_mu;
 std::vector<Flight> g_flights;
 
-bool flight_over(const Flight &f)
+bool flight_over(Flight &f)
 {
-    const bool over = hipStreamQuery(f.stream) != hipErrorNotReady;
-    (void)hipGetLastError();
-    return over;
+    if (f.blocks && hipEventQuery(f.done) == hipSuccess) f.blocks = 0;
+    (void)hipGetLastError();  // not ready
+    return f.blocks == 0;
 }
 
-// ev: an event of the caller's handle, created if it is needed.
-ea_status admit_flight(hipStream_t stream, int device, int blocks, int n_cu, hipEvent_t *ev)
-{
-    int others = 0;
-    Flight *own = nullptr;
-    for (Flight &f : g_flights) {
-        if (f.device != device) continue;
-        if (f.stream == stream) own = &f;
-        else others += f.blocks;
+// Held while such a launch of `blocks` workgroups is enqueued on `stream`: the
+// launch is made to wait, on its stream, for the others if it does not fit
+// beside them, and is listed when this ends.  blocks = 0: nothing to do.  A
+// launch that is being captured runs at replays, out of reach: neither.
+class FlightLaunch {
+public:
+    FlightLaunch(hipStream_t stream, int device, int blocks, int n_cu) : stream_(stream), blocks_(blocks)
+    {
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (blocks && hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
+        if (!blocks || capturing != hipStreamCaptureStatusNone) return;
+        lk_ = std::unique_lock<std::mutex>(g_flight_mu);
+        st_ = admit(device, n_cu);
     }
-    if (own) own->blocks = blocks >= own->blocks || flight_over(*own) ? blocks : own->blocks;
-    if (others + blocks > n_cu) {
-        for (size_t i = 0; i < g_flights.size();) {
-            const Flight f = g_flights[i];
-            if (f.device != device || f.stream == stream) {
-                ++i;
-            } else if (flight_over(f)) {
-                g_flights.erase(g_flights.begin() + (long)i);
-            } else {
-                if (!*ev) EA_HIP(hipEventCreateWithFlags(ev, hipEventDisableTiming));
-                EA_HIP(hipEventRecord(*ev, f.stream));
-                EA_HIP(hipStreamWaitEvent(stream, *ev, 0));
-                ++i;
-            }
+    FlightLaunch(const FlightLaunch &) = delete;
+    FlightLaunch &operator=(const FlightLaunch &) = delete;
+    ~FlightLaunch()
+    {
+        if (!listed_) return;
+        Flight &f = g_flights[at_];
+        f.blocks = std::max(f.blocks, blocks_);
+        (void)hipEventRecord(f.done, stream_);
+    }
+    ea_status status() const { return st_; }
+
+private:
+    ea_status admit(int device, int n_cu)
+    {
+        int others = 0;
+        at_ = g_flights.size();
+        for (size_t i = 0; i < g_flights.size(); ++i) {
+            if (g_flights[i].device != device) continue;
+            if (g_flights[i].stream == stream_) at_ = i;
+            else others += g_flights[i].blocks;
         }
+        if (others + blocks_ > n_cu)
+            for (Flight &f : g_flights)
+                if (f.device == device && f.stream != stream_ && !flight_over(f))
+                    EA_HIP(hipStreamWaitEvent(stream_, f.done, 0));
+        if (at_ == g_flights.size()) {
+            Flight f{stream_, device, 0, nullptr};
+            EA_HIP(hipEventCreateWithFlags(&f.done, hipEventDisableTiming));
+            g_flights.push_back(f);
+        } else if (g_flights[at_].blocks > blocks_) {
+            (void)flight_over(g_flights[at_]);
+        }
+        listed_ = true;
+        return EA_OK;
     }
-    if (!own) g_flights.push_back(Flight{stream, device, blocks});
-    return EA_OK;
-}
 
-// Before a stream is destroyed (and after it has been waited for).
+    hipStream_t stream_;
+    int blocks_;
+    size_t at_ = 0;
+    bool listed_ = false;
+    ea_status st_ = EA_OK;
+    std::unique_lock<std::mutex> lk_;
+};
+
+// Before a handle's stream may go away, and after it has been waited for.  What
+// another handle has in flight on the same stream by now stays listed.
 void forget_flights(hipStream_t stream)
 {
     std::lock_guard<std::mutex> lk(g_flight_mu);
-    g_flights.erase(std::remove_if(g_flights.begin(), g_flights.end(),
-                                   [stream](const Flight &f) { return f.stream == stream; }),
-                    g_flights.end());
+    for (size_t i = 0; i < g_flights.size();) {
+        if (g_flights[i].stream != stream || !flight_over(g_flights[i])) {
+            ++i;
+            continue;
+        }
+        (void)hipEventDestroy(g_flights[i].done);
+        g_flights.erase(g_flights.begin() + (long)i);
+    }
 }
 
 ea_status group_event(ea_sim *s)
@@ -740,9 +775,8 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
 {
     ea_sim *lead = runs[0];
     const Layout &y = lead->lay;
-    std::lock_guard<std::mutex> flight(g_flight_mu);
-    ea_status st = admit_flight(lead->stream, lead->device, plan.B, g_slab_cus, &lead->group_event);
-    if (st != EA_OK) return st;
+    FlightLaunch flight(lead->stream, lead->device, plan.B, g_slab_cus);
+    if (flight.status() != EA_OK) return flight.status();
     for (int i = 0; i < n; ++i) {
         ea_sim *m = runs[i];
         if (!m->xbuf_clean) {  // entries of no earlier epoch

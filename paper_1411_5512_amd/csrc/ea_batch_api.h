@@ -480,8 +480,8 @@ struct ea_batch {
     uint32_t *d_err = nullptr;                // set by a split pair that gave up waiting
     std::vector<ea::BatchUnit> units;
     int device = 0;                       // the device current at ea_batch_create
-    int split_units = 0;                  // units of split replicas, which wait for each other (admit_flight)
-    hipEvent_t flight_event = nullptr;
+    int n_cu = 0;                         // its compute units
+    int split_units = 0;                  // units of split replicas, which wait for each other (FlightLaunch)
     size_t lds_bytes = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
@@ -785,6 +785,7 @@ ea_status batch_create_cfg(const ea_job *jobs, int32_t n_jobs, void *stream, con
     }
     order_units(ptrs, span, b->units);
     (void)hipGetDevice(&b->device);
+    (void)hipDeviceGetAttribute(&b->n_cu, hipDeviceAttributeMultiprocessorCount, b->device);
     for (const ea::BatchUnit &u : b->units) b->split_units += b->jobs[(size_t)u.job].parts == 2 ? 1 : 0;
     st = ea_batch_reset(b);
     if (st != EA_OK) {
@@ -811,23 +812,6 @@ ea_status reset_batch_device(ea_batch *b)
     EA_HIP(hipGetLastError());
     return EA_OK;
 }
-
-// Held while a launch with split replicas is enqueued (admit_flight).
-struct BatchFlight {
-    std::unique_lock<std::mutex> lk;
-    ea_status st = EA_OK;
-    explicit BatchFlight(ea_batch *b)
-    {
-        if (!b->split_units) return;
-        int n_cu = 0;
-        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess) {
-            st = fail(EA_ERR_DEVICE, "hipDeviceGetAttribute failed");
-            return;
-        }
-        lk = std::unique_lock<std::mutex>(g_flight_mu);
-        st = admit_flight(b->stream, b->device, b->split_units, n_cu, &b->flight_event);
-    }
-};
 
 // After a synchronised run: did a split pair give up waiting?
 ea_status check_batch_err(ea_batch *b)
@@ -909,7 +893,6 @@ void ea_batch_destroy(ea_batch *b)
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->split_units) forget_flights(b->stream);
-    if (b->flight_event) (void)hipEventDestroy(b->flight_event);
     if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->buf) (void)hipFree(b->buf);
@@ -940,8 +923,8 @@ ea_status ea_batch_run(ea_batch *b, uint64_t t_stop)
     EA_HIP(hipMemcpyAsync(b->d_units, launch.data(), sizeof(ea::BatchUnit) * launch.size(),
                           hipMemcpyHostToDevice, b->stream));
     {
-        BatchFlight flight(b);
-        if (flight.st != EA_OK) return flight.st;
+        FlightLaunch flight(b->stream, b->device, b->split_units, b->n_cu);
+        if (flight.status() != EA_OK) return flight.status();
         hipLaunchKernelGGL(ea::batch_kernel, dim3((unsigned)launch.size()), dim3(ea::kBatchThreads), b->lds_bytes,
                            b->stream, b->d_jobs, b->d_units, debug_poison_word(), (int)(b->lds_bytes / 4));
         EA_HIP(hipGetLastError());
@@ -996,8 +979,8 @@ ea_status ea_batch_replay(ea_batch *b)
     if (!b) return fail(EA_ERR_ARG, "batch is NULL");
     if (!b->graph_exec) return fail(EA_ERR_STATE, "ea_batch_capture first");
     {
-        BatchFlight flight(b);
-        if (flight.st != EA_OK) return flight.st;
+        FlightLaunch flight(b->stream, b->device, b->split_units, b->n_cu);
+        if (flight.status() != EA_OK) return flight.status();
         EA_HIP(hipGraphLaunch(b->graph_exec, b->stream));
     }
     EA_HIP(hipStreamSynchronize(b->stream));
