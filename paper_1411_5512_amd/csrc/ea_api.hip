@@ -7,6 +7,8 @@
 #include "ea_shells.h"
 #include "ea_fft.h"
 
+#include <hip/hip_ext.h>
+
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -672,14 +674,18 @@ ea_status slab_plan_of(const ea_sim *s, int n_runs, SlabPlan *plan)
 // Launches whose workgroups wait for each other must not share the device with
 // another such launch unless both fit at once: two that are each resident in
 // part would wait until they give up.  Every stream that has had one is listed
-// with an event recorded directly behind its last, so that a launch waits for
-// launches only, never for what a caller queued after them, and nothing is
-// asked of a stream that someone may be capturing.
+// with an event that its last one carries, so that a launch waits for launches
+// only, never for what a caller queued after them, and nothing is asked of a
+// stream that someone may be capturing.  The event costs a run of L = 16 with
+// one sweep, one measurement and its spins read (65 us) 0.6 us carried by the
+// launch and without a system-scope fence, 1.6 us recorded behind it, 3.5 us
+// recorded with the fence.
 struct Flight {
-    hipStream_t stream;
+    hipStream_t stream;  // null: free for the next stream
     int device, blocks;  // workgroups of the launches in flight there, 0 once they are known to be over
     hipEvent_t done;
 };
+constexpr size_t kFreeFlights = 16;  // at most, kept for their events
 std::mutex g_flight_mu;
 std::vector<Flight> g_flights;
 
@@ -711,7 +717,13 @@ public:
         if (!listed_) return;
         Flight &f = g_flights[at_];
         f.blocks = std::max(f.blocks, blocks_);
-        (void)hipEventRecord(f.done, stream_);
+        if (!carried_) (void)hipEventRecord(f.done, stream_);
+    }
+    // The event for the last launch to carry (hipExtLaunchKernelGGL), which then is not recorded here.
+    hipEvent_t event_to_carry()
+    {
+        carried_ = listed_;
+        return listed_ ? g_flights[at_].done : nullptr;
     }
     ea_status status() const { return st_; }
 
@@ -719,10 +731,12 @@ private:
     ea_status admit(int device, int n_cu)
     {
         int others = 0;
+        size_t vacant = g_flights.size();
         at_ = g_flights.size();
         for (size_t i = 0; i < g_flights.size(); ++i) {
             if (g_flights[i].device != device) continue;
             if (g_flights[i].stream == stream_) at_ = i;
+            else if (!g_flights[i].stream) vacant = i;
             else others += g_flights[i].blocks;
         }
         if (others + blocks_ > n_cu)
@@ -730,9 +744,13 @@ private:
                 if (f.device == device && f.stream != stream_ && !flight_over(f))
                     EA_HIP(hipStreamWaitEvent(stream_, f.done, 0));
         if (at_ == g_flights.size()) {
-            Flight f{stream_, device, 0, nullptr};
-            EA_HIP(hipEventCreateWithFlags(&f.done, hipEventDisableTiming));
-            g_flights.push_back(f);
+            at_ = vacant;
+            if (at_ == g_flights.size()) {
+                Flight f{stream_, device, 0, nullptr};
+                EA_HIP(hipEventCreateWithFlags(&f.done, hipEventDisableTiming | hipEventDisableSystemFence));
+                g_flights.push_back(f);
+            }
+            g_flights[at_].stream = stream_;
         } else if (g_flights[at_].blocks > blocks_) {
             (void)flight_over(g_flights[at_]);
         }
@@ -743,7 +761,7 @@ private:
     hipStream_t stream_;
     int blocks_;
     size_t at_ = 0;
-    bool listed_ = false;
+    bool listed_ = false, carried_ = false;
     ea_status st_ = EA_OK;
     std::unique_lock<std::mutex> lk_;
 };
@@ -753,13 +771,16 @@ private:
 void forget_flights(hipStream_t stream)
 {
     std::lock_guard<std::mutex> lk(g_flight_mu);
-    for (size_t i = 0; i < g_flights.size();) {
-        if (g_flights[i].stream != stream || !flight_over(g_flights[i])) {
-            ++i;
-            continue;
-        }
+    size_t free_now = 0;
+    for (Flight &f : g_flights) {
+        if (f.stream == stream && flight_over(f)) f.stream = nullptr;
+        free_now += f.stream ? 0 : 1;
+    }
+    for (size_t i = g_flights.size(); free_now > kFreeFlights && i-- > 0;) {
+        if (g_flights[i].stream) continue;
         (void)hipEventDestroy(g_flights[i].done);
         g_flights.erase(g_flights.begin() + (long)i);
+        --free_now;
     }
 }
 
@@ -845,13 +866,15 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
             d.serial = (uint32_t)m->xserial;
             m->xserial += n_cycles + 1;
         }
-        const dim3 grid((unsigned)plan.B);
+        const dim3 grid((unsigned)plan.B), block(ea::kSlabThreads);
+        // the last launch carries the flight's event itself
+        const hipEvent_t stop = done + chunk == sweeps ? flight.event_to_carry() : nullptr;
         if (span) {
-            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, true>), grid, dim3(ea::kSlabThreads),
-                                                  lds, lead->stream, a));
+            EA_DISPATCH_W(y.W, hipExtLaunchKernelGGL((ea::slab_sweep_kernel<WW, true>), grid, block, (uint32_t)lds,
+                                                     lead->stream, nullptr, stop, 0, a));
         } else {
-            EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::slab_sweep_kernel<WW, false>), grid, dim3(ea::kSlabThreads),
-                                                  lds, lead->stream, a));
+            EA_DISPATCH_W(y.W, hipExtLaunchKernelGGL((ea::slab_sweep_kernel<WW, false>), grid, block, (uint32_t)lds,
+                                                     lead->stream, nullptr, stop, 0, a));
         }
         EA_HIP(hipGetLastError());
         done += chunk;
