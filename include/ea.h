@@ -176,7 +176,8 @@ ea_status ea_words_per_row(const ea_sim *sim, int32_t *rw);
  * scratch buffer of 8 (2 L^2 ceil(L/64) + 3 (L/2)^2 + 1) bytes on the first
  * call, and on the first FFT-route call one of at most 8 L^2 (L + 16) + 256 bytes
  * (136 MiB at L = 256), both kept until ea_destroy.  EA_ERR_ARG for n_shells outside
- * [1, 3 (L/2)^2 + 1]; EA_ERR_NOMEM if a scratch buffer cannot be allocated;
+ * [1, 3 (L/2)^2 + 1]; EA_ERR_NOMEM if a scratch buffer cannot be allocated
+ * (see ea_set_shell_route for the FFT route's);
  * EA_ERR_DEVICE if a sum of the FFT route is not within 1/4 of an integer
  * (outside the fp64 error bound, which is below 1e-7 here). */
 ea_status ea_c4_shells(ea_sim *sim, int32_t n_shells, int64_t *out);
@@ -186,8 +187,9 @@ ea_status ea_c4_shells(ea_sim *sim, int32_t n_shells, int64_t *out);
  *   EA_SHELLS_AUTO    the FFT route for L >= 48, else direct (the default);
  *   EA_SHELLS_DIRECT  the direct route for every L;
  *   EA_SHELLS_FFT     the FFT route for every L.
- * Both routes give identical results.  Where L is neither 2^k nor 3 2^k and the
- * FFT route's scratch cannot be allocated, a call takes the direct route.
+ * Both routes give identical results.  Where the FFT route's scratch cannot be
+ * allocated, a call takes the direct route; with EA_SHELLS_FFT and L = 2^k or
+ * 3 2^k it returns EA_ERR_NOMEM.
  * Process-wide, read at each call.
  * EA_ERR_ARG for another value. */
 enum { EA_SHELLS_AUTO = 0, EA_SHELLS_DIRECT = 1, EA_SHELLS_FFT = 2 };

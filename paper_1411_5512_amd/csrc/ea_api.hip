@@ -933,6 +933,11 @@ bool shells_by_fft(int L)
     return r == EA_SHELLS_FFT || L >= kFftAutoMinL;
 }
 
+// Where the FFT route's scratch cannot be had, a call takes the direct route,
+// unless the caller asked for the FFT route at a side (2^k, 3 2^k) whose answer
+// to that has always been EA_ERR_NOMEM.
+bool shells_may_fall_back(int L) { return g_shell_route.load() != EA_SHELLS_FFT || ea::fft_general_side(L); }
+
 // Device scratch of a handle's full-vector C4 calls (ea_batch_c4_shells,
 // ea_msc_c4_shells): allocated on the first call, grown when a call needs
 // more, freed with the handle.  The calls synchronise before they return, so
@@ -1483,20 +1488,20 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
         hipError_t e = device_alloc(&s->c4_scratch, 8 * (q_words + (size_t)max_shells));
         if (e != hipSuccess) return fail(EA_ERR_NOMEM, "hipMalloc(c4 scratch): %s", hipGetErrorString(e));
     }
-    unsigned long long *qd = s->c4_scratch, *shells = s->c4_scratch + q_words;
-    ea::Geom g = s->geom();
-    EA_DISPATCH_W(s->lay.W, hipLaunchKernelGGL((ea::dense_q_kernel<WW>), dim3(blocks_for(q_words)), dim3(256), 0,
-                                               s->stream, s->lat, g, dw, qd));
     bool fft = shells_by_fft(L);
     if (fft && !s->fft_work) {
         hipError_t e = device_alloc(&s->fft_work, fft_work_bytes(L));
         if (e != hipSuccess) {
-            if (!ea::fft_general_side(L))
+            if (!shells_may_fall_back(L))
                 return fail(EA_ERR_NOMEM, "hipMalloc(c4 FFT work, %zu bytes): %s", fft_work_bytes(L),
                             hipGetErrorString(e));
-            fft = false;  // sides that once had only the direct route keep it where memory is short
+            fft = false;
         }
     }
+    unsigned long long *qd = s->c4_scratch, *shells = s->c4_scratch + q_words;
+    ea::Geom g = s->geom();
+    EA_DISPATCH_W(s->lay.W, hipLaunchKernelGGL((ea::dense_q_kernel<WW>), dim3(blocks_for(q_words)), dim3(256), 0,
+                                               s->stream, s->lat, g, dw, qd));
     if (!fft)
         hipLaunchKernelGGL(ea::zero_u64_kernel, dim3(blocks_for((size_t)n_shells)), dim3(256), 0, s->stream, shells,
                            (size_t)n_shells);

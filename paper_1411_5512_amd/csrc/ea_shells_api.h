@@ -29,8 +29,7 @@ ea_status shell_scratch(ShellScratch &sc, int L, int n_shells, unsigned long lon
     size_t fft_bytes = shells_by_fft(L) ? fft_work_bytes(L) : 0;
     const size_t words = q_words + (size_t)n_shells, head = (8 * words + 255) / 256 * 256;
     ea_status st = sc.reserve(head + fft_bytes);
-    if (st != EA_OK && fft_bytes && ea::fft_general_side(L)) {
-        // sides that once had only the direct route keep it where memory is short
+    if (st != EA_OK && fft_bytes && shells_may_fall_back(L)) {
         fft_bytes = 0;
         st = sc.reserve(head);
     }
