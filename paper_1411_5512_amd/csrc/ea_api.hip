@@ -1773,22 +1773,52 @@ namespace {
 
 // Device bytes in which a run's int8 arrays are converted: the slab exchange
 // area, which is idle between launches (and cleared before the next one), or
-// for lattices without one a buffer kept from the first call on.
-ea_status io_buffer(ea_sim *s, char **buf, size_t *bytes)
+// for lattices without one a buffer kept from the first call on.  False if
+// there is no room for that one.
+bool io_buffer(ea_sim *s, char **buf, size_t *bytes)
 {
     if (s->xbuf) {
         s->xbuf_clean = false;
         *buf = (char *)s->xbuf;
         *bytes = 8 * s->lay.xbuf_entries;
-        return EA_OK;
+        return true;
     }
     *bytes = (size_t)s->lay.L * s->lay.L * s->lay.L;
-    if (!s->io) {
-        const hipError_t e = device_alloc(&s->io, *bytes);
-        if (e != hipSuccess)
-            return fail(EA_ERR_NOMEM, "hipMalloc(conversion buffer, %zu bytes): %s", *bytes, hipGetErrorString(e));
-    }
+    if (!s->io && device_alloc(&s->io, *bytes) != hipSuccess) return false;
     *buf = (char *)s->io;
+    return true;
+}
+
+// The conversions on the host, for lattices that could get no such buffer.
+template <int ND>
+ea_status host_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
+{
+    const Layout &y = s->lay;
+    std::vector<uint32_t> words(2 * (size_t)ND * (size_t)y.plane);
+    EA_HIP(hipMemcpyAsync(words.data(), planes, 4 * words.size(), hipMemcpyDeviceToHost, s->stream));
+    EA_HIP(hipStreamSynchronize(s->stream));
+    const int64_t N = (int64_t)y.L * y.L * y.L;
+    for (int64_t i = 0; i < N; ++i) {
+        const SiteAddr a = address_of(y, i);
+        for (int d = 0; d < ND; ++d)
+            pm1[ND * i + d] = (words[(size_t)(2 * d + a.c) * (size_t)y.plane + a.word] >> a.bit) & 1u ? (int8_t)-1 : (int8_t)1;
+    }
+    return EA_OK;
+}
+
+template <int ND>
+ea_status host_pm1_in(ea_sim *s, uint32_t *planes, const int8_t *pm1)
+{
+    const Layout &y = s->lay;
+    std::vector<uint32_t> words(2 * (size_t)ND * (size_t)y.plane, 0u);
+    const int64_t N = (int64_t)y.L * y.L * y.L;
+    for (int64_t i = 0; i < N; ++i) {
+        const SiteAddr a = address_of(y, i);
+        for (int d = 0; d < ND; ++d)
+            if (pm1[ND * i + d] < 0) words[(size_t)(2 * d + a.c) * (size_t)y.plane + a.word] |= 1u << a.bit;
+    }
+    EA_HIP(hipMemcpyAsync(planes, words.data(), 4 * words.size(), hipMemcpyHostToDevice, s->stream));
+    EA_HIP(hipStreamSynchronize(s->stream));
     return EA_OK;
 }
 
@@ -1811,8 +1841,10 @@ ea_status copy_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
         return st;
     }
     size_t cap = 0;
-    ea_status st = io_buffer(s, &buf, &cap);
-    if (st != EA_OK) return st;
+    if (!io_buffer(s, &buf, &cap)) {
+        const ea_status st = host_pm1_out<ND>(s, planes, pm1);
+        return st == EA_OK ? sync_and_check(s) : st;
+    }
     const int step = (int)std::min<size_t>((size_t)y.rows, cap / row_bytes);
     for (int row = 0; row < y.rows; row += step) {
         const int n = std::min(step, y.rows - row);
@@ -1830,8 +1862,7 @@ ea_status copy_pm1_in(ea_sim *s, uint32_t *planes, const int8_t *pm1)
 {
     char *buf = nullptr;
     size_t cap = 0;
-    ea_status st = io_buffer(s, &buf, &cap);
-    if (st != EA_OK) return st;
+    if (!io_buffer(s, &buf, &cap)) return host_pm1_in<ND>(s, planes, pm1);
     const Layout &y = s->lay;
     const ea::Geom g = s->geom();
     const size_t row_bytes = (size_t)ND * (size_t)y.L;

@@ -96,3 +96,25 @@ for L in (64, 72):
         except ea.abi.EAError as e:
             assert L == 64 and e.status == ea.abi.EA_ERR_NOMEM, (L, e)
 """)
+
+
+def test_spins_and_couplings_without_a_conversion_buffer(ea_gpu, tmp_path):
+    """A packing too fine for the slab path has no exchange area to convert
+    in; where there is no room for a buffer either, the arrays still pass."""
+    _run(tmp_path, """
+L, rw = 96, 12
+a = ea.Sim(L, 0.4, 0.8, seed=3, words_per_row=rw); a.sweep(3)
+ref = ea.Sim(L, 0.4, 0.8, seed=3); ref.sweep(3)
+rng = np.random.default_rng(1)
+spins = rng.choice(np.array([-1, 1], dtype=np.int8), size=L ** 3)
+bonds = rng.choice(np.array([-1, 1], dtype=np.int8), size=3 * L ** 3)
+with short(400_000):
+    assert all(np.array_equal(a.spins(r), ref.spins(r)) for r in (0, 1)) and refused.value == 2
+    assert np.array_equal(a.bonds().ravel(), ref.bonds().ravel())
+    a.set_spins(1, spins); a.set_bonds(bonds)
+    assert refused.value == 5, refused.value
+ref.set_spins(1, spins); ref.set_bonds(bonds)
+assert np.array_equal(a.spins(1), spins) and np.array_equal(a.bonds().ravel(), bonds)
+a.sweep(2); ref.sweep(2)
+assert all(np.array_equal(a.spins(r), ref.spins(r)) for r in (0, 1))
+""")
