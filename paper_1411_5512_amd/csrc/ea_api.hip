@@ -1822,6 +1822,16 @@ ea_status host_pm1_in(ea_sim *s, uint32_t *planes, const int8_t *pm1)
     return EA_OK;
 }
 
+// The end of a copy to the caller: spins are undefined after a slab launch
+// that gave up, couplings are not.
+template <int ND>
+ea_status sync_copied(ea_sim *s)
+{
+    if constexpr (ND == 1) return sync_and_check(s);
+    EA_HIP(hipStreamSynchronize(s->stream));
+    return EA_OK;
+}
+
 // Packed planes to the caller's array and back, nd bytes per site, as many
 // rows at a time as the buffer holds.  Both wait for the stream.
 template <int ND>
@@ -1836,14 +1846,14 @@ ea_status copy_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
         EA_DISPATCH_W(y.W, hipLaunchKernelGGL((ea::to_pm1_kernel<WW, ND>), dim3(blocks_for((size_t)y.rows * (y.L / 8))),
                                               dim3(256), 0, s->stream, planes, g, 0, y.rows, (uint2 *)buf));
         EA_HIP(hipGetLastError());
-        ea_status st = sync_and_check(s);
-        std::memcpy(pm1, buf, n_bytes);
+        ea_status st = sync_copied<ND>(s);
+        if (st == EA_OK) std::memcpy(pm1, buf, n_bytes);
         return st;
     }
     size_t cap = 0;
     if (!io_buffer(s, &buf, &cap)) {
         const ea_status st = host_pm1_out<ND>(s, planes, pm1);
-        return st == EA_OK ? sync_and_check(s) : st;
+        return st == EA_OK ? sync_copied<ND>(s) : st;
     }
     const int step = (int)std::min<size_t>((size_t)y.rows, cap / row_bytes);
     for (int row = 0; row < y.rows; row += step) {
@@ -1854,7 +1864,7 @@ ea_status copy_pm1_out(ea_sim *s, const uint32_t *planes, int8_t *pm1)
         EA_HIP(hipMemcpyAsync(pm1 + (size_t)row * row_bytes, buf, (size_t)n * row_bytes, hipMemcpyDeviceToHost,
                               s->stream));
     }
-    return sync_and_check(s);
+    return sync_copied<ND>(s);
 }
 
 template <int ND>

@@ -53,3 +53,43 @@ def test_allocation_failure_does_not_stay_pending(ea_gpu):
     s.sweep(1)
     s.sync()
     s.close()
+
+
+@pytest.mark.parametrize("L", [8, 16, 40])
+def test_couplings_after_a_launch_that_gave_up(ea_gpu, L):
+    """A slab launch that gave up leaves the spins undefined, not the couplings.
+    The error word is set from here; it lies 192 bytes before the exchange
+    area, the last part of the caller's buffer, of 32 bytes per word of a plane
+    and slot."""
+    s = ea_gpu.Sim(L, 0.4, 0.8, seed=5)
+    s.sweep(1)
+    s.sync()
+    want = s.bonds()
+    plane = L * L * s.words_per_row
+    aligned = (s._buf.data_ptr() + 255) // 256 * 256 - s._buf.data_ptr()
+    end = aligned + s._buf.numel() - 256
+    gave_up = False
+    for slots in range(1, 9):
+        at = end - 32 * plane * slots - 192
+        s._buf[at] = 1
+        try:
+            s.sync()
+        except ea_gpu.abi.EAError as e:
+            gave_up = e.status == ea_gpu.abi.EA_ERR_DEVICE
+            break
+    assert gave_up
+    for call in (s.measure, lambda: s.spins(0)):
+        with pytest.raises(ea_gpu.abi.EAError):
+            call()
+    assert np.array_equal(s.bonds(), want)
+    s.set_bonds(-want)
+    assert np.array_equal(s.bonds(), -want)
+    # a reset clears the word, and the counters with it
+    s.reset(seed=5, sample=0)
+    t = ea_gpu.Sim(L, 0.4, 0.8, seed=5)
+    s.sweep(4)
+    t.sweep(4)
+    _same(s.measure(), t.measure())
+    assert np.array_equal(s.bonds(), want) and all(np.array_equal(s.spins(r), t.spins(r)) for r in (0, 1))
+    s.close()
+    t.close()
