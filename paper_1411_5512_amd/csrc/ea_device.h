@@ -407,7 +407,7 @@ __device__ __forceinline__ uint32_t append_below8(uint32_t accept, const uint32_
                  "v_addc_co_u32_e64 %0, %5, %0, %0, %3\n\t"
                  "v_addc_co_u32_e64 %0, %5, %0, %0, %4\n\t"
                  "s_setprio 0"
-                 : "+v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
+                 : "+&v"(accept), "=&s"(m3), "=&s"(m2), "=&s"(m1), "=&s"(m0), "=&s"(co)
                  : "v"(a[3]), "v"(ta.w), "v"(a[2]), "v"(ta.z), "v"(a[1]), "v"(ta.y), "v"(a[0]), "v"(ta.x),
                    "v"(b[3]), "v"(tb.w), "v"(b[2]), "v"(tb.z), "v"(b[1]), "v"(tb.y), "v"(b[0]), "v"(tb.x));
     return accept;
