@@ -377,23 +377,39 @@ void debug_order_units(const JobRef *jobs, std::vector<ea::BatchUnit> &units)
 // slabs all fit the device at once (one per CU, so that both workgroups of
 // every pair are dispatched at the start), the in-order dispatch of the
 // resulting unit list onto n_cu one-unit CUs is simulated and the threshold
-// with the shortest estimated makespan is kept.  Time model per half-step
-// (measured on MI355X): a whole replica takes kHalfStepL64 (L/64)^kSizeExp
-// (smaller lattices use a CU less fully than the site count alone says); a
-// slab takes half of that plus kSlabExchange for the boundary exchange (wait,
-// remote reads, publication): whole / slab 4.5 / 2.97 us at L = 48, 8.2 / 4.07 at
-// 56, 9.2 / 5.38 at 64.  Only jobs in their default launch configuration (the
-// slab kernel exists for that one) split.
-constexpr double kHalfStepL64 = 9.2e-6;
-constexpr double kSizeExp = 2.5;  // L = 48 measured at 0.49 of L = 64
-constexpr double kSlabExchange = 0.75e-6;
+// with the shortest estimated makespan is kept.  Only jobs in their default
+// launch configuration (the slab kernel exists for that one) split.
+//
+// Time model per half-step, from figures measured on a full MI355X.  A SIMD
+// takes kWord + kWordSite W for a word of W sites (the fixed part is the
+// lattice reads and the decision), but a half-step at least kChain +
+// kChainSite W, one wave's chain.  A whole replica's threads walk nz planes
+// each, so planes come in groups: at L = 56 14 groups of 4 keep 13 of 16 waves
+// busy, on SIMDs of 3 and of 4, and a half-step takes between the mean load
+// and the largest.  (A power of L misses that: with 9.2 us (L/64)^2.5, L = 56
+// was priced at 6.6.)  A slab's words spread evenly; kSlabExchange covers its
+// boundary exchange (wait, remote reads, publication).  Model / measured, us:
+// whole L = 16 0.61 / 0.61, 24 1.01 / 1.14, 32 1.70 / 1.61, 40 3.38 / 3.41,
+// 48 4.56 / 4.69, 56 7.95 / 8.27, 64 9.43 / 9.28; slab L = 48 3.10 / 3.05,
+// 56 4.18 / 4.18, 64 5.54 / 5.59.
+constexpr double kWord = 0.26e-6, kWordSite = 0.0103e-6;
+constexpr double kChain = 0.33e-6, kChainSite = 0.035e-6;
+constexpr double kSlabExchange = 0.82e-6;
+
+double half_step_seconds(const BatchJobHost &h, bool slab)
+{
+    const int L = h.job.L, plane = L * h.RW;
+    const double word = kWord + kWordSite * h.W;
+    if (slab) return word * (L / 2) * plane / 256.0 + kSlabExchange;
+    const int groups = h.cfg.nt / plane, nz = (L + groups - 1) / groups;
+    const int waves = ((L + nz - 1) / nz * plane + 63) / 64;
+    const double load = 0.5 * (waves / 4.0 + (waves + 3) / 4);
+    return std::max(word * nz * load, kChain + kChainSite * h.W);
+}
 
 double unit_seconds(const BatchJobHost &h, bool slab)
 {
-    const double x = (double)h.job.L / 64.0;
-    const double whole = kHalfStepL64 * std::pow(x, kSizeExp);
-    const double per_half = slab ? 0.5 * whole + kSlabExchange : whole;
-    return 2.0 * (double)std::max<uint64_t>(1, h.job.n_sweeps) * per_half;
+    return 2.0 * (double)std::max<uint64_t>(1, h.job.n_sweeps) * half_step_seconds(h, slab);
 }
 
 double simulate_dispatch(const std::vector<std::pair<double, int>> &units, int n_cu)
