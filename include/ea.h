@@ -184,7 +184,8 @@ ea_status ea_c4_shells(ea_sim *sim, int32_t n_shells, int64_t *out);
 
 /* Route of the full-vector C4 shells (ea_c4_shells, ea_batch_c4_shells,
  * ea_msc_c4_shells; ea_c4_shells_into always takes the direct route):
- *   EA_SHELLS_AUTO    the FFT route for L >= 48, else direct (the default);
+ *   EA_SHELLS_AUTO    the FFT route for L >= 48, else, and for few shells of
+ *                     L <= 88, direct (the default);
  *   EA_SHELLS_DIRECT  the direct route for every L;
  *   EA_SHELLS_FFT     the FFT route for every L.
  * Both routes give identical results.  Where the FFT route's scratch cannot be

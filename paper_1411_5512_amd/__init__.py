@@ -51,8 +51,8 @@ SHELLS_AUTO, SHELLS_DIRECT, SHELLS_FFT = 0, 1, 2
 
 def set_shell_route(route: int = SHELLS_AUTO) -> None:
     """Route of the full-vector C4 shells (ea_set_shell_route): automatic
-    (FFT for L >= 48), direct bit counting, or FFT for every L.  Both give
-    identical results."""
+    (FFT for L >= 48 unless few shells are wanted), direct bit counting, or
+    FFT for every L.  Both give identical results."""
     abi.check(abi.lib().ea_set_shell_route(int(route)))
 
 

@@ -921,16 +921,28 @@ ea_status launch_shell_rows(const unsigned long long *qd, int L, int n_shells, u
 
 // Route of the full-vector C4 shells (ea_set_shell_route).
 std::atomic<int32_t> g_shell_route{EA_SHELLS_AUTO};
-// automatic route: FFT from this side on.  A call, direct against FFT: L = 32
-// 57 / 79 us, L = 48 112 / 84, L = 72 876 / 109, L = 128 15.9 ms / 0.14, L = 136
-// 22 ms / 0.23, L = 256 863 ms / 0.37.
+// Automatic route: FFT from this side on, unless few shells are wanted.  All
+// shells |r| <= L/2, direct against FFT: L = 32 57 / 79 us, L = 48 110 / 65, L = 72
+// 823 / 96, L = 128 15.9 ms / 0.14, L = 136 22.4 ms / 0.22, L = 256 863 ms / 0.37.
 constexpr int kFftAutoMinL = 48;
 
-bool shells_by_fft(int L)
+// The direct kernel skips what lies beyond the last shell, the FFT route gives
+// them all.  Up to these many shells the direct call is the faster one, and it
+// takes no scratch array: L = 48 10 shells 45 / 63 us (a handle's first call
+// 58 / 96), 300 73 / 66; L = 56 30 60 / 77, 100 77 / 77; L = 72 30 83 / 91, 100
+// 106 / 91; L = 88 10 113 / 110 (115 / 182); from L = 104 on 2 shells 151 / 133.
+// (L = 64, where both are within 6 us up to 30 shells, is left to the FFT.)
+bool few_shells(int L, int n_shells)
+{
+    const double x = L / 48.0;
+    return L <= 88 && L != 64 && n_shells * x * x * x * x * x <= 220.0;
+}
+
+bool shells_by_fft(int L, int n_shells)
 {
     const int32_t r = g_shell_route.load();
     if (r == EA_SHELLS_DIRECT) return false;
-    return r == EA_SHELLS_FFT || L >= kFftAutoMinL;
+    return r == EA_SHELLS_FFT || (L >= kFftAutoMinL && !few_shells(L, n_shells));
 }
 
 // Where the FFT route's scratch cannot be had, a call takes the direct route,
@@ -1488,7 +1500,7 @@ ea_status ea_c4_shells(ea_sim *s, int32_t n_shells, int64_t *out)
         hipError_t e = device_alloc(&s->c4_scratch, 8 * (q_words + (size_t)max_shells));
         if (e != hipSuccess) return fail(EA_ERR_NOMEM, "hipMalloc(c4 scratch): %s", hipGetErrorString(e));
     }
-    bool fft = shells_by_fft(L);
+    bool fft = shells_by_fft(L, n_shells);
     if (fft && !s->fft_work) {
         hipError_t e = device_alloc(&s->fft_work, fft_work_bytes(L));
         if (e != hipSuccess) {

@@ -26,7 +26,7 @@ ea_status shell_scratch(ShellScratch &sc, int L, int n_shells, unsigned long lon
 {
     *dw = 2 * ((L + 63) / 64);
     const size_t q_words = (size_t)L * L * (size_t)*dw;
-    size_t fft_bytes = shells_by_fft(L) ? fft_work_bytes(L) : 0;
+    size_t fft_bytes = shells_by_fft(L, n_shells) ? fft_work_bytes(L) : 0;
     const size_t words = q_words + (size_t)n_shells, head = (8 * words + 255) / 256 * 256;
     ea_status st = sc.reserve(head + fft_bytes);
     if (st != EA_OK && fft_bytes && shells_may_fall_back(L)) {

@@ -118,3 +118,23 @@ assert np.array_equal(a.spins(1), spins) and np.array_equal(a.bonds().ravel(), b
 a.sweep(2); ref.sweep(2)
 assert all(np.array_equal(a.spins(r), ref.spins(r)) for r in (0, 1))
 """)
+
+
+def test_few_shells_take_no_scratch_array(ea_gpu, tmp_path):
+    """Where the direct count of a few shells is the faster call, the automatic
+    route makes it and asks for no FFT scratch; past the line it is the FFT."""
+    _run(tmp_path, """
+for L, few in ((48, 220), (56, 101), (72, 28), (80, 17), (88, 10)):
+    want = ea.Sim(L, 0.4, 0.8, seed=L); want.sweep(5)
+    w = want.c4_shells()
+    for n, asked in ((1, 0), (few, 0), (few + 1, 1)):
+        s = ea.Sim(L, 0.4, 0.8, seed=L); s.sweep(5)
+        with short(600_000):
+            got = s.c4_shells(n)
+            assert refused.value == asked, (L, n, refused.value)
+        assert np.array_equal(got, w[:n]), (L, n)
+s = ea.Sim(64, 0.4, 0.8, seed=64)
+with short(600_000):
+    s.c4_shells(1)
+    assert refused.value == 1
+""")
