@@ -53,12 +53,12 @@ struct BatchJobHost {
     uint32_t *err = nullptr;  // device word a split pair sets when it gives up waiting
     char *base = nullptr;     // device region of this job
     uint64_t t_host = 0;      // sweeps done (host mirror)
-    std::vector<unsigned long long> obs_host;  // the counters of every measurement, once fetched
-    bool obs_fetched = false; // since the last launch or reset
+    std::vector<unsigned long long> obs_host;  // the counters of measurements [obs_lo, obs_hi)
+    size_t obs_lo = 0, obs_hi = 0;             // (final once reached, until a reset)
     bool started = false;     // a span has run (events at t = 0 are taken)
 };
 
-constexpr size_t kObsFetchBytes = 1 << 20;  // results of one job fetched in one copy, at most
+constexpr size_t kObsFetchBytes = 1 << 17;  // results of one job fetched in one copy, at most
 
 bool batch_L_ok(int L) { return L >= 8 && L <= ea::kBatchMaxL && L % 8 == 0; }
 
@@ -243,7 +243,7 @@ ea_status init_job_device(BatchJobHost &h, hipStream_t stream)
     EA_HIP(hipGetLastError());
     h.t_host = 0;
     h.started = false;
-    h.obs_fetched = false;
+    h.obs_lo = h.obs_hi = 0;
     return EA_OK;
 }
 
@@ -827,7 +827,7 @@ ea_status reset_batch_device(ea_batch *b)
         pos = std::max(pos, h.POS);
         h.t_host = 0;
         h.started = false;
-        h.obs_fetched = false;
+        h.obs_lo = h.obs_hi = 0;
     }
     hipLaunchKernelGGL(ea::batch_reset_kernel, dim3((unsigned)b->jobs.size(), 10, blocks_for((size_t)pos)), dim3(256), 0,
                        b->stream, b->d_jobs, b->d_err);
@@ -954,7 +954,6 @@ ea_status ea_batch_run(ea_batch *b, uint64_t t_stop)
     for (auto &h : b->jobs) {
         h.t_host = std::max<uint64_t>(h.t_host, std::min<uint64_t>(t_stop, h.job.n_sweeps));
         h.started = true;
-        h.obs_fetched = false;
     }
     // the unit table is read by the kernel: keep the host copy stable until it ran
     EA_HIP(hipStreamSynchronize(b->stream));
@@ -1009,7 +1008,7 @@ ea_status ea_batch_replay(ea_batch *b)
     for (auto &h : b->jobs) {
         h.t_host = h.job.n_sweeps;
         h.started = true;
-        h.obs_fetched = false;
+        h.obs_lo = h.obs_hi = 0;
     }
     return check_batch_err(b);
 }
@@ -1030,18 +1029,21 @@ ea_status ea_batch_result(ea_batch *b, int32_t job, int32_t k, ea_obs *out)
     if (k < 0 || k >= h.job.n_meas) return fail(EA_ERR_ARG, "measurement %d out of range", k);
     if (h.meas_t[(size_t)k] > h.t_host || !h.started)
         return fail(EA_ERR_STATE, "measurement %d (t=%u) not reached", k, h.meas_t[(size_t)k]);
-    // a caller reads a job's measurements one after the other: one copy brings
-    // them all (15 us a copy, whatever its size here), unless they are many
-    const size_t stride = (size_t)h.obs_stride, all = (size_t)h.job.n_meas * stride;
-    const bool whole = 8 * all <= kObsFetchBytes;
-    if (!whole || !h.obs_fetched) {
-        h.obs_host.resize(whole ? all : stride);
-        EA_HIP(hipMemcpyAsync(h.obs_host.data(), h.base + h.off_obs + (whole ? 0 : 8 * (size_t)k * stride),
-                              8 * h.obs_host.size(), hipMemcpyDeviceToHost, b->stream));
+    // a caller reads a job's measurements one after the other: a copy brings
+    // those reached from k on (15 us a copy, whatever its size here)
+    const size_t stride = (size_t)h.obs_stride, at = (size_t)k;
+    if (at < h.obs_lo || at >= h.obs_hi) {
+        const size_t reached = (size_t)(std::upper_bound(h.meas_t.begin(), h.meas_t.end(), (uint64_t)h.t_host) -
+                                        h.meas_t.begin());
+        const size_t n = std::min(reached - at, std::max<size_t>(1, kObsFetchBytes / (8 * stride)));
+        h.obs_lo = h.obs_hi = at;
+        h.obs_host.resize(n * stride);
+        EA_HIP(hipMemcpyAsync(h.obs_host.data(), h.base + h.off_obs + 8 * at * stride, 8 * n * stride,
+                              hipMemcpyDeviceToHost, b->stream));
         EA_HIP(hipStreamSynchronize(b->stream));
-        h.obs_fetched = whole;
+        h.obs_hi = at + n;
     }
-    return fill_obs(h, h.obs_host.data() + (whole ? (size_t)k * stride : 0), k, out);
+    return fill_obs(h, h.obs_host.data() + (at - h.obs_lo) * stride, k, out);
 }
 
 ea_status ea_batch_parts(ea_batch *b, int32_t job, int32_t *parts)
