@@ -634,11 +634,9 @@ ea_status slab_choose(int L, int rw, int n_runs, int K_req, int g_req, SlabPlan 
         const double c = slab_model_us(L, rw, (int)((P + B - 1) / B), g);
         if (found && c >= best) return;
         if (!slab_plan_fits(L, rw, n_runs, B, g, n_cu, lds_limit, &p)) return;
-        {
-            best = c;
-            *plan = p;
-            found = true;
-        }
+        best = c;
+        *plan = p;
+        found = true;
     };
     const int g_lo = g_req > 0 ? g_req : 1, g_hi = g_req > 0 ? g_req : 4;
     if (K_req > 0) {
@@ -869,13 +867,11 @@ ea_status launch_slab(ea_sim *const *runs, int n, uint64_t sweeps, const SlabPla
         const dim3 grid((unsigned)plan.B), block(ea::kSlabThreads);
         // the last launch carries the flight's event itself
         const hipEvent_t stop = done + chunk == sweeps ? flight.event_to_carry() : nullptr;
-        if (span) {
-            EA_DISPATCH_W(y.W, hipExtLaunchKernelGGL((ea::slab_sweep_kernel<WW, true>), grid, block, (uint32_t)lds,
-                                                     lead->stream, nullptr, stop, 0, a));
-        } else {
-            EA_DISPATCH_W(y.W, hipExtLaunchKernelGGL((ea::slab_sweep_kernel<WW, false>), grid, block, (uint32_t)lds,
-                                                     lead->stream, nullptr, stop, 0, a));
-        }
+        auto launch = [&](void (*kernel)(ea::SlabLaunch)) {
+            if (stop) hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, lead->stream, nullptr, stop, 0, a);
+            else hipLaunchKernelGGL(kernel, grid, block, lds, lead->stream, a);
+        };
+        EA_DISPATCH_W(y.W, launch(span ? ea::slab_sweep_kernel<WW, true> : ea::slab_sweep_kernel<WW, false>));
         EA_HIP(hipGetLastError());
         done += chunk;
     }

@@ -518,14 +518,15 @@ __device__ void batch_run_unit(const BatchJobDev &J, int r, uint32_t t_stop, boo
 // other slab's adjacent plane (periodic in z), of the other colour; those
 // boundary words pass through a small exchange area in global memory.
 //
-// In each half-step wave 0 updates the slab's two boundary planes: it waits
-// until the partner slab has published its boundary words of the previous
-// half-step (a counter stored with release, read with acquire, agent scope),
-// updates its own boundary words and publishes them.  The other waves update
-// the interior planes meanwhile, which need nothing from the partner, so the
-// exchange latency hides behind interior work; the half-step still ends with
-// one workgroup barrier.  Publication counter of a slab: 1 once its state at
-// t = 0 is out, 2t + h + 2 after half-step h of sweep t.  Boundary words
+// In each half-step the first waves update the slab's two boundary planes, a
+// wave each (wave 0 both at L = 64, see slab_half_step): a wave waits until the
+// partner slab has published its plane next to this one in the previous
+// half-step (a counter per plane, agent scope), updates its words and publishes
+// them.  The other waves update the interior planes meanwhile, which need
+// nothing from the partner, so the exchange latency hides behind interior work;
+// the half-step still ends with one workgroup barrier.  Publication counter of
+// a plane: 1 once its state at t = 0 is out, 2t + h + 2 after half-step h of
+// sweep t.  Boundary words
 // written in sweep t go to slot t & 1 (the state at t = 0 to slot 1): a
 // measurement at t reads both colours of the partner's slot (t - 1) & 1
 // while the partner may already be writing sweep t into the other slot.  A wait gives up

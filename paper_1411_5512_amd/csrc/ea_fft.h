@@ -31,10 +31,10 @@ namespace ea {
 constexpr int kFftTile = 2048;  // complex elements held by one workgroup, at most
 constexpr int kFftThreads = 256;
 
-// The passes, in order: forward along x from the dense q rows, forward along
-// y, forward along z + |.|^2 + inverse along z, inverse along y, inverse along
+// The passes, in order: forward along x from the dense q rows
+// (fft_bits_kernel), forward along y, forward along z + |.|^2 + inverse along z, inverse along y, inverse along
 // x + rounding (fft_bin_kernel); then the shell sums (fft_shell_sum_kernel).
-enum FftOp { kFftFwdBitsX = 0, kFftFwdY = 1, kFftSquareZ = 2, kFftInvY = 3, kFftInvBinX = 4 };
+enum FftOp { kFftFwdY = 1, kFftSquareZ = 2, kFftInvY = 3 };  // the passes along y and z
 
 struct FftArgs {
     double2 *z;                    // element (kx <= L/2, y, z) at (z L + y) fft_stride(L) + kx
@@ -379,7 +379,7 @@ __device__ __forceinline__ double2 fft_unpack(double2 zk, double2 zm, bool secon
                   : make_double2(0.5 * (zk.x + zm.x), 0.5 * (zk.y - zm.y));
 }
 
-// The tile of pass kFftFwdBitsX before its transform: 2 B rows, packed in
+// The tile of the first pass before its transform: 2 B rows, packed in
 // pairs as complex lines LP apart.  Their words come through LDS: read where
 // the sites are expanded they were a chain of loads (the pass at L = 128 took
 // 19 us).
@@ -405,7 +405,7 @@ __device__ __forceinline__ void fft_clear(const FftArgs &a, int tid)
     if (blockIdx.x == 0 && tid == 0) *a.err = 0u;
 }
 
-// Pass kFftFwdBitsX: 2 B rows per workgroup, transformed in pairs.
+// The first pass: 2 B rows per workgroup, transformed in pairs.
 template <int L>
 __global__ __launch_bounds__(kFftThreads) void fft_bits_kernel(FftArgs a)
 {
@@ -674,7 +674,7 @@ __device__ __forceinline__ void fft_general_twiddles(double2 *tw, int L, int tid
 
 __device__ __forceinline__ int fft_general_place(const FftGeneral &f, int k) { return (k % f.m) * f.P + k / f.m; }
 
-// Pass kFftFwdBitsX (fft_bits_kernel).
+// The first pass (fft_bits_kernel).
 __global__ __launch_bounds__(kFftThreads) void fft_general_bits_kernel(FftArgs a, FftGeneral f)
 {
     __shared__ double2 s[kFftGeneralLds];

@@ -242,8 +242,8 @@ void server_slab_plan(ServerJob &j, int share)
 // An LDS-sized job (L >= kLoneStreamL) admitted while some worker has no
 // streamed job runs as a streamed job instead: alone in the batched kernel
 // its two replicas would hold two CUs for the whole run while the rest of
-// the device idles (an L = 64 job: 24.8 us per sweep there, about 2.3 us as
-// a slab job on many CUs).  Re-plans j.h for the plain form's layout and
+// the device idles (an L = 64 job: 18.6 us per sweep there, 2.1 us as a slab
+// job on many CUs; an L = 48 job 9.4).  Re-plans j.h for the plain form's layout and
 // returns true if it did.  Results never depend on the form.
 constexpr int kLoneStreamL = 48;
 
@@ -262,7 +262,7 @@ bool stream_small_job(const ea_server *s, ServerJob &j)
     return true;
 }
 
-// A batched job with at least this many site-sweeps left (about 50 ms of an
+// A batched job with at least this many site-sweeps left (about 37 ms of an
 // L = 64 job in the batched kernel) may move to the slab path.
 constexpr double kMoveMinSiteSweeps = 64.0 * 64 * 64 * 2000;
 

@@ -97,3 +97,27 @@ def test_a_listed_stream_can_be_captured(ea_gpu):
     a.sync()
     for s in (a, b, want):
         s.close()
+
+
+@pytest.mark.parametrize("L", [16, 64, 128])
+def test_a_captured_sweep_runs_at_its_replay(ea_gpu, L):
+    """Captured by the caller, a sweep does nothing until the graph runs, and
+    then what it does eagerly."""
+    import torch
+    a, want = (ea_gpu.Sim(L, 0.4, 0.8, seed=3) for _ in range(2))
+    for s in (a, want):
+        s.sweep(2)
+        s.sync()
+    before = [a.spins(r) for r in (0, 1)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=a._stream, capture_error_mode="thread_local"):
+        a.sweep(5)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(a.spins(r), before[r]) for r in (0, 1))
+    graph.replay()
+    torch.cuda.synchronize()
+    want.sweep(5)
+    want.sync()
+    assert all(np.array_equal(a.spins(r), want.spins(r)) for r in (0, 1))
+    a.close()
+    want.close()
