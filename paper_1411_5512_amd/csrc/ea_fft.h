@@ -5,19 +5,21 @@
 // of |F|^2 is N sum_x q(x) q(x + r) for every r at once.  Five passes over a
 // complex fp64 array of L^2 rows of L/2 + 1 elements, each transforming whole lines
 // of one axis in LDS, replace the direct kernel's L^6 / 64 word operations by
-// O(L^3 log L) flops and 56 bytes of HBM traffic per site.  q is real, so
+// O(L^3 log L) flops and 50 bytes of HBM traffic per site (56 with the
+// rows' padding at L = 128).  q is real, so
 // only the columns kx <= L/2 are kept between the passes along x, and those
 // two passes transform two real rows as one complex line.  At L = 128 the five
-// passes take 69 us (79 with all columns), a whole call 127 (158); each
-// workgroup's chain of load, transform and store bounds them, at about 2 TB/s.
+// passes take 69 us (79 with all columns), a whole call among others 122 (158);
+// each workgroup's chain of load, transform and store bounds them, at 1.1 to 2.9
+// TB/s.
 //
 // The forward transforms are decimation in frequency (natural order in,
 // digit-reversed order out along each axis: for L = 3P a radix-3 stage of
 // span P first, then radix-2 stages on each third) and the inverse ones
 // decimation in time (digit-reversed in, natural out: the same stages in the
 // opposite order); |F|^2 is taken pointwise in between, so only the passes
-// along x, which pair kx with L - kx, look an index up.  The autocorrelation is even, so the last two passes transform
-// only the planes z <= L/2.  The sums are integers of magnitude <= N and the
+// along x, which pair kx with L - kx, look an index up.  The autocorrelation is
+// even, so the last two passes transform only the planes z <= L/2.  The sums are integers of magnitude <= N and the
 // rounding error of the fp64 transforms is ~1e-16 log2(N) of the largest
 // |F|^2 (<= N^2), i.e. below 1e-7 after the division by N at L = 256: each
 // sum is rounded to the nearest integer, and a sum found farther than 1/4
@@ -32,8 +34,9 @@ constexpr int kFftTile = 2048;  // complex elements held by one workgroup, at mo
 constexpr int kFftThreads = 256;
 
 // The passes, in order: forward along x from the dense q rows
-// (fft_bits_kernel), forward along y, forward along z + |.|^2 + inverse along z, inverse along y, inverse along
-// x + rounding (fft_bin_kernel); then the shell sums (fft_shell_sum_kernel).
+// (fft_bits_kernel), forward along y, forward along z + |.|^2 + inverse along
+// z, inverse along y, inverse along x + rounding (fft_bin_kernel); then the
+// shell sums (fft_shell_sum_kernel).
 enum FftOp { kFftFwdY = 1, kFftSquareZ = 2, kFftInvY = 3 };  // the passes along y and z
 
 struct FftArgs {
@@ -589,8 +592,8 @@ __global__ __launch_bounds__(256) void fft_shell_sum_kernel(FftArgs a, int L)
 // over b, at k P + j -- X[k + m j] in an order of its own, which the inverse
 // takes as it is: P-point over j, conjugate twiddle, m-point over k.  m + P
 // complex multiply-adds an element and transform instead of L; the LDS reads
-// of a wave's inputs bound it.  A call against the direct count: L = 72 0.11 ms
-// (0.87), L = 136 0.23 (22).
+// of a wave's inputs bound it.  A call against the direct count: L = 72 0.10 ms
+// (0.82), L = 136 0.22 (22).
 struct FftGeneral {
     int L, m, P, B, LP;  // side = m P; lines per tile; LDS stride of a line
 };
